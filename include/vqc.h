@@ -149,9 +149,9 @@ typedef struct {
                               rows [B, P] */
     int32_t tile_qubits; /* streaming path: qubits per tile, 12, 13 or 14
                             (0 = the default: with the generated kernels 12,
-                            unless its plan takes more than a quarter more
-                            passes than 13, then 13; 14 with the
-                            interpreter).  Each qubit less halves a
+                            unless it takes more than a quarter more passes
+                            than 13, with the CNOTs as gates or without, then
+                            13; 14 with the interpreter).  Each qubit less halves a
                             workgroup's LDS, so more workgroups share a CU
                             and one's HBM traffic overlaps another's compute,
                             at the cost of more passes where the circuit
@@ -389,8 +389,10 @@ typedef struct {
     int32_t threads;        /* workgroup size */
     int32_t fwd_passes;     /* kernel passes of the forward (1 when resident) */
     int32_t bwd_passes;     /* kernel passes of the backward */
-    int32_t fwd_exchanges;  /* on-chip layout exchanges in the forward */
-    int32_t bwd_exchanges;  /* on-chip layout exchanges in the backward */
+    /* the schedule with every primitive as an instruction: its on-chip layout
+       exchanges and its length per sweep.  The generated kernels of circuits
+       of 9 or more qubits run no CNOTs and fewer exchanges than this */
+    int32_t fwd_exchanges, bwd_exchanges;
     int32_t fwd_instructions, bwd_instructions;
     int32_t lds_bytes_fwd, lds_bytes_bwd;
     int32_t engine;         /* VQC_ENGINE_* */

@@ -179,7 +179,14 @@ size_t fd_rows_bytes(const Plan& p, int64_t batch) {
 }
 
 size_t required_bytes(const vqc_circuit* c, int64_t batch, int mode) {
-  if (mode == 2 && c->step) c = c->step;  // the training step runs the step circuit
+  if (mode == 2 && c->step) {
+    // the training step runs the step circuit; its workspace also holds the
+    // other calls' (the whole circuit may take more passes, hence states)
+    vqc_circuit* const step = c->step;
+    size_t whole = required_bytes_core(c->plan, batch, 1) + (size_t)batch * c->plan.n * 4;
+    if (c->shared) whole = align_up(whole, 256) + (size_t)batch * c->plan.P * 4;
+    return std::max(batch ? whole : 0, required_bytes(step, batch, mode));
+  }
   const Plan& p = c->plan;
   if (batch == 0) return 0;
   if (mode == 3) return fd_rows_bytes(p, batch) + (c->shared ? (size_t)batch * p.P * 4 : 0);
@@ -589,24 +596,29 @@ int vqc_compile(const vqc_op* ops, int32_t n_ops, int32_t n_qubits, int32_t n_pa
   if (!c) return fail(VQC_ERR_OOM, "out of host memory");
   std::string msg;
   int rc = vqc::build_plan(hops, n_qubits, n_params, n_inputs, path, reg_bits, c->plan, msg,
-                           engine == VQC_ENGINE_JIT, tile);
+                           engine == VQC_ENGINE_JIT, tile, false);
   if (rc != 0) {
     delete c;
     return fail(rc, msg);
   }
-  // Default tiles of the generated kernels: 12 qubits unless that takes more
-  // than a quarter more passes than 13.  Four workgroups per CU instead of two
-  // hide more latency: measured 1.6-4 % faster on the 14-qubit re-uploading
-  // workload (same passes) and 3.5 % on the 16-qubit ring (29 passes, not 24).
+  // Default tiles of the generated kernels: 12 qubits unless they take more
+  // than a quarter more passes than 13, with the CNOTs as gates or without.
+  // Four workgroups per CU instead of two hide more latency (with the CNOTs as
+  // gates 1.6-4 % on the 14-qubit re-uploading workload at the same passes).
   if (engine == VQC_ENGINE_JIT && tile == 0 && c->plan.path == VQC_PATH_STREAM) {
     Plan p12;
     std::string msg12;
-    const size_t n13 = c->plan.fpass.size() + c->plan.bpass.size();
-    if (vqc::build_plan(hops, n_qubits, n_params, n_inputs, path, reg_bits, p12, msg12, true, 12) ==
-            0 &&
-        4 * (p12.fpass.size() + p12.bpass.size()) <= 5 * n13)
+    if (vqc::build_plan(hops, n_qubits, n_params, n_inputs, path, reg_bits, p12, msg12, true, 12,
+                        false) == 0 &&
+        4 * p12.gate_passes <= 5 * c->plan.gate_passes &&
+        4 * vqc::linear_passes(p12) <= 5 * vqc::linear_passes(c->plan))
       c->plan = std::move(p12);
   }
+  if (engine == VQC_ENGINE_JIT && (rc = vqc::build_linear_plan(c->plan, msg)) != 0) {
+    delete c;
+    return fail(rc, msg);
+  }
+
   // The generated adjoint passes hold 16 amplitudes per thread (the batched
   // gradient reduction fits there); reg_bits = 5 asks for 32.  32 halve the
   // workgroups per CU that hide each pass's loads and stores.  Measured on one

@@ -139,11 +139,19 @@ Frame frame_rows(const Plan& p) {
   return f;
 }
 
-std::vector<int> stream_rotations(const uint32_t* ins, int n_ins) {
+// One instruction stream: of the linear schedule (lin), or instruction pairs.
+struct Stream {
+  const uint32_t* ins = nullptr;
+  const LinIns* lin = nullptr;
+  int n = 0;
+};
+
+std::vector<int> stream_rotations(const Stream& s) {
   std::vector<int> occ;
-  for (int pc = 0; pc < n_ins; ++pc) {
-    const int op = ins[2 * pc] & 31;
-    if (op == OP_RX || op == OP_RY || op == OP_RZ) occ.push_back((int)ins[2 * pc + 1]);
+  for (int pc = 0; pc < s.n; ++pc) {
+    const int op = s.lin ? s.lin[pc].op : (int)(s.ins[2 * pc] & 31);
+    if (op == OP_RX || op == OP_RY || op == OP_RZ)
+      occ.push_back(s.lin ? s.lin[pc].arg : (int)s.ins[2 * pc + 1]);
   }
   return occ;
 }
@@ -160,19 +168,19 @@ struct TanMode {
 
 size_t align16(size_t v) { return (v + 15) / 16 * 16; }
 
-TanMode tan_mode(const Plan& p, const uint32_t* fins, int fn, const uint32_t* bins, int bn, int S,
-                 bool esign, size_t base) {
+TanMode tan_mode(const Plan& p, const Stream* f, const Stream* b, int S, bool esign,
+                 size_t base) {
   TanMode t;
   const int nocc = (int)p.occ_src.size();
   t.W = std::max(1, (nocc + 31) / 32);
-  if (fins) t.focc = stream_rotations(fins, fn);
-  if (bins) t.bocc = stream_rotations(bins, bn);
+  if (f) t.focc = stream_rotations(*f);
+  if (b) t.bocc = stream_rotations(*b);
   t.esign = esign;
   size_t off = align16(base);
   t.off_bits = off;
   off = align16(off + (size_t)(t.W + 1) * 4);  // + 1: the ballot writes word pairs
   t.off_gm = off;
-  if (bins) off = align16(off + (size_t)nocc * 4);
+  if (b) off = align16(off + (size_t)nocc * 4);
   t.off_es = off;
   if (esign) off = align16(off + (size_t)p.n * 4);
   t.end = off;
@@ -503,15 +511,445 @@ std::string occ_scale(const Plan& p, uint32_t occ) {
   return o.str();
 }
 
-// What a stream does with its swap frame at its end (vqc_device.h, "swap
-// frame"): resolve it (the epilogue or the stores read positions; a pass's
-// closing exchange has usually folded it already), or drop it (nothing reads
-// the state).
-enum FrameEnd { kFrameResolve, kFrameDrop };
 
-// Statements of one instruction stream for register width R.  With tangent
-// tables (tm.on) rotations use the tangent form and blocks are rescaled, and
-// CNOTs from a thread / tile bit onto a register bit go to the swap frame.
+// What the emitters of one instruction stream share.
+struct Emit {
+  std::ostringstream& o;
+  const Plan& p;
+  bool bwd;
+  int R;
+  const GradMode& gm;
+  bool batched;                  // pending partials (emit_flush)
+  Pending pend;
+  bool ahead;                    // table entries read one gate ahead (tables in LDS)
+  std::vector<int> rots;         // the stream's rotations in the order they run
+  size_t ri = 0;                 // the next one's index
+  int m = 0, nrot = 0;           // rotations so far / in all (block rescales)
+  // the sign bit of parity(tb & mask), tb the physical bits above the registers
+  std::function<std::string(uint32_t)> sign;
+};
+
+void emit_pending_decl(Emit& E) {
+  if (!E.batched) return;
+  E.o << "  float pd0 = 0.f, pd1 = 0.f, pd2 = 0.f, pd3 = 0.f, pd4 = 0.f, pd5 = 0.f, pd6 = 0.f, "
+         "pd7 = 0.f, pd8 = 0.f, pd9 = 0.f, pd10 = 0.f, pd11 = 0.f, pd12 = 0.f, pd13 = 0.f, "
+         "pd14 = 0.f, pd15 = 0.f;\n";
+}
+
+// Before a rotation with gradient `slot`: flush when its position is taken by
+// another slot.
+void emit_slot_ready(Emit& E, int slot) {
+  if (!E.batched || slot < 0) return;
+  const int pos = slot & 15;
+  if (E.pend.tag[pos] >= 0 && E.pend.tag[pos] != slot) emit_flush(E.o, E.pend);
+}
+
+// Collects the thread's gradient partial g of `slot`.  The empty asms keep the
+// update in place: left free, the compiler sinks the partial's computation
+// into the flush (or the additions to the kernel's end) and keeps the old
+// states alive.
+void emit_collect(Emit& E, int slot) {
+  std::ostringstream& o = E.o;
+  if (slot < 0) {
+    o << " (void)g;";
+  } else if (E.batched) {
+    const int pos = slot & 15;
+    o << " pd" << pos << (E.pend.tag[pos] == slot ? " += g;" : " = g;") << " asm volatile(\"\" : \"+v\"(pd"
+      << pos << "));";
+    E.pend.tag[pos] = slot;
+  } else if (E.gm.regs) {
+    o << " const float gs = group_sum<" << E.gm.tm << ">(g); ga[" << slot / E.gm.tm
+      << "] += (opaque(ln) == " << slot % E.gm.tm << "u) ? gs : 0.f; asm volatile(\"\" : \"+v\"(ga["
+      << slot / E.gm.tm << "]));";
+  } else {
+    o << " { const float gs = group_sum<" << E.gm.tm << ">(g); if (w.leader) atomicAdd(&w.acc["
+      << slot << " * w.G + w.grp], gs); }";
+  }
+}
+
+// Rescales by the block's factors where a block of rotations ends among the
+// next n.
+void emit_rescale(Emit& E, int n) {
+  bool resc = false;
+  for (int i = 0; i < n; ++i)
+    if ((E.m + i) % kBlock == kBlock - 1 || E.m + i == E.nrot - 1) resc = true;
+  E.m += n;
+  if (!resc) return;
+  E.o << " rescale<R>(a, bp);";
+  if (E.bwd) E.o << " rescale<R>(l, bp);";
+  E.o << " bp = 1.f;";
+}
+
+// ------------------------------------------------------------- runs of RZs
+// A run of RZs (tangent form: amplitude x times 1 - i t z(x) per gate, z the
+// sign of a parity over register and thread bits) is one diagonal D: the
+// forward multiplies each amplitude by D once.  The adjoint takes every
+// gradient of the run from Im(conj(lambda) psi), which no diagonal gate changes
+// (the tangent form scales it by 1 / cos^2 per gate, which the block factor bp
+// carries), then multiplies psi and lambda by the inverse diagonal once.  The
+// RZs with one register mask multiply into one factor (their thread signs go
+// into t).  D's entries are formed in double, depth first over the register
+// bits so that one product per level is live, each factor where the last bit
+// of its mask is known, and each entry goes to float once.
+struct RzItem {
+  int occ, slot;
+  uint32_t reg, thr;  // parity masks: register bits, bits above them
+};
+
+// How D is formed: the register bits in the order they are fixed, and the
+// flip f of register bits that takes every factor to its conjugate (parity(m &
+// f) odd for every mask m), or 0.  Without a thread part D(u ^ f) is then the
+// conjugate of D(u) and half the entries need forming: order[0] is a bit of f
+// and stays 0.
+struct DiagonalForm {
+  std::vector<int> order;
+  uint32_t flip = 0;
+  int cost = 0;  // double-precision operations and conversions
+};
+
+DiagonalForm diagonal_form(const std::map<uint32_t, int>& cnt, bool thread, int R) {
+  DiagonalForm best;
+  if (cnt.empty()) return best;
+  uint32_t all = 0, flip = 0;
+  for (const auto& c : cnt) all |= c.first;
+  for (uint32_t f = 1; !thread && !flip && f < (1u << R); ++f) {
+    if (f & ~all) continue;
+    bool odd = true;
+    for (const auto& c : cnt) odd = odd && __builtin_parity(c.first & f);
+    if (odd) flip = f;
+  }
+  std::vector<int> perm;
+  for (int b = 0; b < R; ++b)
+    if ((all >> b) & 1u) perm.push_back(b);
+  best.cost = -1;
+  do {
+    if (flip && !((flip >> perm[0]) & 1u)) continue;
+    int cost = 0;
+    bool first = !thread;
+    uint32_t known = 0;
+    for (size_t d = 0; d < perm.size(); ++d) {
+      const uint32_t now = known | 1u << perm[d];
+      const int nodes = flip ? 1 << d : 2 << d;
+      for (const auto& c : cnt) {
+        if ((c.first & now) != c.first || (c.first & known) == c.first) continue;
+        cost += first ? 0 : nodes * (c.second == 1 ? 2 : 4);
+        first = false;
+      }
+      known = now;
+    }
+    cost += (flip ? 1 : 2) << perm.size();  // to float
+    if (best.cost < 0 || cost < best.cost) {
+      best.cost = cost;
+      best.order = perm;
+      best.flip = flip;
+    }
+  } while (std::next_permutation(perm.begin(), perm.end()));
+  return best;
+}
+
+std::map<uint32_t, int> mask_counts(const std::vector<RzItem>& run) {
+  std::map<uint32_t, int> cnt;
+  for (const RzItem& it : run)
+    if (it.reg) ++cnt[it.reg];
+  return cnt;
+}
+
+// Instruction counts of a run as one diagonal, and gate by gate.
+int fused_cost(const std::vector<RzItem>& run, int R, bool bwd) {
+  const int N = 1 << R, states = bwd ? 2 : 1;
+  const std::map<uint32_t, int> cnt = mask_counts(run);
+  int thread = 0, multi = 0;
+  for (const RzItem& it : run) thread += !it.reg;
+  for (const auto& c : cnt) multi += (c.first & (c.first - 1u)) != 0;
+  const int products = (int)run.size() - thread - (int)cnt.size();
+  int cost = diagonal_form(cnt, thread > 0, R).cost + 2 * thread + 4 * products + states * 4 * N;
+  if (bwd) cost += 3 * N + 3 * (int)run.size() + (multi ? N : 0);
+  return cost;
+}
+int single_cost(size_t n, int R, bool bwd) { return (int)n * (bwd ? 6 : 2) * (1 << R); }
+
+// Splits a run into the diagonals to apply (each at least a tenth cheaper than
+// its gates one by one, the margin for its registers) and the RZs left gate by
+// gate: all in one, or the RZs of at most one register bit apart from the rest
+// (whose many masks each cost products).
+void split_run(const std::vector<RzItem>& run, int R, bool bwd,
+               std::vector<std::vector<RzItem>>& fused, std::vector<RzItem>& single) {
+  auto cost = [&](const std::vector<RzItem>& r) {
+    const int sep = single_cost(r.size(), R, bwd);
+    if (r.size() < 2) return sep;
+    const int one = fused_cost(r, R, bwd);
+    return 10 * one < 9 * sep ? one : sep;
+  };
+  std::vector<RzItem> narrow, wide;
+  for (const RzItem& it : run) (it.reg & (it.reg - 1u) ? wide : narrow).push_back(it);
+  std::vector<std::vector<RzItem>> parts{run};
+  if (!narrow.empty() && !wide.empty() && cost(narrow) + cost(wide) < cost(run))
+    parts = {narrow, wide};
+  for (const auto& r : parts) {
+    if (r.size() >= 2 && 10 * fused_cost(r, R, bwd) < 9 * single_cost(r.size(), R, bwd))
+      fused.push_back(r);
+    else
+      single.insert(single.end(), r.begin(), r.end());
+  }
+}
+
+void emit_rz_run(Emit& E, const std::vector<RzItem>& run) {
+  std::ostringstream& o = E.o;
+  const int R = E.R, N = 1 << R, L = (int)run.size();
+  const bool bwd = E.bwd;
+  const char* sg = bwd ? "" : "-";  // factor 1 + i sg x for z = +1
+  o << "  { // " << L << " RZs as one diagonal\n";
+  if (!E.ahead) {  // the tables in registers (table_row)
+    for (int i = 0; i < L; ++i) {
+      const int occ = run[i].occ;
+      o << "    const float2 tc" << i << " = table_entry<" << occ % 64 << ">(T" << occ / 64 << ");";
+      if (bwd) o << " const float gm" << i << " = table_entry<" << occ % 64 << ">(G" << occ / 64 << ");";
+      o << "\n";
+    }
+  } else {  // in LDS, the run's first entries read ahead
+    if (E.rots[E.ri] != run[0].occ) o << "#error rotation prefetch out of order\n";
+    for (int i = 0; i < L; ++i) {
+      if (i == 0) {
+        o << "    const float2 tc0 = tcn;";
+        if (bwd) o << " const float gm0 = gmn;";
+      } else {
+        o << "    const float2 tc" << i << " = w.tab[" << run[i].occ << "];";
+        if (bwd) o << " const float gm" << i << " = gmul[" << run[i].occ << "];";
+      }
+      o << "\n";
+    }
+    E.ri += L;
+    if (E.ri < E.rots.size()) {
+      o << "    tcn = w.tab[" << E.rots[E.ri] << "];";
+      if (bwd) o << " gmn = gmul[" << E.rots[E.ri] << "];";
+      o << "\n";
+    }
+  }
+  // the thread's signs, one per distinct parity
+  std::vector<uint32_t> thr;
+  for (const RzItem& it : run)
+    if (it.thr && std::find(thr.begin(), thr.end(), it.thr) == thr.end()) {
+      o << "    const uint32_t fs" << thr.size() << " = " << E.sign(it.thr) << ";\n";
+      thr.push_back(it.thr);
+    }
+  auto fs = [&](uint32_t mask) {
+    return "fs" + std::to_string(std::find(thr.begin(), thr.end(), mask) - thr.begin());
+  };
+  int nt = 0;
+  for (int i = 0; i < L; ++i) {
+    const RzItem& it = run[i];
+    o << "    const float t" << i << " = ";
+    if (it.thr) o << "flip_sign(tc" << i << ".x, " << fs(it.thr) << ");\n";
+    else o << "tc" << i << ".x;\n";
+    if (!it.reg) ++nt;
+  }
+  if (bwd) {
+    // the gradients, all from Im(conj(lambda) psi) at the run's output: its
+    // signed sums over the register bits (what no gate asks for is dropped by
+    // the compiler)
+    for (int u = 0; u < N; ++u)
+      o << "    const float I" << u << " = fmaf(-l.i[" << u << "], a.r[" << u << "], l.r[" << u
+        << "] * a.i[" << u << "]);\n";
+    std::vector<std::string> P(N);
+    for (int u = 0; u < N; ++u) P[u] = "I" + std::to_string(u);
+    for (int j = 0; j < R; ++j) {
+      std::vector<std::string> Q(N);
+      for (int u = 0; u < N; ++u) {
+        const int lo = u & ~(1 << j), hi = u | (1 << j);
+        Q[u] = "P" + std::to_string(j) + "_" + std::to_string(u);
+        o << "    const float " << Q[u] << " = " << P[lo] << ((u >> j) & 1 ? " - " : " + ") << P[hi]
+          << ";\n";
+      }
+      P.swap(Q);
+    }
+    o << "    const float bb = bp * bp;\n";
+    for (int i = 0; i < L; ++i) {
+      const RzItem& it = run[i];
+      emit_slot_ready(E, it.slot);
+      o << "    { float g = "
+        << (it.thr ? "flip_sign(" + P[it.reg] + ", " + fs(it.thr) + ")" : P[it.reg]) << "; g *= gm"
+        << i << " * bb;" << occ_scale(E.p, it.occ);
+      emit_collect(E, it.slot);
+      o << " }\n";
+    }
+  }
+  for (int i = 0; i < L; ++i) o << "    bp *= tc" << i << ".y;\n";
+  // The diagonal in double precision (every entry rounded to float once: its
+  // rounding is shared by the amplitudes it multiplies, so a float product's
+  // error, about sqrt(L) ulp, would shift the norm coherently).
+  bool haveT = false;
+  for (int i = 0; i < L; ++i) {
+    if (run[i].reg) continue;
+    const std::string x = std::string(sg) + "(double)t" + std::to_string(i);
+    if (!haveT) {
+      o << "    double Tr = 1.0, Ti = " << x << ";\n";
+      haveT = true;
+    } else {
+      o << "    { const double x = " << x << ", nr = fma(-x, Ti, Tr); Ti = fma(x, Tr, Ti); Tr = nr; }\n";
+    }
+  }
+  // per register mask: the factor for even parity, 1 + i s (one RZ) or F (a
+  // product); the factor for odd parity is its conjugate
+  std::map<uint32_t, int> cnt = mask_counts(run);
+  for (const auto& c : cnt) {
+    const uint32_t mk = c.first;
+    bool first = true;
+    for (int i = 0; i < L; ++i) {
+      if (run[i].reg != mk) continue;
+      const std::string x = std::string(sg) + "(double)t" + std::to_string(i);
+      if (cnt[mk] == 1)
+        o << "    const double s" << mk << " = " << x << ";\n";
+      else if (first)
+        o << "    double F" << mk << "r = 1.0, F" << mk << "i = " << x << ";\n";
+      else
+        o << "    { const double x = " << x << ", nr = fma(-x, F" << mk << "i, F" << mk << "r); F"
+          << mk << "i = fma(x, F" << mk << "r, F" << mk << "i); F" << mk << "r = nr; }\n";
+      first = false;
+    }
+  }
+  // y = x times mask mk's factor for parity h
+  auto times = [&](const std::string& x, uint32_t mk, uint32_t h, const std::string& y) {
+    if (cnt[mk] == 1) {
+      const std::string sp = h ? "(-s" + std::to_string(mk) + ")" : "s" + std::to_string(mk);
+      o << "const double " << y << "r = fma(-" << sp << ", " << x << "i, " << x << "r), " << y
+        << "i = fma(" << sp << ", " << x << "r, " << x << "i);";
+    } else {
+      const std::string fr = "F" + std::to_string(mk) + "r";
+      const std::string fi = h ? "(-F" + std::to_string(mk) + "i)" : "F" + std::to_string(mk) + "i";
+      o << "const double " << y << "r = fma(" << x << "r, " << fr << ", -(" << x << "i * " << fi
+        << ")), " << y << "i = fma(" << x << "r, " << fi << ", " << x << "i * " << fr << ");";
+    }
+  };
+  // the factor itself (the product's first factor when there is no thread part)
+  auto first_factor = [&](uint32_t mk, uint32_t h, const std::string& y) {
+    if (cnt[mk] == 1)
+      o << "const double " << y << "r = 1.0, " << y << "i = " << (h ? "-" : "") << "s" << mk << ";";
+    else
+      o << "const double " << y << "r = F" << mk << "r, " << y << "i = " << (h ? "-" : "") << "F"
+        << mk << "i;";
+  };
+  auto apply = [&](int u, const char* st, const char* ei) {
+    o << "      { const float xr = " << st << ".r[" << u << "], xi = " << st << ".i[" << u << "]; "
+      << st << ".r[" << u << "] = fmaf(xr, er, -(xi * " << ei << ")); " << st << ".i[" << u
+      << "] = fmaf(xr, " << ei << ", xi * er); }\n";
+  };
+  const DiagonalForm form = diagonal_form(cnt, haveT, R);
+  uint32_t all = 0;
+  for (const auto& c : cnt) all |= c.first;
+  int uid = 0;
+  std::function<void(size_t, uint32_t, uint32_t, std::string)> walk =
+      [&](size_t d, uint32_t known, uint32_t val, std::string x) {
+        if (d == form.order.size()) {
+          o << "    { const float er = (float)" << x << "r, ei = (float)" << x << "i;\n";
+          for (int u = 0; u < N; ++u) {
+            const bool same = ((uint32_t)u & all) == val;
+            if (!same && !(form.flip && ((uint32_t)u & all) == (val ^ form.flip))) continue;
+            apply(u, "a", same ? "ei" : "(-ei)");
+            if (bwd) apply(u, "l", same ? "ei" : "(-ei)");
+          }
+          o << "    }\n";
+          return;
+        }
+        const uint32_t now = known | 1u << form.order[d];
+        for (uint32_t h = 0; h < (form.flip && d == 0 ? 1u : 2u); ++h) {
+          const uint32_t v = val | h << form.order[d];
+          std::string y = x;
+          o << "    { ";
+          for (const auto& c : cnt) {
+            const uint32_t mk = c.first;
+            if ((mk & now) != mk || (mk & known) == mk) continue;
+            const std::string z = "N" + std::to_string(uid++) + "_";
+            const uint32_t par = (uint32_t)__builtin_parity(v & mk);
+            if (y.empty()) first_factor(mk, par, z);
+            else times(y, mk, par, z);
+            y = z;
+          }
+          o << "\n";
+          walk(d + 1, now, v, y);
+          o << "    }\n";
+        }
+      };
+  walk(0, 0u, 0u, haveT ? "T" : "");
+  o << "   ";
+  emit_rescale(E, L);
+  o << "\n    gate_boundary(w);\n  }\n";
+}
+
+// A run of CZs is one diagonal of signs: amplitude u of the thread is negated
+// when c[u] ^ t0 ^ (XOR of m[r] over the register bits r set in u) is 1.  Each
+// CZ is the product of two parities over register bits (compile time) and
+// thread / tile bits: c the register parts' product, m and t0 the thread
+// parts' shares.  One sign flip per value instead of one per gate.
+struct CzItem {
+  uint32_t a, b;  // parity masks over the physical bits
+};
+
+void emit_cz_run(Emit& E, const std::vector<CzItem>& run) {
+  std::ostringstream& o = E.o;
+  const int R = E.R, N = 1 << R;
+  const uint32_t regs = (uint32_t)N - 1u;
+  std::vector<int> cu(N, 0);
+  std::vector<std::string> mr(R);
+  std::string t0;
+  auto thread = [&](uint32_t mask) {  // parity of the bits above the registers, in bit 0
+    const uint32_t m = mask >> R;
+    if (!(m & (m - 1u))) return "(tb >> " + std::to_string(__builtin_ctz(m)) + ")";
+    return "(uint32_t)__builtin_popcount(tb & " + hex(m) + ")";
+  };
+  for (const CzItem& c : run) {
+    for (int u = 0; u < N; ++u)
+      cu[u] ^= __builtin_parity(c.a & u) & __builtin_parity(c.b & u);
+    const std::string A = c.a >> R ? thread(c.a) : "", B = c.b >> R ? thread(c.b) : "";
+    for (int r = 0; r < R; ++r) {
+      if (((c.b >> r) & 1u) && !A.empty()) mr[r] += (mr[r].empty() ? "" : " ^ ") + A;
+      if (((c.a >> r) & 1u) && !B.empty()) mr[r] += (mr[r].empty() ? "" : " ^ ") + B;
+    }
+    if (!A.empty() && !B.empty()) t0 += (t0.empty() ? "" : " ^ ") + ("(" + A + " & " + B + ")");
+  }
+  (void)regs;
+  o << "  { const uint32_t tb = opaque(w.tb); (void)tb;\n"
+    << "    const uint32_t s0 = " << (t0.empty() ? "0u" : "(" + t0 + ") & 1u") << ";\n";
+  for (int r = 0; r < R; ++r)
+    o << "    const uint32_t m" << r << " = " << (mr[r].empty() ? "0u" : "(" + mr[r] + ") & 1u")
+      << ";\n";
+  for (int u = 1; u < N; ++u) {
+    int low = 0;
+    while (!((u >> low) & 1)) ++low;
+    o << "    const uint32_t s" << u << " = s" << (u & (u - 1)) << " ^ m" << low << ";\n";
+  }
+  for (const char* st : {"a", "l"}) {
+    if (st[0] == 'l' && !E.bwd) break;
+    for (int u = 0; u < N; ++u)
+      o << "    " << st << ".r[" << u << "] = flip_sign(" << st << ".r[" << u << "], (s" << u << " ^ "
+        << cu[u] << "u) << 31); " << st << ".i[" << u << "] = flip_sign(" << st << ".i[" << u
+        << "], (s" << u << " ^ " << cu[u] << "u) << 31);\n";
+  }
+  o << "  }\n";
+}
+
+// An exchange of the states named in `sts`: cross-lane moves when it only
+// swaps register bits with lane bits, else through LDS.
+void emit_exchange_code(Emit& E, uint32_t arg, int k, const std::vector<const char*>& sts) {
+  std::ostringstream& o = E.o;
+  const int R = E.R, t = k - R;
+  std::vector<std::pair<int, int>> swaps;
+  if (lane_exchange(E.p, arg, k, R, t, swaps)) {
+    o << "  { const uint32_t ln = opaque(__lane_id());\n";
+    for (const auto& sw : swaps) {
+      o << "   ";
+      for (const char* st : sts)
+        o << " lane_swap<R, " << sw.first << ", " << sw.second << ">(" << st << ", ln);";
+      o << "\n";
+    }
+    o << "  }\n";
+    return;
+  }
+  o << "  { static constexpr uint32_t col[] = {";
+  for (int i = 0; i < 2 * k; ++i) o << (i ? "," : "") << hex(E.p.cols[arg + i]);
+  o << "};\n    exchange" << (sts.size() == 2 ? "2<R>(a, l" : std::string("<R>(") + sts[0])
+    << ", w.xbuf, w.plane, col, " << k << ", " << t << ", w.stid, w.sl);\n  }\n";
+}
+
 // Whether a rotation joins a run of RZs applied as one diagonal: an RZ whose
 // angle is not a constant.  A constant's float (cos, sin) pair is chosen so
 // that the norm errors of the circuit's constant gates cancel one by one;
@@ -565,59 +1003,27 @@ std::vector<uint32_t> cluster_diagonals(const Plan& p, const uint32_t* ins, int 
   return out;
 }
 
+// Statements of one gate stream for register width R (4 amplitudes per thread,
+// or several samples per workgroup).  With tangent tables (tm.on) rotations use
+// the tangent form and blocks are rescaled.
 void emit_schedule(std::ostringstream& o, const Plan& p, const uint32_t* ins, int n_ins, bool bwd,
                    int R, int k, int S, const GradMode& gm, const TanMode& tm,
-                   const std::vector<char>* skip = nullptr, FrameEnd fend = kFrameResolve) {
+                   const std::vector<char>* skip = nullptr) {
   const int t = k - R;
   const bool tan = tm.on;
-  // the swap frame: fs<r> (0 or 1 << 31 per thread) for register bit r; dirty:
-  // the bits whose frame may be set here (known while generating)
-  // (not in the kernels with gates on lane bits: there the lane swaps, which
-  // would have to resolve the frame first, follow most CNOTs)
-  const bool frames = tan && p.lanes == 0;
-  // runs of RZs on different bits become one diagonal (emit_rz_run below;
-  // one sample per workgroup, tangent form)
+  // runs of RZs on different bits become one diagonal (emit_rz_run; one sample
+  // per workgroup, tangent form)
   const bool fuse = tan && S == 1 && R >= 2;
   std::vector<uint32_t> clustered;
   if (fuse) {
     clustered = cluster_diagonals(p, ins, n_ins);
     ins = clustered.data();
   }
-  uint32_t dirty = 0;
-  if (frames) {
-    o << "  uint32_t";
-    for (int r = 0; r < R; ++r) o << (r ? ", " : " ") << "fs" << r << " = 0u";
-    o << ";\n";
-  }
-  // conditional swaps along the frame's bits in `bits` (one per state)
-  auto resolve = [&](uint32_t bits) {
-    bits &= dirty;
-    for (int r = 0; r < R; ++r) {
-      if (!((bits >> r) & 1u)) continue;
-      o << "  cnot_tr<R, " << r << ">(a, fs" << r << " != 0u);";
-      if (bwd) o << " cnot_tr<R, " << r << ">(l, fs" << r << " != 0u);";
-      o << " fs" << r << " = 0u;\n";
-    }
-    dirty &= ~bits;
-  };
-  const int nrot = (int)(bwd ? tm.bocc.size() : tm.focc.size());
-  int m = 0;  // rotation index in the stream
   // batched pending partials (a reduce-scatter per 16 slots instead of a DPP
-  // sum per rotation).  With 16 amplitudes per thread the pending registers
-  // sit beside psi and lambda: the streaming passes stay at 109-120 VGPRs, four
-  // waves per SIMD (16-qubit adjoint 15 % fewer instructions, 1.93 -> 1.79
-  // ms); the resident kernels go from four waves per SIMD to three (the
-  // 12-qubit backward 110 -> 150 VGPRs) or stay at three (the 12-qubit step,
-  // 168 VGPRs and the same spills) and still gain: step 0.879 -> 0.838 ms,
-  // backward 0.666 -> 0.654 ms.  Not in 1024-thread workgroups (a 14-qubit
-  // resident sample): those hold at most 128 VGPRs, and the pending registers
-  // spilled 1.1 KiB per thread there (569 k -> 444 k evals/s).
-  const bool batched = batched_flush(p, bwd, gm, R, k);
-  Pending pend;
-  if (batched)
-    o << "  float pd0 = 0.f, pd1 = 0.f, pd2 = 0.f, pd3 = 0.f, pd4 = 0.f, pd5 = 0.f, pd6 = 0.f, "
-         "pd7 = 0.f, pd8 = 0.f, pd9 = 0.f, pd10 = 0.f, pd11 = 0.f, pd12 = 0.f, pd13 = 0.f, "
-         "pd14 = 0.f, pd15 = 0.f;\n";
+  // sum per rotation)
+  Emit E{o, p, bwd, R, gm, batched_flush(p, bwd, gm, R, k), Pending(), false, {}, 0, 0, 0, nullptr};
+  E.nrot = (int)(bwd ? tm.bocc.size() : tm.focc.size());
+  emit_pending_decl(E);
   if (tan && bwd)
     o << "  const float* gmul = reinterpret_cast<const float*>(w.smem + " << tm.off_gm << "u);\n";
   if (tan)  // product of the factors cos(phi') of the current block so far
@@ -651,22 +1057,6 @@ void emit_schedule(std::ostringstream& o, const Plan& p, const uint32_t* ins, in
         o << "  const float G" << m << " = table_row(gmul, " << m << ", " << last << ");\n";
     }
   }
-  // The table entries of the next rotation are read one gate ahead (tangent
-  // form, tables in LDS): each gate is its own basic block (gate_boundary),
-  // so a read placed in the gate that uses it would leave the LDS latency
-  // exposed at every rotation.
-  std::vector<int> rots;
-  for (int pc = 0; pc < n_ins; ++pc) {
-    const int op = ins[2 * pc] & 31;
-    const int occ = (int)ins[2 * pc + 1];
-    if ((op == OP_RX || op == OP_RY || op == OP_RZ) && !(skip && (*skip)[occ])) rots.push_back(occ);
-  }
-  const bool ahead = tan && !sreg && !rots.empty();
-  size_t ri = 0;  // the next rotation's index in rots
-  if (ahead) {
-    o << "  float2 tcn = w.tab[" << rots[0] << "];\n";
-    if (bwd) o << "  float gmn = gmul[" << rots[0] << "];\n";
-  }
   // The sample's thread bits, computed once in the 4-amplitude kernels: their
   // few waves leave registers to spare, and each lane-bit gate then skips
   // recomputing its bit (and the sign mask formed from it) from an opaque
@@ -680,300 +1070,18 @@ void emit_schedule(std::ostringstream& o, const Plan& p, const uint32_t* ins, in
   auto bit = [&](int p) {
     return hbits ? "hb" + std::to_string(p - R) : "tile_bit<R>(w, " + std::to_string(p) + ")";
   };
-  // A run of RZs (tangent form: amplitude x times 1 - i t z(x) per gate) is
-  // one diagonal D: the forward multiplies each amplitude by D once.  The
-  // adjoint takes every gradient of the run from Im(conj(lambda) psi), which
-  // no diagonal gate changes (the tangent form scales it by 1 / cos^2 per
-  // gate, which the block factor bp carries), then multiplies psi and lambda
-  // by the inverse diagonal once.  D's entries (one per value of the run's
-  // register bits, times the thread-bit factor) are formed in double,
-  // depth first over those bits so that one product per level is live, and
-  // each goes to float once.  A run is fused when an instruction count of
-  // both ways says so, with a tenth of margin for the fused code's
-  // registers.
-  struct RzItem {
-    int occ, bit, slot;
-  };
-  auto fused_cheaper = [&](const std::vector<RzItem>& run) {
-    if (run.size() < 2) return false;
-    const int N = 1 << R;
-    int nt = 0, extra = 0;
-    uint32_t B = 0;
-    for (const auto& it : run) {
-      if (it.bit >= R) ++nt;
-      else {
-        if ((B >> it.bit) & 1u) ++extra;
-        B |= 1u << it.bit;
-      }
-    }
-    const int mb = __builtin_popcount(B);
-    int build = 2 * nt + 4 * extra;
-    for (int i = 1; i < mb; ++i) build += 4 << (i - 1);
-    if (mb) build += 4 << (mb - 1);
-    const int states = bwd ? 2 : 1;
-    const int fused = build + states * 4 * N + (bwd ? 3 * N + 3 * (int)run.size() : 0);
-    const int sep = (int)run.size() * (bwd ? 6 : 2) * N;
-    return 10 * fused < 9 * sep;
-  };
-  auto emit_rz_run = [&](const std::vector<RzItem>& run) {
-    const int N = 1 << R, L = (int)run.size();
-    const char* sg = bwd ? "" : "-";  // factor 1 + i sg x for z = +1
-    o << "  { // " << L << " RZs as one diagonal\n";
-    if (S == 1 && R <= 2) {  // the tables in registers (table_row)
-      for (int i = 0; i < L; ++i) {
-        const int occ = run[i].occ;
-        o << "    const float2 tc" << i << " = table_entry<" << occ % 64 << ">(T" << occ / 64 << ");";
-        if (bwd) o << " const float gm" << i << " = table_entry<" << occ % 64 << ">(G" << occ / 64 << ");";
-        o << "\n";
-      }
-    } else {  // in LDS, the run's first entries read ahead
-      if (rots[ri] != run[0].occ) o << "#error rotation prefetch out of order\n";
-      for (int i = 0; i < L; ++i) {
-        if (i == 0) {
-          o << "    const float2 tc0 = tcn;";
-          if (bwd) o << " const float gm0 = gmn;";
-        } else {
-          o << "    const float2 tc" << i << " = w.tab[" << run[i].occ << "];";
-          if (bwd) o << " const float gm" << i << " = gmul[" << run[i].occ << "];";
-        }
-        o << "\n";
-      }
-      ri += L;
-      if (ri < rots.size()) {
-        o << "    tcn = w.tab[" << rots[ri] << "];";
-        if (bwd) o << " gmn = gmul[" << rots[ri] << "];";
-        o << "\n";
-      }
-    }
-    uint32_t B = 0;
-    int nt = 0;
-    for (int i = 0; i < L; ++i) {
-      const int b = run[i].bit;
-      const bool neg = b < R && ((dirty >> b) & 1u);
-      o << "    const float t" << i << " = "
-        << (neg ? "flip_sign(tc" + std::to_string(i) + ".x, fs" + std::to_string(b) + ")"
-                : "tc" + std::to_string(i) + ".x")
-        << ";\n";
-      if (b >= R) {
-        // t times the thread's z on its bit
-        o << "    const float z" << i << " = flip_sign(t" << i << ", " << bit(b) << " << 31);\n";
-        ++nt;
-      } else {
-        B |= 1u << b;
-      }
-    }
-    if (bwd) {
-      // the gradients, all from Im(conj(lambda) psi) at the run's output
-      for (int u = 0; u < N; ++u)
-        o << "    const float I" << u << " = fmaf(-l.i[" << u << "], a.r[" << u << "], l.r[" << u
-          << "] * a.i[" << u << "]);\n";
-      std::vector<std::string> P(N);
-      for (int u = 0; u < N; ++u) P[u] = "I" + std::to_string(u);
-      for (int j = 0; j < R; ++j) {
-        const int half = (int)P.size() / 2;
-        if ((B >> j) & 1u) {  // sum over z on register bit j
-          o << "    const float gb" << j << " = ";
-          for (int w2 = 0; w2 < half; ++w2)
-            o << (w2 ? " + " : "") << "(" << P[2 * w2] << " - " << P[2 * w2 + 1] << ")";
-          o << ";\n";
-        }
-        if (!nt && !(B >> (j + 1))) break;
-        std::vector<std::string> Q(half);
-        for (int w2 = 0; w2 < half; ++w2) {
-          Q[w2] = "P" + std::to_string(j) + "_" + std::to_string(w2);
-          o << "    const float " << Q[w2] << " = " << P[2 * w2] << " + " << P[2 * w2 + 1] << ";\n";
-        }
-        P.swap(Q);
-      }
-      o << "    const float bb = bp * bp;\n";
-      for (int i = 0; i < L; ++i) {
-        const int b = run[i].bit, slot = run[i].slot;
-        if (batched && slot >= 0) {
-          const int pos = slot & 15;
-          if (pend.tag[pos] >= 0 && pend.tag[pos] != slot) emit_flush(o, pend);
-        }
-        std::string g;
-        if (b >= R)
-          g = "flip_sign(" + P[0] + ", " + bit(b) + " << 31)";
-        else if ((dirty >> b) & 1u)
-          g = "flip_sign(gb" + std::to_string(b) + ", fs" + std::to_string(b) + ")";
-        else
-          g = "gb" + std::to_string(b);
-        o << "    { float g = " << g << "; g *= gm" << i << " * bb;" << occ_scale(p, run[i].occ);
-        if (slot < 0) {
-          o << " (void)g;";
-        } else if (batched) {
-          const int pos = slot & 15;
-          o << " pd" << pos << (pend.tag[pos] == slot ? " += g;" : " = g;")
-            << " asm volatile(\"\" : \"+v\"(pd" << pos << "));";
-          pend.tag[pos] = slot;
-        } else if (gm.regs) {
-          o << " const float gs = group_sum<" << gm.tm << ">(g); ga[" << slot / gm.tm
-            << "] += (opaque(ln) == " << slot % gm.tm << "u) ? gs : 0.f; asm volatile(\"\" : \"+v\"(ga["
-            << slot / gm.tm << "]));";
-        } else {
-          o << " { const float gs = group_sum<" << gm.tm << ">(g); if (w.leader) atomicAdd(&w.acc["
-            << slot << " * w.G + w.grp], gs); }";
-        }
-        o << " }\n";
-      }
-    }
-    for (int i = 0; i < L; ++i) o << "    bp *= tc" << i << ".y;\n";
-    // The diagonal in double precision (every entry rounded to float once:
-    // its rounding is shared by the amplitudes it multiplies, so a float
-    // product's error, about sqrt(L) ulp, would shift the norm coherently).
-    // The thread part: the product of 1 + i sg z over the thread-bit RZs.
-    bool haveT = false;
-    for (int i = 0; i < L; ++i) {
-      if (run[i].bit < R) continue;
-      const std::string x = std::string(sg) + "(double)z" + std::to_string(i);
-      if (!haveT) {
-        o << "    double Tr = 1.0, Ti = " << x << ";\n";
-        haveT = true;
-      } else {
-        o << "    { const double x = " << x << ", nr = fma(-x, Ti, Tr); Ti = fma(x, Tr, Ti); Tr = nr; }\n";
-      }
-    }
-    // per register bit: the factor for z = +1, 1 + i s (one RZ) or F (a
-    // product); the factor for z = -1 is its conjugate
-    std::vector<int> bits;
-    std::map<int, int> cnt;
-    for (int i = 0; i < L; ++i)
-      if (run[i].bit < R && cnt[run[i].bit]++ == 0) bits.push_back(run[i].bit);
-    std::sort(bits.begin(), bits.end());
-    for (int b : bits) {
-      bool first = true;
-      for (int i = 0; i < L; ++i) {
-        if (run[i].bit != b) continue;
-        const std::string x = std::string(sg) + "(double)t" + std::to_string(i);
-        if (cnt[b] == 1)
-          o << "    const double s" << b << " = " << x << ";\n";
-        else if (first)
-          o << "    double F" << b << "r = 1.0, F" << b << "i = " << x << ";\n";
-        else
-          o << "    { const double x = " << x << ", nr = fma(-x, F" << b << "i, F" << b << "r); F"
-            << b << "i = fma(x, F" << b << "r, F" << b << "i); F" << b << "r = nr; }\n";
-        first = false;
-      }
-    }
-    // y = x times bit b's factor for bit value h
-    auto times = [&](const std::string& x, int b, int h, const std::string& y) {
-      if (cnt[b] == 1) {
-        const std::string sp = h ? "(-s" + std::to_string(b) + ")" : "s" + std::to_string(b);
-        o << "const double " << y << "r = fma(-" << sp << ", " << x << "i, " << x << "r), " << y
-          << "i = fma(" << sp << ", " << x << "r, " << x << "i);";
-      } else {
-        const std::string fr = "F" + std::to_string(b) + "r";
-        const std::string fi = h ? "(-F" + std::to_string(b) + "i)" : "F" + std::to_string(b) + "i";
-        o << "const double " << y << "r = fma(" << x << "r, " << fr << ", -(" << x << "i * " << fi
-          << ")), " << y << "i = fma(" << x << "r, " << fi << ", " << x << "i * " << fr << ");";
-      }
-    };
-    // the factor itself (the product's first factor when there is no thread part)
-    auto first_factor = [&](int b, int h, const std::string& y) {
-      if (cnt[b] == 1)
-        o << "const double " << y << "r = 1.0, " << y << "i = " << (h ? "-" : "") << "s" << b << ";";
-      else
-        o << "const double " << y << "r = F" << b << "r, " << y << "i = " << (h ? "-" : "") << "F" << b
-          << "i;";
-    };
-    auto apply = [&](int u, const char* st) {
-      o << "      { const float xr = " << st << ".r[" << u << "], xi = " << st << ".i[" << u << "]; "
-        << st << ".r[" << u << "] = fmaf(xr, er, -(xi * ei)); " << st << ".i[" << u
-        << "] = fmaf(xr, ei, xi * er); }\n";
-    };
-    // depth-first over the register bits: one live product per level; at a
-    // leaf (a value of every bit) the entry goes to float and multiplies the
-    // amplitudes with those bits
-    std::function<void(size_t, uint32_t, const std::string&)> walk =
-        [&](size_t d, uint32_t val, const std::string& x) {
-          if (d == bits.size()) {
-            o << "    { const float er = (float)" << x << "r, ei = (float)" << x << "i;\n";
-            uint32_t Bm = 0;
-            for (int b : bits) Bm |= 1u << b;
-            for (int u = 0; u < N; ++u) {
-              if (((uint32_t)u & Bm) != val) continue;
-              apply(u, "a");
-              if (bwd) apply(u, "l");
-            }
-            o << "    }\n";
-            return;
-          }
-          const int b = bits[d];
-          for (int h = 0; h < 2; ++h) {
-            const std::string y = "N" + std::to_string(d) + std::to_string(h);
-            o << "    { ";
-            if (x.empty()) first_factor(b, h, y);
-            else times(x, b, h, y);
-            o << "\n";
-            walk(d + 1, val | ((uint32_t)h << b), y);
-            o << "    }\n";
-          }
-        };
-    walk(0, 0, haveT ? "T" : "");
-    bool resc = false;
-    for (int i = 0; i < L; ++i)
-      if ((m + i) % kBlock == kBlock - 1 || m + i == nrot - 1) resc = true;
-    m += L;
-    if (resc) {
-      o << "    rescale<R>(a, bp);";
-      if (bwd) o << " rescale<R>(l, bp);";
-      o << " bp = 1.f;\n";
-    }
-    o << "    gate_boundary(w);\n  }\n";
-  };
+  E.sign = [&](uint32_t mask) { return bit(R + __builtin_ctz(mask)) + " << 31"; };
   for (int pc = 0; pc < n_ins; ++pc) {
     const uint32_t w0 = ins[2 * pc], arg = ins[2 * pc + 1];
     const int op = w0 & 31, pa = (w0 >> 5) & 31, pb = (w0 >> 10) & 31;
     const int slot = (int)(w0 >> 16) - 1;
     switch (op) {
-      case OP_EXCHANGE: {
-        std::vector<std::pair<int, int>> swaps;
-        if (lane_exchange(p, arg, k, R, t, swaps)) {
-          // register bits swapped with lane bits: cross-lane moves, no LDS
-          resolve(dirty);
-          o << "  { const uint32_t ln = opaque(__lane_id());\n";
-          for (const auto& sw : swaps) {
-            o << "    lane_swap<R, " << sw.first << ", " << sw.second << ">(a, ln);\n";
-            if (bwd) o << "    lane_swap<R, " << sw.first << ", " << sw.second << ">(l, ln);\n";
-          }
-          o << "  }\n";
-          break;
-        }
-        o << "  { static constexpr uint32_t col[] = {";
-        for (int i = 0; i < 2 * k; ++i) o << (i ? "," : "") << hex(p.cols[arg + i]);
-        o << "};\n";
-        // the swap frame, folded into the write addresses
-        std::string fo = "0u";
-        if (dirty) {
-          o << "    const uint32_t fo = 0u";
-          for (int r = 0; r < R; ++r)
-            if ((dirty >> r) & 1u)
-              o << " ^ ((col[" << r << "] << 2) & (uint32_t)((int32_t)fs" << r << " >> 31))";
-          o << ";\n";
-          fo = "fo";
-        }
-        if (bwd)
-          o << "    exchange2<R>(a, l, w.xbuf, w.plane, col, " << k << ", " << t
-            << ", w.stid, w.sl, " << fo << ");\n";
-        else
-          o << "    exchange<R>(a, w.xbuf, w.plane, col, " << k << ", " << t
-            << ", w.stid, w.sl, " << fo << ");\n";
-        for (int r = 0; r < R; ++r)
-          if ((dirty >> r) & 1u) o << "    fs" << r << " = 0u;\n";
-        dirty = 0;
-        o << "  }\n";
+      case OP_EXCHANGE:
+        if (bwd) emit_exchange_code(E, arg, k, {"a", "l"});
+        else emit_exchange_code(E, arg, k, {"a"});
         break;
-      }
       case OP_CNOT: {
         const char* sts[2] = {"a", "l"};
-        if (frames && pb < R && pa >= R) {
-          // thread / tile control, register target: into the swap frame
-          o << "  fs" << pb << " ^= " << bit(pa) << " << 31;\n";
-          dirty |= 1u << pb;
-          break;
-        }
-        if (pb >= R && pa < R) resolve(1u << pa);  // a register control of a lane target
         for (int s = 0; s < (bwd ? 2 : 1); ++s) {
           if (pb >= R && pa >= R + 2 && pa < R + 6)  // lane target, bank / row control
             o << "  cnot_ll<R, " << pb - R << ", " << pa - R << ">(" << sts[s] << ");\n";
@@ -987,66 +1095,14 @@ void emit_schedule(std::ostringstream& o, const Plan& p, const uint32_t* ins, in
           else
             o << "  cnot_tr<R, " << pb << ">(" << sts[s] << ", " << bit(pa) << ");\n";
         }
-        if (pa < R && pb < R && ((dirty >> pa) & 1u)) {
-          // F CNOT(c, t) = CNOT(c, t) F X_t: the control's frame spreads to the target
-          o << "  fs" << pb << " ^= fs" << pa << ";\n";
-          dirty |= 1u << pb;
-        }
         break;
       }
       case OP_CZ: {
-        // A run of consecutive CZs is one diagonal of signs: amplitude u of the
-        // thread is negated when c[u] ^ t0 ^ (XOR of m[r] over the register bits
-        // r set in u) is 1.  c: the register/register pairs (compile time); m[r]:
-        // the thread / tile bits paired with register bit r; t0: the products
-        // of the thread / tile pairs.  One sign flip per value instead of one
-        // per gate.
+        std::vector<CzItem> run;
         int end = pc;
-        while (end < n_ins && (ins[2 * end] & 31) == OP_CZ) ++end;
-        {
-          uint32_t regs = 0;
-          for (int q = pc; q < end; ++q) {
-            const int x = (ins[2 * q] >> 5) & 31, y = (ins[2 * q] >> 10) & 31;
-            if (x < R) regs |= 1u << x;
-            if (y < R) regs |= 1u << y;
-          }
-          resolve(regs);
-        }
-        const int N = 1 << R;
-        std::vector<int> cu(N, 0);
-        std::vector<std::string> mr(R);
-        std::string t0;
-        for (int q = pc; q < end; ++q) {
-          const int x = (ins[2 * q] >> 5) & 31, y = (ins[2 * q] >> 10) & 31;
-          const int lo = x < y ? x : y, hi = x < y ? y : x;
-          if (hi < R) {
-            for (int u = 0; u < N; ++u) cu[u] ^= (u >> lo) & (u >> hi) & 1;
-          } else if (lo < R) {
-            mr[lo] += (mr[lo].empty() ? "" : " ^ ") + std::string("(tb >> ") +
-                      std::to_string(hi - R) + ")";
-          } else {
-            t0 += (t0.empty() ? "" : " ^ ") + std::string("((tb >> ") + std::to_string(lo - R) +
-                  ") & (tb >> " + std::to_string(hi - R) + "))";
-          }
-        }
-        o << "  { const uint32_t tb = opaque(w.tb); (void)tb;\n"
-          << "    const uint32_t s0 = " << (t0.empty() ? "0u" : "(" + t0 + ") & 1u") << ";\n";
-        for (int r = 0; r < R; ++r)
-          o << "    const uint32_t m" << r << " = "
-            << (mr[r].empty() ? "0u" : "(" + mr[r] + ") & 1u") << ";\n";
-        for (int u = 1; u < N; ++u) {
-          int low = 0;
-          while (!((u >> low) & 1)) ++low;
-          o << "    const uint32_t s" << u << " = s" << (u & (u - 1)) << " ^ m" << low << ";\n";
-        }
-        for (const char* st : {"a", "l"}) {
-          if (st[0] == 'l' && !bwd) break;
-          for (int u = 0; u < N; ++u)
-            o << "    " << st << ".r[" << u << "] = flip_sign(" << st << ".r[" << u << "], (s" << u
-              << " ^ " << cu[u] << "u) << 31); " << st << ".i[" << u << "] = flip_sign(" << st
-              << ".i[" << u << "], (s" << u << " ^ " << cu[u] << "u) << 31);\n";
-        }
-        o << "  }\n";
+        for (; end < n_ins && (ins[2 * end] & 31) == OP_CZ; ++end)
+          run.push_back({1u << ((ins[2 * end] >> 5) & 31), 1u << ((ins[2 * end] >> 10) & 31)});
+        emit_cz_run(E, run);
         pc = end - 1;
         break;
       }
@@ -1061,86 +1117,63 @@ void emit_schedule(std::ostringstream& o, const Plan& p, const uint32_t* ins, in
             if (ope != OP_RX && ope != OP_RY && ope != OP_RZ) break;
             if (skip && (*skip)[occ]) continue;  // a head rotation: not run here
             if (!fusable_rz(p, we, occ)) break;
-            run.push_back({(int)occ, (int)((ins[2 * end] >> 5) & 31), (int)(ins[2 * end] >> 16) - 1});
+            const int b = (int)((we >> 5) & 31);
+            run.push_back({(int)occ, (int)(we >> 16) - 1, b < R ? 1u << b : 0u,
+                           b < R ? 0u : 1u << (b - R)});
           }
-          if (fused_cheaper(run)) {
-            emit_rz_run(run);
+          if (run.size() >= 2 &&
+              10 * fused_cost(run, R, bwd) < 9 * single_cost(run.size(), R, bwd)) {
+            emit_rz_run(E, run);
             pc = end - 1;
             break;
           }
         }
         const bool reg = pa < R;
         const char* kind = op == OP_RX ? "rx" : op == OP_RY ? "ry" : "rz";
-        if (batched && slot >= 0) {  // the slot's position is taken by another slot
-          const int pos = slot & 15;
-          if (pend.tag[pos] >= 0 && pend.tag[pos] != slot) emit_flush(o, pend);
-        }
-        const std::string at = std::to_string(arg) + " * " + std::to_string(S) + " + w.sl";
+        const std::string mask = std::to_string(reg ? 1 << pa : 0);
+        const std::string masks = op == OP_RY ? mask + ", " + mask : mask;
+        emit_slot_ready(E, slot);
+        // RX / RY off the register bits sit on a lane bit (planner option)
+        const std::string lane = std::to_string(pa - R);
+        const std::string hi = pa >= R ? bit(pa) : "0u";
         if (tan) {
-          if (sreg) {
-            o << "  { const float2 tc = table_entry<" << arg % 64 << ">(T" << arg / 64 << "); ";
-          } else if (ahead) {
-            o << "  { const float2 tc = tcn; ";
-            if (bwd) o << "const float gm = gmn; ";
-            if (ri + 1 < rots.size()) {
-              o << "tcn = w.tab[" << rots[ri + 1] << "]; ";
-              if (bwd) o << "gmn = gmul[" << rots[ri + 1] << "]; ";
-            }
-            ++ri;
-          } else {
-            o << "  { const float2 tc = w.tab[" << arg << "]; ";
-          }
-          // negated under the swap frame (RY, RZ on a frame bit)
-          const bool neg = reg && op != OP_RX && ((dirty >> pa) & 1u);
-          if (neg)
-            o << "const float t = flip_sign(tc.x, fs" << pa << "); ";
-          else
-            o << "const float t = tc.x; ";
-          // RX / RY off the register bits sit on a lane bit (planner option)
-          const std::string lane = std::to_string(pa - R);
-          const std::string hi = pa >= R ? bit(pa) : "0u";
+          o << "  { const float2 tc = table_entry<" << arg % 64 << ">(T" << arg / 64 << "); "
+            << "const float t = tc.x; ";
           if (!bwd) {
             if (reg)
-              o << kind << "_t<R, " << pa << ">(a, t);";
+              o << kind << "_t<R, " << masks << ">(a, t);";
             else if (op == OP_RZ)
-              o << "phase_t<R>(a, flip_sign(t, " << hi << " << 31));";
+              o << "rz_t<R, 0>(a, flip_sign(t, " << hi << " << 31));";
             else if (op == OP_RX)
               o << "rx_lane_t<R, " << lane << ">(a, t);";
             else
               o << "ry_lane_t<R, " << lane << ">(a, t, " << hi << ");";
           } else {
             if (reg)
-              o << "float g = adj_" << kind << "_t<R, " << pa << ">(a, l, t);";
+              o << "float g = adj_" << kind << "_t<R, " << masks << ">(a, l, t);";
             else if (op == OP_RZ)
-              o << "float g = adj_phase_t<R>(a, l, t, " << hi << ");";
+              o << "float g = flip_sign(adj_rz_t<R, 0>(a, l, flip_sign(t, " << hi << " << 31)), "
+                << hi << " << 31);";
             else if (op == OP_RX)
               o << "float g = adj_rx_lane_t<R, " << lane << ">(a, l, t);";
             else
               o << "float g = adj_ry_lane_t<R, " << lane << ">(a, l, t, " << hi << ");";
-            if (neg) o << " g = flip_sign(g, fs" << pa << ");";
             // the states carry 1 / (the factors of the block before this gate)
-            if (sreg)
-              o << " g *= table_entry<" << arg % 64 << ">(G" << arg / 64 << ") * (bp * bp);";
-            else if (ahead)
-              o << " g *= gm * (bp * bp);";
-            else
-              o << " g *= gmul[" << arg << "] * (bp * bp);";
-            o << occ_scale(p, arg);
+            o << " g *= table_entry<" << arg % 64 << ">(G" << arg / 64 << ") * (bp * bp);"
+              << occ_scale(p, arg);
           }
           o << " bp *= tc.y;";
         } else {
+          const std::string at = std::to_string(arg) + " * " + std::to_string(S) + " + w.sl";
           if (sreg)
             o << "  { const float2 cs = table_entry<" << arg % 64 << ">(T" << arg / 64 << "); ";
           else if (vreg)
             o << "  { const float2 cs = V" << arg << "; ";
           else
             o << "  { const float2 cs = w.tab[" << at << "]; ";
-          // RX / RY off the register bits sit on a lane bit (planner option)
-          const std::string lane = std::to_string(pa - R);
-          const std::string hi = pa >= R ? bit(pa) : "0u";
           if (!bwd) {
             if (reg)
-              o << kind << "_reg<R, " << pa << ">(a, cs.x, cs.y);";
+              o << kind << "_reg<R, " << masks << ">(a, cs.x, cs.y);";
             else if (op == OP_RZ)  // RZ on a thread / tile bit
               o << "phase_all<R>(a, cs.x, flip_sign(cs.y, (" << hi << " ^ 1u) << 31));";
             else if (op == OP_RX)
@@ -1149,7 +1182,7 @@ void emit_schedule(std::ostringstream& o, const Plan& p, const uint32_t* ins, in
               o << "ry_lane<R, " << lane << ">(a, cs.x, cs.y, " << hi << ");";
           } else {
             if (reg)
-              o << "float g = adj_" << kind << "<R, " << pa << ">(a, l, cs.x, cs.y);";
+              o << "float g = adj_" << kind << "<R, " << masks << ">(a, l, cs.x, cs.y);";
             else if (op == OP_RZ)
               o << "float g = adj_rz_uniform<R>(a, l, cs.x, cs.y, " << hi << ");";
             else if (op == OP_RX)
@@ -1159,32 +1192,8 @@ void emit_schedule(std::ostringstream& o, const Plan& p, const uint32_t* ins, in
             o << occ_scale(p, arg);
           }
         }
-        if (bwd) {
-          if (slot < 0) {
-            o << " (void)g;";
-          } else if (batched) {
-            const int pos = slot & 15;
-            // the empty asm keeps the partial's computation here: left free, the
-            // compiler sinks it into the flush and keeps the old states alive
-            o << " pd" << pos << (pend.tag[pos] == slot ? " += g;" : " = g;")
-              << " asm volatile(\"\" : \"+v\"(pd" << pos << "));";
-            pend.tag[pos] = slot;
-          } else if (gm.regs)
-            // the empty asm keeps the update here: left free, the additions drift
-            // to the end of the kernel and every partial stays alive until then
-            o << " const float gs = group_sum<" << gm.tm << ">(g); ga[" << slot / gm.tm
-              << "] += (opaque(ln) == " << slot % gm.tm << "u) ? gs : 0.f; asm volatile(\"\" : \"+v\"(ga["
-              << slot / gm.tm << "]));";
-          else
-            o << " { const float gs = group_sum<" << gm.tm << ">(g); if (w.leader) atomicAdd(&w.acc["
-              << slot << " * w.G + w.grp], gs); }";
-        }
-        if (tan && (m % kBlock == kBlock - 1 || m == nrot - 1)) {
-          o << " rescale<R>(a, bp);";
-          if (bwd) o << " rescale<R>(l, bp);";
-          o << " bp = 1.f;";
-        }
-        ++m;
+        if (bwd) emit_collect(E, slot);
+        if (tan) emit_rescale(E, 1);
         // gate by gate instruction selection (see gate_boundary); the small
         // kernels with gates on lane bits leave the scheduler free instead, so
         // that the DPP moves fold into the multiplies that use them
@@ -1192,24 +1201,142 @@ void emit_schedule(std::ostringstream& o, const Plan& p, const uint32_t* ins, in
       }
     }
   }
-  if (batched) emit_flush(o, pend);
-  if (frames) {
-    if (fend == kFrameResolve) resolve(dirty);
-    for (int r = 0; r < R; ++r) o << "  (void)fs" << r << ";\n";
-  }
+  if (E.batched) emit_flush(o, E.pend);
 }
 
-// The circuit's constants, compiled in (the interpreter reads them from the
-// plan's arrays): the qubit count, the mapping (qubit -> physical bit) that
-// the <Z> epilogue or the forming of lambda uses (map_off in the plan's maps),
-// and every angle occurrence's record.  A gate list's constants then cost no
-// dependent loads from device memory before the first gate.
-void emit_constants(std::ostringstream& o, const Plan& p, int map_off) {
-  o << "static constexpr int kN = " << p.n << ", kNocc = " << p.occ_src.size()
-    << ", kS = " << (p.path == VQC_PATH_RESIDENT ? p.S : 1) << ";\n"
-    << "__device__ __forceinline__ static uint32_t zmask(const uint8_t*, const uint32_t*, "
-       "int q) {\n";
-  // physical bits of each measured qubit's Z-string under this mapping
+// Statements of a linear schedule (linear_plan.h): no CNOT runs, a rotation
+// pairs amplitudes along a mask of register bits with the sign of a parity
+// over all physical bits.  A parity over the bits above the registers costs
+// three instructions per gate (and, popcount, shift) and one sign flip of t (and
+// of the gradient); a CNOT as a gate cost about as much, needed its target on a
+// register bit and blocked the gates of later layers.  Measured on one box,
+// steps with the CNOTs as gates and without: 12 qubits, 6 strongly entangling
+// layers, 4096 samples 751 -> 493 us (33 -> 11-15 exchanges per sweep); 16-qubit
+// ring of 8 Rot layers, 256 samples 1543 -> 1060 us (10 -> 5 passes each way);
+// 20 qubits, 4 layers, 3 samples 298 -> 197 us (6 -> 3 passes); 13-qubit
+// forward, 128 samples 40.9 -> 28.7 us (37 -> 14 exchanges).
+void emit_linear(std::ostringstream& o, const Plan& p, const LinIns* ins, int n_ins, bool bwd,
+                 int R, int k, const GradMode& gm, const TanMode& tm) {
+  const bool tan = tm.on;
+  // Batched pending partials: with 16 amplitudes per thread the pending
+  // registers sit beside psi and lambda.  Not in 1024-thread workgroups (a
+  // 14-qubit resident sample): those hold at most 128 VGPRs, and the pending
+  // registers spilled 1.1 KiB per thread there (569 k -> 444 k evals/s).
+  Emit E{o, p, bwd, R, gm, batched_flush(p, bwd, gm, R, k), Pending(), tan, {}, 0, 0, 0, nullptr};
+  E.nrot = (int)(bwd ? tm.bocc.size() : tm.focc.size());
+  E.sign = [](uint32_t mask) {
+    // from an opaque copy of tb, so that the masks are not kept alive
+    if (!(mask & (mask - 1u)))
+      return "(opaque(w.tb) << " + std::to_string(31 - __builtin_ctz(mask)) + ") & 0x80000000u";
+    return "(uint32_t)__builtin_popcount(opaque(w.tb) & " + hex(mask) + ") << 31";
+  };
+  emit_pending_decl(E);
+  if (tan && bwd)
+    o << "  const float* gmul = reinterpret_cast<const float*>(w.smem + " << tm.off_gm << "u);\n";
+  if (tan) o << "  float bp = 1.f;\n";
+  // The stream in the order it runs: gates, and runs of RZs split into the
+  // diagonals to apply and single gates.
+  struct Unit {
+    const LinIns* gate;
+    std::vector<RzItem> run;
+  };
+  const uint32_t regs = (1u << R) - 1u;
+  std::vector<Unit> units;
+  auto held = [&](const LinIns& n) { return n.op == OP_RZ && p.occ_src[n.arg] != kSrcConst; };
+  for (int i = 0; i < n_ins;) {
+    if (!tan || !held(ins[i])) {
+      units.push_back({&ins[i++], {}});
+      continue;
+    }
+    std::vector<RzItem> run;
+    const int first = i;
+    for (; i < n_ins && held(ins[i]); ++i)
+      run.push_back({ins[i].arg, ins[i].slot, ins[i].z & regs, ins[i].z >> R});
+    std::vector<std::vector<RzItem>> fused;
+    std::vector<RzItem> single;
+    split_run(run, R, bwd, fused, single);
+    for (const auto& f : fused) units.push_back({nullptr, f});
+    for (const RzItem& it : single)
+      for (int j = first; j < i; ++j)
+        if (ins[j].arg == it.occ) units.push_back({&ins[j], {}});
+  }
+  for (const Unit& u : units) {
+    if (!u.gate)
+      for (const RzItem& it : u.run) E.rots.push_back(it.occ);
+    else if (u.gate->op == OP_RX || u.gate->op == OP_RY || u.gate->op == OP_RZ)
+      E.rots.push_back(u.gate->arg);
+  }
+  // The table entries of the next rotation are read one gate ahead (tangent
+  // form): each gate is its own basic block (gate_boundary), so a read placed
+  // in the gate that uses it would leave the LDS latency exposed at every
+  // rotation.
+  if (tan && !E.rots.empty()) {
+    o << "  float2 tcn = w.tab[" << E.rots[0] << "];\n";
+    if (bwd) o << "  float gmn = gmul[" << E.rots[0] << "];\n";
+  }
+  for (size_t i = 0; i < units.size(); ++i) {
+    if (!units[i].gate) {
+      emit_rz_run(E, units[i].run);
+      continue;
+    }
+    const LinIns& n = *units[i].gate;
+    if (n.op == OP_EXCHANGE) {
+      if (n.lam) emit_exchange_code(E, (uint32_t)n.arg, k, {"l"});
+      else if (bwd) emit_exchange_code(E, (uint32_t)n.arg, k, {"a", "l"});
+      else emit_exchange_code(E, (uint32_t)n.arg, k, {"a"});
+      continue;
+    }
+    if (n.op == OP_CZ) {
+      std::vector<CzItem> run;
+      size_t end = i;
+      for (; end < units.size() && units[end].gate && units[end].gate->op == OP_CZ; ++end)
+        run.push_back({units[end].gate->z, units[end].gate->z2});
+      emit_cz_run(E, run);
+      i = end - 1;
+      continue;
+    }
+    const std::string kind = n.op == OP_RX ? "rx" : n.op == OP_RY ? "ry" : "rz";
+    const std::string masks = n.op == OP_RX ? std::to_string(n.x)
+                              : n.op == OP_RY ? std::to_string(n.x) + ", " + std::to_string(n.z & regs)
+                                              : std::to_string(n.z & regs);
+    const uint32_t thr = n.op == OP_RX ? 0u : n.z >> R;
+    emit_slot_ready(E, n.slot);
+    o << "  { ";
+    if (tan) {
+      o << "const float2 tc = tcn; ";
+      if (bwd) o << "const float gm = gmn; ";
+      if (++E.ri < E.rots.size()) {
+        o << "tcn = w.tab[" << E.rots[E.ri] << "]; ";
+        if (bwd) o << "gmn = gmul[" << E.rots[E.ri] << "]; ";
+      }
+    } else {
+      o << "const float2 cs = w.tab[" << n.arg << "]; ";
+    }
+    const std::string from = tan ? "tc.x" : "cs.y";
+    if (thr) o << "const uint32_t fs = " << E.sign(thr) << "; const float t = flip_sign(" << from
+               << ", fs); ";
+    else o << "const float t = " << from << "; ";
+    const std::string tail = tan ? "t);" : "cs.x, t);";
+    if (!bwd) {
+      o << kind << (tan ? "_t<R, " : "_reg<R, ") << masks << ">(a, " << tail;
+    } else {
+      o << "float g = adj_" << kind << (tan ? "_t<R, " : "<R, ") << masks << ">(a, l, " << tail;
+      if (thr) o << " g = flip_sign(g, fs);";
+      // the states carry 1 / (the factors of the block before this gate)
+      if (tan) o << " g *= gm * (bp * bp);";
+      o << occ_scale(p, (uint32_t)n.arg);
+    }
+    if (tan) o << " bp *= tc.y;";
+    if (bwd) emit_collect(E, n.slot);
+    if (tan) emit_rescale(E, 1);
+    o << " gate_boundary(w); }\n";
+  }
+  if (E.batched) emit_flush(o, E.pend);
+}
+
+// Physical bits of each measured qubit's Z-string under the mapping (qubit ->
+// physical bit) at map_off in the plan's maps.
+std::vector<uint32_t> z_masks(const Plan& p, int map_off) {
   std::vector<uint32_t> zm(p.n);
   for (int q = 0; q < p.n; ++q) {
     const uint32_t m = p.zmask.empty() ? 1u << q : p.zmask[q];
@@ -1218,6 +1345,19 @@ void emit_constants(std::ostringstream& o, const Plan& p, int map_off) {
       if ((m >> b) & 1u) pm |= 1u << p.maps[map_off + b];
     zm[q] = pm;
   }
+  return zm;
+}
+
+// The circuit's constants, compiled in (the interpreter reads them from the
+// plan's arrays): the qubit count, the parity masks of the measured Z-strings
+// that the <Z> epilogue or the forming of lambda uses (zm, see z_masks), and
+// every angle occurrence's record.  A gate list's constants then cost no
+// dependent loads from device memory before the first gate.
+void emit_constants(std::ostringstream& o, const Plan& p, const std::vector<uint32_t>& zm) {
+  o << "static constexpr int kN = " << p.n << ", kNocc = " << p.occ_src.size()
+    << ", kS = " << (p.path == VQC_PATH_RESIDENT ? p.S : 1) << ";\n"
+    << "__device__ __forceinline__ static uint32_t zmask(const uint8_t*, const uint32_t*, "
+       "int q) {\n";
   emit_array(o, "uint32_t", "t", zm);
   o << "  return t[q];\n}\n"
     << "__device__ __forceinline__ static OccRec occ(const int32_t*, const int32_t*, const float*, "
@@ -1276,16 +1416,33 @@ void emit_constants(std::ostringstream& o, const Plan& p, int map_off) {
   o << std::defaultfloat;
 }
 
+// logical(): the basis-state index of each of a thread's amplitudes at the end
+// of a resident linear schedule's forward (the trailing entanglers included),
+// the XOR of one column per physical bit.
+void emit_logical(std::ostringstream& o, const Plan& p, bool linear) {
+  o << "static constexpr bool kLinear = " << (linear ? "true" : "false") << ";\n";
+  if (!linear) return;
+  const std::vector<uint32_t>& c = p.lin.lcol;
+  o << "template <int R>\n"
+    << "__device__ __forceinline__ static LogicalIndex<R> logical(uint32_t tb) {\n"
+    << "  LogicalIndex<R> li;\n  li.xt = 0u; li.pr = 0u; li.pt = false;\n";
+  for (int b = 0; b < p.R; ++b) o << "  li.rq[" << b << "] = " << hex(c[b]) << ";\n";
+  for (int b = p.R; b < p.k; ++b)
+    o << "  li.xt ^= ((tb >> " << b - p.R << ") & 1u) ? " << hex(c[b]) << " : 0u;\n";
+  o << "  return li;\n}\n";
+}
+
 // A schedule struct: run() for one stream, the group sum used for <Z>, and
 // (when `tables`) the kernel's tangent-form tables.
 void emit_sched_struct(std::ostringstream& o, const std::string& name, const Plan& p,
-                       const uint32_t* ins, int n_ins, bool bwd, int R, int k, int S,
-                       const GradMode& gm, const TanMode& tm, const Frame* tables, int map_off,
+                       const Stream& st, bool bwd, int R, int k, int S, const GradMode& gm,
+                       const TanMode& tm, const Frame* tables, const std::vector<uint32_t>& zm,
                        bool load = false, int fixed_flags = -1,
                        const std::vector<char>* skip = nullptr,
-                       const std::string& head = std::string(), FrameEnd fend = kFrameResolve) {
+                       const std::string& head = std::string()) {
   o << "struct " << name << " {\n";
-  emit_constants(o, p, map_off);
+  emit_constants(o, p, zm);
+  emit_logical(o, p, st.lin && p.path == VQC_PATH_RESIDENT);
   o << "static constexpr int kFixedFlags = " << fixed_flags << ";\n";
   // the streaming step's product head (stream_product_start, stream_head_partials)
   if (head.empty()) o << "static constexpr bool kProductStart = false, kHeadPartials = false;\n";
@@ -1300,7 +1457,8 @@ void emit_sched_struct(std::ostringstream& o, const std::string& name, const Pla
     o << "  const uint32_t ln = (uint32_t)w.stid & " << gm.tm - 1 << "u;\n"
       << "  float ga[" << gm.nr << "];\n"
       << "#pragma unroll\n  for (int j = 0; j < " << gm.nr << "; ++j) ga[j] = 0.f;\n";
-  emit_schedule(o, p, ins, n_ins, bwd, R, k, S, gm, tm, skip, fend);
+  if (st.lin) emit_linear(o, p, st.lin, st.n, bwd, R, k, gm, tm);
+  else emit_schedule(o, p, st.ins, st.n, bwd, R, k, S, gm, tm, skip);
   if (regs)  // every (slot, group) accumulator is written by exactly one lane
     o << "#pragma unroll\n  for (int j = 0; j < " << gm.nr << "; ++j) {\n"
       << "    const uint32_t slot = j * " << gm.tm << "u + "
@@ -1340,22 +1498,17 @@ bool tangent_wanted(int S, int R) {
 // in parallel.  esign: the kernel computes <Z> (forward) or forms lambda
 // (adjoint).
 std::string kernel_unit(const Plan& p, const Frame& fr, const std::string& name,
-                        const uint32_t* ins, int n_ins, bool bwd, bool stream, int R, int S,
-                        int threads, size_t lds, int n_slots, bool esign, int map_off,
+                        const Stream& st, bool bwd, bool stream, int R, int S, int threads,
+                        size_t lds, int n_slots, bool esign, const std::vector<uint32_t>& zm,
                         bool load = false, int fixed_flags = -1,
                         const std::string& head = std::string()) {
   std::ostringstream o;
   o << "#include \"vqc_device.h\"\nnamespace vqc {\n";
   const int lanes = stream ? threads : 1 << (p.k - R);
-  TanMode tm = tan_mode(p, bwd ? nullptr : ins, n_ins, bwd ? ins : nullptr, n_ins, S, esign, lds);
+  TanMode tm = tan_mode(p, bwd ? nullptr : &st, bwd ? &st : nullptr, S, esign, lds);
   tm.on = tm.on && tangent_wanted(S, R);
-  // the swap frame at the stream's end: resolved where the state is read or
-  // stored after the sweep, dropped by a resident adjoint and by the last
-  // streaming adjoint pass without a product head (nothing reads their states)
-  FrameEnd fend = bwd ? kFrameDrop : kFrameResolve;
-  if (stream && bwd && (!(fixed_flags & PF_LAST_ADJ) || !head.empty())) fend = kFrameResolve;
-  emit_sched_struct(o, "Sched", p, ins, n_ins, bwd, R, p.k, S, grad_mode(lanes, n_slots), tm, &fr,
-                    map_off, load, fixed_flags, nullptr, head, fend);
+  emit_sched_struct(o, "Sched", p, st, bwd, R, p.k, S, grad_mode(lanes, n_slots), tm, &fr, zm,
+                    load, fixed_flags, nullptr, head);
   o << "}  // namespace vqc\n"
     << "extern \"C\" __global__ void __launch_bounds__(" << threads << ") " << occupancy(R)
     << name
@@ -1557,7 +1710,7 @@ void emit_head_contraction(std::ostringstream& o, const Plan& p, const std::vect
 int head_nv(const Plan& p) { return (4 * p.n + 15) / 16 * 16; }
 
 // struct Head of the training step: the head tables and mappings.
-void emit_head(std::ostringstream& o, const Plan& p, size_t off) {
+void emit_head(std::ostringstream& o, const Plan& p, size_t off, int start_off, int end_off) {
   const int L = head_len(p), n = p.n, k = p.k, R = p.R;
   o << "struct Head {\n"
     << "static constexpr bool kOn = true;\n"
@@ -1566,8 +1719,8 @@ void emit_head(std::ostringstream& o, const Plan& p, size_t off) {
   emit_head_pre(o, p, "preload");
   o << "using Pre = HeadPre<kL>;\n";
   std::vector<int> sreg, sthr, ereg, ethr;
-  head_bits(p, p.start_off, R, k - R, sreg, sthr);
-  head_bits(p, p.bwd_end_off, R, k - R, ereg, ethr);
+  head_bits(p, start_off, R, k - R, sreg, sthr);
+  head_bits(p, end_off, R, k - R, ereg, ethr);
   // init(): every head walked by its qubit's lane, then the product state in
   // the forward's start mapping
   o << "template <int R>\n"
@@ -1697,8 +1850,17 @@ std::string step_unit(const Plan& p, const Frame& fr) {
   o << "#include \"vqc_device.h\"\nnamespace vqc {\n";
   const int lanes = 1 << (p.k - p.R);
   const GradMode gm = grad_mode(lanes, p.P + p.F);
-  const int nf = (int)p.fwd.size() / 2, nb = (int)p.bwd.size() / 2;
-  TanMode tm = tan_mode(p, p.fwd.data(), nf, p.bwd.data(), nb, p.S, true, p.lds_step);
+  Stream f{p.fwd.data(), nullptr, (int)p.fwd.size() / 2};
+  Stream b{p.bwd.data(), nullptr, (int)p.bwd.size() / 2};
+  // a linear schedule without the heads' rotations, or with them when the head
+  // records below do not fit
+  const LinSchedule* lin = p.linear ? &p.lin_step : nullptr;
+  auto use_linear = [&] {
+    f = Stream{nullptr, lin->f.data(), (int)lin->f.size()};
+    b = Stream{nullptr, lin->b.data(), (int)lin->b.size()};
+  };
+  if (lin) use_linear();
+  TanMode tm = tan_mode(p, &f, &b, p.S, true, p.lds_step);
   tm.on = tm.on && tangent_wanted(p.S, p.R);
   std::vector<char> head = head_occurrences(p, tm);
   size_t head_off = 0, end = tm.on ? tm.end : p.lds_step;
@@ -1720,13 +1882,19 @@ std::string step_unit(const Plan& p, const Frame& fr) {
       head.clear();
     }
   }
+  if (lin && head.empty()) {
+    lin = &p.lin;
+    use_linear();
+    tm.focc = stream_rotations(f);
+    tm.bocc = stream_rotations(b);
+  }
   const std::vector<char>* skip = head.empty() ? nullptr : &head;
-  emit_sched_struct(o, "SchedF", p, p.fwd.data(), nf, false, p.R, p.k, p.S, gm, tm, &fr,
-                    p.end_off, false, -1, skip, std::string(), kFrameResolve);
-  emit_sched_struct(o, "SchedB", p, p.bwd.data(), nb, true, p.R, p.k, p.S, gm, tm, nullptr,
-                    p.end_off, false, -1, skip, std::string(),
-                    skip ? kFrameResolve : kFrameDrop);
-  if (skip) emit_head(o, p, head_off);
+  const std::vector<uint32_t> zm = lin ? lin->zrow : z_masks(p, p.end_off);
+  emit_sched_struct(o, "SchedF", p, f, false, p.R, p.k, p.S, gm, tm, &fr, zm, false, -1, skip);
+  emit_sched_struct(o, "SchedB", p, b, true, p.R, p.k, p.S, gm, tm, nullptr, zm, false, -1, skip);
+  if (skip)
+    emit_head(o, p, head_off, lin ? lin->start_off : p.start_off,
+              lin ? lin->bwd_end_off : p.bwd_end_off);
   o << "}  // namespace vqc\n"
     << "extern \"C\" __global__ void __launch_bounds__(" << p.WG << ") " << occupancy(p.R)
     << "vqc_rs(const vqc::TileArgs A) {\n"
@@ -1768,7 +1936,7 @@ std::string table_unit(const Plan& p, const Frame& fr, const std::string& name =
   if (!t.on) return "";
   std::ostringstream o;
   o << "#include \"vqc_device.h\"\nnamespace vqc {\nstruct Sched {\n";
-  emit_constants(o, p, p.end_off);
+  emit_constants(o, p, p.lin.zrow);
   emit_tables(o, p, t, fr, kTableThreads, true, false, head.empty() ? nullptr : &head);
   o << "};\n}  // namespace vqc\n"
     << "extern \"C\" __global__ void __launch_bounds__(" << kTableThreads
@@ -1782,12 +1950,17 @@ std::vector<JitUnit> jit_units(const Plan& p) {
   std::vector<JitUnit> u;
   const Frame fr = frame_rows(p);
   if (p.path == VQC_PATH_RESIDENT) {
-    u.push_back({"vqc_rf", kernel_unit(p, fr, "vqc_rf", p.fwd.data(), (int)p.fwd.size() / 2,
-                                       false, false, p.R, p.S, p.WG, p.lds_fwd, p.P + p.F, true,
-                                       p.end_off), 'r'});
-    u.push_back({"vqc_rb", kernel_unit(p, fr, "vqc_rb", p.bwd.data(), (int)p.bwd.size() / 2,
-                                       true, false, p.R, p.S, p.WG, p.lds_bwd, p.P + p.F, true,
-                                       p.end_off), 'b'});
+    Stream f{p.fwd.data(), nullptr, (int)p.fwd.size() / 2};
+    Stream b{p.bwd.data(), nullptr, (int)p.bwd.size() / 2};
+    if (p.linear) {
+      f = Stream{nullptr, p.lin.f.data(), (int)p.lin.f.size()};
+      b = Stream{nullptr, p.lin.b.data(), (int)p.lin.b.size()};
+    }
+    const std::vector<uint32_t> zm = p.linear ? p.lin.zrow : z_masks(p, p.end_off);
+    u.push_back({"vqc_rf", kernel_unit(p, fr, "vqc_rf", f, false, false, p.R, p.S, p.WG, p.lds_fwd,
+                                       p.P + p.F, true, zm), 'r'});
+    u.push_back({"vqc_rb", kernel_unit(p, fr, "vqc_rb", b, true, false, p.R, p.S, p.WG, p.lds_bwd,
+                                       p.P + p.F, true, zm), 'b'});
     u.push_back({"vqc_rs", step_unit(p, fr), 's'});
     return u;
   }
@@ -1802,20 +1975,20 @@ std::vector<JitUnit> jit_units(const Plan& p) {
     const PassPlan& pp = p.fpass[i];
     const std::string head = ph && (pp.flags & PF_INIT)
                                  ? stream_product_start(p, pp.start_off, p.Rf) : std::string();
-    u.push_back({name, kernel_unit(p, fr, name, p.fwd.data() + 2 * pp.ins_off, pp.n_ins, false,
-                                   true, p.Rf, 1, 1 << (p.k - p.Rf), p.lds_fwd, pp.n_slots,
-                                   (pp.flags & PF_ZPART) != 0, pp.end_off, load,
-                                   (int)(pp.flags & ~PF_INIT), head), 'F'});
+    const Stream st{nullptr, p.lin.f.data() + pp.ins_off, pp.n_ins};
+    u.push_back({name, kernel_unit(p, fr, name, st, false, true, p.Rf, 1, 1 << (p.k - p.Rf),
+                                   p.lds_fwd, pp.n_slots, (pp.flags & PF_ZPART) != 0, p.lin.zrow,
+                                   load, (int)(pp.flags & ~PF_INIT), head), 'F'});
   }
   for (size_t i = 0; i < p.bpass.size(); ++i) {
     const std::string name = pre + "b" + std::to_string(i);
     const PassPlan& pp = p.bpass[i];
     const std::string head = ph && (pp.flags & PF_LAST_ADJ)
                                  ? stream_head_partials(p, pp.end_off, p.Rb) : std::string();
-    u.push_back({name, kernel_unit(p, fr, name, p.bwd.data() + 2 * pp.ins_off, pp.n_ins, true,
-                                   true, p.Rb, 1, 1 << (p.k - p.Rb), p.lds_bwd, pp.n_slots,
-                                   (pp.flags & PF_MAKE_LAMBDA) != 0, pp.start_off, load,
-                                   (int)(pp.flags & ~PF_INIT), head), 'B'});
+    const Stream st{nullptr, p.lin.b.data() + pp.ins_off, pp.n_ins};
+    u.push_back({name, kernel_unit(p, fr, name, st, true, true, p.Rb, 1, 1 << (p.k - p.Rb),
+                                   p.lds_bwd, pp.n_slots, (pp.flags & PF_MAKE_LAMBDA) != 0,
+                                   p.lin.zrow_b, load, (int)(pp.flags & ~PF_INIT), head), 'B'});
   }
   if (load) u.push_back({pre + "t", tables, 'T'});
   if (ph) u.push_back({"vqc_hg", head_finish_unit(p, "vqc_hg"), 'G'});

@@ -1,0 +1,940 @@
+// linear_plan.h -- schedules of the generated kernels that hold one sample per
+// workgroup (part of planner.cpp).
+//
+// Entanglers as a change of basis.  A CNOT permutes basis states linearly over
+// GF(2), so it need not run: the state is kept as if no CNOT had been applied,
+// and every later gate is the Pauli rotation (or pair of Z-strings, for a CZ)
+// that the CNOTs before it turn it into.  In these fixed coordinates y in
+// GF(2)^n qubit q's X acts as y -> y ^ v_q and its Z reads parity(w_q & y);
+// CNOT(c, t) maps v_c ^= v_t, w_t ^= w_c.  A rotation is then a pair (x, z):
+// RX pairs y with y ^ x, RY does so with the sign of parity(z & y), RZ and CZ
+// are diagonal in parities, and two gates commute when their symplectic product
+// is even, which lets more gates pass a waiting one than disjoint qubits do.
+//
+// A layout of the register tile is any basis of GF(2)^n: physical bit p moves
+// along vector b[p].  A gate runs where its x lies in the span of the register
+// bits' vectors; an exchange changes the local basis by any invertible map for
+// the price of a permutation.  A streaming pass holds a k-dimensional subspace
+// and the states between two passes are stored in a basis in which both
+// passes' subspaces are spanned by address bits.  Measured on one box against
+// the schedules that run the CNOTs: see emit_linear (jit.cpp).
+
+// An echelon basis of a subspace, by leading bit.
+struct Span {
+  uint32_t row[32];
+  int dim = 0;
+  Span() { std::memset(row, 0, sizeof row); }
+  uint32_t residue(uint32_t v) const {
+    for (uint32_t todo = v; todo;) {
+      const int b = 31 - __builtin_clz(todo);
+      if (row[b]) v ^= row[b];
+      todo = b ? v & ((1u << b) - 1u) : 0u;
+    }
+    return v;
+  }
+  bool holds(uint32_t v) const { return residue(v) == 0; }
+  bool add(uint32_t v) {
+    v = residue(v);
+    if (!v) return false;
+    row[31 - __builtin_clz(v)] = v;
+    ++dim;
+    return true;
+  }
+};
+
+uint32_t odd(uint32_t v) { return (uint32_t)__builtin_parity(v); }
+
+// The Paulis of the gates left waiting in a scan, kept by column (bit r of
+// cx[b]: row r's x has bit b) so that a test costs one XOR per bit of the tested
+// Pauli.  Rows are appended as they come; when all 64 are taken they are
+// replaced by a basis of their span (at most 2 kMaxQubits rows), which blocks
+// the same Paulis.
+struct Waiting {
+  uint64_t cx[32], cz[32];
+  uint64_t row[64];
+  int rows = 0;
+  Waiting() {
+    std::memset(cx, 0, sizeof cx);
+    std::memset(cz, 0, sizeof cz);
+  }
+  void append(uint64_t v) {
+    row[rows] = v;
+    for (uint32_t m = (uint32_t)(v >> 32); m; m &= m - 1u) cx[__builtin_ctz(m)] |= 1ull << rows;
+    for (uint32_t m = (uint32_t)v; m; m &= m - 1u) cz[__builtin_ctz(m)] |= 1ull << rows;
+    ++rows;
+  }
+  void compress() {
+    uint64_t lead[64] = {0}, keep[64];
+    int n = 0;
+    for (int r = 0; r < rows; ++r)
+      for (uint64_t v = row[r]; v;) {
+        const int b = 63 - __builtin_clzll(v);
+        if (!lead[b]) {
+          keep[n++] = lead[b] = v;
+          break;
+        }
+        v ^= lead[b];
+      }
+    *this = Waiting();
+    for (int r = 0; r < n; ++r) append(keep[r]);
+  }
+  void add(uint32_t x, uint32_t z) {
+    if (rows == 64) compress();
+    append((uint64_t)x << 32 | z);
+  }
+  bool blocks(uint32_t x, uint32_t z) const {
+    uint64_t anti = 0;
+    for (; z; z &= z - 1u) anti ^= cx[__builtin_ctz(z)];
+    for (; x; x &= x - 1u) anti ^= cz[__builtin_ctz(x)];
+    return anti != 0;
+  }
+};
+static_assert(2 * kMaxQubits < 64, "a basis of the waiting Paulis leaves room for another row");
+
+// A gate in the fixed coordinates: kind P_RX, P_RY, P_RZ (x = 0) or P_CZ (z, z2).
+struct LinGate {
+  int kind;
+  uint32_t x, z, z2;
+  int occ;
+  bool held;  // a diagonal gate taken in runs: a CZ, or an RZ whose angle varies
+};
+
+// The circuit's gates (those of `skip` left out), and the rows of every
+// measured qubit's Z after the whole circuit, the folded trailing entanglers
+// included.
+std::vector<LinGate> linear_gates(const Plan& plan, const std::vector<char>* skip,
+                                  std::vector<uint32_t>& wfull) {
+  uint32_t v[kMaxQubits], w[kMaxQubits];
+  for (int q = 0; q < kMaxQubits; ++q) v[q] = w[q] = 1u << q;
+  std::vector<LinGate> g;
+  for (const Prim& p : plan.prims) {
+    switch (p.kind) {
+      case P_CNOT:
+        v[p.q0] ^= v[p.q1];
+        w[p.q1] ^= w[p.q0];
+        break;
+      case P_CZ: g.push_back({P_CZ, 0u, w[p.q0], w[p.q1], -1, true}); break;
+      default:
+        if (skip && (*skip)[p.occ]) break;
+        g.push_back({p.kind, p.kind == P_RZ ? 0u : v[p.q0], p.kind == P_RX ? 0u : w[p.q0], 0u,
+                     p.occ, p.kind == P_RZ && plan.occ_src[p.occ] != VQC_SRC_CONST});
+    }
+  }
+  for (const Prim& p : plan.tail)
+    if (p.kind == P_CNOT) w[p.q1] ^= w[p.q0];
+  wfull.assign(w, w + plan.n);
+  return g;
+}
+
+// Which gates a scan may take: all; all but the held diagonals; diagonals only.
+enum ScanMode { kTakeAll, kTakeEager, kTakeDiagonal };
+
+// occ_slot: at most `cap` gradient slots per streaming pass (its accumulators
+// in LDS).
+struct ScanLimits {
+  int cap = INT_MAX;
+  const std::vector<int32_t>* occ_slot = nullptr;
+  size_t window = SIZE_MAX;  // gates looked at
+};
+
+// Walks the gates `pos` in order and takes every one that commutes with all
+// gates left waiting before it, may run (mode, slot cap) and moves along a
+// vector of S.  Returns how many of those taken are not diagonal.  cand: the
+// directions outside S of gates that nothing else stops, one per coset.
+int scan_gates(const std::vector<LinGate>& g, const std::vector<int>& pos, const Span& S,
+               ScanMode mode, const ScanLimits& cap, std::vector<int>* took,
+               std::vector<uint32_t>* cand) {
+  constexpr size_t kMaxCand = 16;
+  constexpr int kGiveUp = 128;  // gates stopped in a row: those after them stay for a later scan
+  Waiting wait;
+  std::set<int> slots;
+  int stopped = 0;
+  std::vector<uint32_t> cosets;
+  int count = 0;
+  const size_t end = std::min(pos.size(), cap.window);
+  for (size_t j = 0; j < end && stopped < kGiveUp; ++j) {
+    const int i = pos[j];
+    const LinGate& e = g[i];
+    bool stop = wait.blocks(e.x, e.z) || (e.kind == P_CZ && wait.blocks(0u, e.z2));
+    if (!stop) stop = mode == kTakeEager ? e.held : mode == kTakeDiagonal ? e.x != 0u : false;
+    if (!stop && cap.occ_slot && e.occ >= 0) {
+      const int s = (*cap.occ_slot)[e.occ];
+      if (s >= 0 && !slots.count(s)) {
+        if ((int)slots.size() >= cap.cap) stop = true;
+        else if (S.holds(e.x)) slots.insert(s);
+      }
+    }
+    if (!stop) {
+      const uint32_t r = S.residue(e.x);
+      if (!r) {
+        stopped = 0;
+        if (took) took->push_back(i);
+        if (e.x) ++count;
+        continue;
+      }
+      if (cand && cand->size() < kMaxCand &&
+          std::find(cosets.begin(), cosets.end(), r) == cosets.end()) {
+        cosets.push_back(r);
+        cand->push_back(e.x);
+      }
+    }
+    ++stopped;
+    wait.add(e.x, e.z);
+    if (e.kind == P_CZ) wait.add(0u, e.z2);
+  }
+  return count;
+}
+
+// Up to `dims` independent directions that let a scan take the most gates:
+// grown one at a time, by the count each candidate gives (ties: the earlier
+// gate's), or in circuit order; the better of the two.
+std::vector<uint32_t> choose_directions(const std::vector<LinGate>& g, const std::vector<int>& pos,
+                                        int dims, ScanMode mode, const ScanLimits& cap) {
+  std::vector<uint32_t> best;
+  int best_count = -1;
+  for (int look = 1; look >= 0; --look) {
+    Span S;
+    std::vector<uint32_t> dirs;
+    while ((int)dirs.size() < dims) {
+      std::vector<uint32_t> cand;
+      scan_gates(g, pos, S, mode, cap, nullptr, &cand);
+      if (cand.empty()) break;
+      size_t pick = 0;
+      if (look && cand.size() > 1) {
+        int most = -1;
+        for (size_t c = 0; c < cand.size(); ++c) {
+          Span s = S;
+          s.add(cand[c]);
+          const int n = scan_gates(g, pos, s, mode, cap, nullptr, nullptr);
+          if (n > most) {
+            most = n;
+            pick = c;
+          }
+        }
+      }
+      S.add(cand[pick]);
+      dirs.push_back(cand[pick]);
+    }
+    const int n = scan_gates(g, pos, S, mode, cap, nullptr, nullptr);
+    if (n > best_count) {
+      best_count = n;
+      best = dirs;
+    }
+  }
+  return best;
+}
+
+// A basis of GF(2)^n: physical bit (or address bit) p moves along b[p].
+struct Basis {
+  int n = 0;
+  uint32_t b[kMaxQubits] = {0};
+  uint32_t inv[kMaxQubits] = {0};  // coordinate p of v is parity(inv[p] & v)
+  bool invert() {
+    uint32_t m[kMaxQubits], id[kMaxQubits];
+    for (int i = 0; i < n; ++i) {
+      m[i] = 0;
+      for (int p = 0; p < n; ++p) m[i] |= ((b[p] >> i) & 1u) << p;
+      id[i] = 1u << i;
+    }
+    for (int p = 0; p < n; ++p) {
+      int r = p;
+      while (r < n && !((m[r] >> p) & 1u)) ++r;
+      if (r == n) return false;
+      std::swap(m[r], m[p]);
+      std::swap(id[r], id[p]);
+      for (int i = 0; i < n; ++i)
+        if (i != p && ((m[i] >> p) & 1u)) {
+          m[i] ^= m[p];
+          id[i] ^= id[p];
+        }
+    }
+    for (int p = 0; p < n; ++p) inv[p] = id[p];
+    return true;
+  }
+  uint32_t coord(uint32_t v) const {
+    uint32_t c = 0;
+    for (int p = 0; p < n; ++p) c |= odd(inv[p] & v) << p;
+    return c;
+  }
+  uint32_t row(uint32_t z) const {  // parity mask over the bits of a parity of coordinates
+    uint32_t m = 0;
+    for (int p = 0; p < n; ++p) m |= odd(z & b[p]) << p;
+    return m;
+  }
+  bool same(const Basis& o) const { return std::memcmp(b, o.b, sizeof(uint32_t) * n) == 0; }
+  bool unit() const {
+    for (int p = 0; p < n; ++p)
+      if (b[p] & (b[p] - 1u)) return false;
+    return true;
+  }
+};
+
+// Exchange tables from basis A to basis B of the same k-dimensional local
+// space.  The LDS slot of an amplitude is a linear function lam of its
+// position; its bank bits are independent on the lane bits' span of A and on
+// that of B, so that 32 consecutive lanes hit 32 banks both when writing and
+// when reading: on the intersection of the spans the bank bits are shared, and
+// each further vector of B's span takes the bank bit of one of A's.  The rest
+// of lam numbers the bank bits' kernel.
+int emit_linear_exchange(const Basis& A, const Basis& B, int k, int R,
+                         std::vector<uint32_t>& cols) {
+  const int lb = std::min(kBankBits, k - R);
+  // B's vectors in A's coordinates
+  uint32_t in_a[kMaxQubits];
+  for (int p = 0; p < k; ++p) in_a[p] = A.coord(B.b[p]);
+  const uint32_t lanes = ((1u << lb) - 1u) << R;
+  // UB = span of in_a[R .. R + lb): vectors reduced outside A's lane bits
+  std::vector<std::pair<uint32_t, uint32_t>> out;  // (reduced outside part, vector)
+  std::vector<uint32_t> both, rest;                // UB within UA; UB's others
+  for (int i = 0; i < lb; ++i) {
+    uint32_t v = in_a[R + i], o = v & ~lanes;
+    for (const auto& e : out)
+      if (o & (e.first & (0u - e.first))) {
+        o ^= e.first;
+        v ^= e.second;
+      }
+    if (o) {
+      for (auto& e : out)
+        if (e.first & (o & (0u - o))) {
+          e.first ^= o;
+          e.second ^= v;
+        }
+      out.push_back({o, v});
+    } else {
+      both.push_back(v);
+    }
+  }
+  for (const auto& e : out) rest.push_back(e.second);
+  // a basis of the local space: both | part of UA | rest | others, with lam of each
+  Basis full;
+  full.n = k;
+  uint32_t lam[kMaxQubits] = {0};
+  Span s;
+  int at = 0, bank = 0, high = lb;
+  for (uint32_t v : both) {
+    s.add(v);
+    lam[at] = 1u << bank++;
+    full.b[at++] = v;
+  }
+  const int shared = bank;
+  for (int i = 0; i < lb; ++i)
+    if (s.add(1u << (R + i))) {
+      lam[at] = 1u << bank++;
+      full.b[at++] = 1u << (R + i);
+    }
+  int j = shared;
+  for (uint32_t v : rest)
+    if (s.add(v)) {
+      lam[at] = 1u << j++ | 1u << high++;
+      full.b[at++] = v;
+    }
+  for (int p = 0; p < k; ++p)
+    if (s.add(1u << p)) {
+      lam[at] = 1u << high++;
+      full.b[at++] = 1u << p;
+    }
+  full.invert();
+  auto slot = [&](uint32_t v) {
+    const uint32_t c = full.coord(v);
+    uint32_t o = 0;
+    for (int p = 0; p < k; ++p)
+      if ((c >> p) & 1u) o ^= lam[p];
+    return o;
+  };
+  const int off = (int)cols.size();
+  for (int p = 0; p < k; ++p) cols.push_back(slot(1u << p));
+  for (int p = 0; p < k; ++p) cols.push_back(slot(in_a[p]));
+  // where each physical bit's vector goes (the generated kernels swap register
+  // bits with lane bits without LDS); k when it is not a vector of B
+  for (int p = 0; p < k; ++p) {
+    uint32_t d = (uint32_t)k;
+    for (int q = 0; q < k; ++q)
+      if (B.b[q] == A.b[p]) d = (uint32_t)q;
+    cols.push_back(d);
+  }
+  return off;
+}
+
+// The basis after an exchange that brings `dirs` onto the register bits:
+// vectors already on a register bit or a thread bit stay where they can, and
+// the register vectors that leave take the thread bits that came free.
+Basis exchanged(const Basis& A, const std::vector<uint32_t>& dirs, int k, int R) {
+  Span want, used;
+  for (uint32_t d : dirs) want.add(d);
+  Basis B = A;
+  std::vector<char> kept(R, 0);
+  int open = R;
+  for (int r = 0; r < R; ++r)
+    if (want.holds(A.b[r])) {
+      used.add(A.b[r]);
+      kept[r] = 1;
+      --open;
+    }
+  std::vector<uint32_t> in;
+  for (uint32_t d : dirs)
+    if (used.add(d)) in.push_back(d);
+  for (int r = 0; r < R && (int)in.size() < open; ++r)
+    if (!kept[r] && used.add(A.b[r])) {
+      kept[r] = 1;
+      --open;
+    }
+  size_t next = 0;
+  for (int r = 0; r < R; ++r)
+    if (!kept[r]) B.b[r] = in[next++];
+  std::vector<int> free_bits;
+  for (int p = R; p < k; ++p)
+    if (!used.add(A.b[p])) free_bits.push_back(p);
+  next = 0;
+  for (int r = 0; r < R; ++r)
+    if (!kept[r] && used.add(A.b[r])) B.b[free_bits[next++]] = A.b[r];
+  B.invert();
+  return B;
+}
+
+struct LinearSweep {
+  std::vector<LinIns> ins;
+  std::vector<uint32_t> cols;  // exchange tables, offsets relative to this vector
+  int exchanges = 0;
+  double cost = 0.0;
+  Basis end;
+};
+
+void linear_exchange(LinearSweep& s, const Basis& to, int k, int R, bool lam) {
+  LinIns e;
+  e.op = OP_EXCHANGE;
+  e.arg = emit_linear_exchange(s.end, to, k, R, s.cols);
+  e.lam = lam;
+  s.ins.push_back(e);
+  ++s.exchanges;
+  s.end = to;
+}
+
+// One register-level sweep over `g` from basis `start`.  Variable RZs and CZs
+// wait until at least `flush_at` other gates on the present register bits wait
+// for them (or nothing else can run): a run of diagonals costs about as much as
+// one of them, an exchange more.  The cost is an instruction count per wave:
+// per exchange and state the LDS accesses and addresses of 2^R amplitudes, per
+// run of diagonals the cheaper of gate by gate and one product.
+LinearSweep linear_sweep(const std::vector<LinGate>& g, const Basis& start, int k, int R, bool bwd,
+                         int flush_at) {
+  LinearSweep s;
+  s.end = start;
+  const double N = 1 << R, states = bwd ? 2.0 : 1.0;
+  const ScanLimits none;
+  ScanLimits near;  // an exchange runs about ten gates: those close by decide
+  near.window = 64;
+  std::vector<int> pos(g.size());
+  for (size_t i = 0; i < g.size(); ++i) pos[i] = (int)i;
+  auto emit_gates = [&](const std::vector<int>& took) {
+    for (int i : took) {
+      const LinGate& e = g[i];
+      LinIns n;
+      n.op = e.kind == P_RX ? OP_RX : e.kind == P_RY ? OP_RY : e.kind == P_RZ ? OP_RZ : OP_CZ;
+      n.x = s.end.coord(e.x);
+      n.z = s.end.row(e.z);
+      n.z2 = s.end.row(e.z2);
+      n.arg = e.occ;
+      s.ins.push_back(n);
+    }
+    std::vector<int> left;
+    size_t t = 0;
+    std::vector<int> sorted(took);
+    std::sort(sorted.begin(), sorted.end());
+    for (int i : pos) {
+      if (t < sorted.size() && sorted[t] == i) ++t;
+      else left.push_back(i);
+    }
+    pos.swap(left);
+  };
+  bool fresh = false;  // an exchange and nothing since
+  while (!pos.empty()) {
+    Span S;
+    for (int r = 0; r < R; ++r) S.add(s.end.b[r]);
+    std::vector<int> took;
+    scan_gates(g, pos, S, kTakeEager, none, &took, nullptr);
+    if (!took.empty()) {
+      emit_gates(took);
+      fresh = false;
+    }
+    if (pos.empty()) break;
+    const int ready = scan_gates(g, pos, S, kTakeAll, none, nullptr, nullptr);
+    std::vector<uint32_t> dirs;
+    bool flush = ready >= flush_at || (fresh && ready > 0);
+    if (!flush) {
+      dirs = choose_directions(g, pos, R, flush_at == INT_MAX ? kTakeEager : kTakeAll, near);
+      flush = true;
+      for (uint32_t d : dirs) flush = flush && S.holds(d);
+    }
+    if (flush) {
+      std::vector<int> diag, fixed, cz, rz;  // (all commute)
+      scan_gates(g, pos, S, kTakeDiagonal, none, &diag, nullptr);
+      if (diag.empty()) {  // only gates off the register bits are left to run
+        dirs = choose_directions(g, pos, R, kTakeAll, none);
+        if (dirs.empty()) break;
+      } else {
+        int held = 0;
+        for (int i : diag) {
+          (g[i].held && g[i].kind == P_RZ ? rz : g[i].held ? cz : fixed).push_back(i);
+          if (g[i].kind == P_RZ && g[i].held) ++held;
+        }
+        if (!cz.empty()) s.cost += states * 2 * N + 60;
+        s.cost += std::min(held * states * (bwd ? 3.0 : 2.0) * N,
+                           states * 4 * N + (bwd ? 3 * N : 0.0) + 60 + 3 * held);
+        fixed.insert(fixed.end(), cz.begin(), cz.end());
+        fixed.insert(fixed.end(), rz.begin(), rz.end());
+        emit_gates(fixed);
+        fresh = false;
+        continue;
+      }
+    }
+    const Basis to = exchanged(s.end, dirs, k, R);
+    if (to.same(s.end)) break;  // internal failure: best_sweep counts the gates
+    linear_exchange(s, to, k, R, false);
+    s.cost += states * (6 * N + 30);
+    fresh = true;
+  }
+  return s;
+}
+
+// The cheapest of the sweeps over a few thresholds; false when a gate never
+// ran.  No threshold wins everywhere (step of 12 qubits, 6 strongly entangling
+// layers: 493, 495 and 500 us with 1, 3 and none, 481 us with the choice; 14
+// qubits re-uploading: 9.81, 9.61, 9.51 and 9.55 ms).
+bool best_sweep(const std::vector<LinGate>& g, const Basis& start, int k, int R, bool bwd,
+                LinearSweep& best) {
+  best.cost = -1.0;
+  for (int flush_at : {1, 3, INT_MAX}) {
+    LinearSweep s = linear_sweep(g, start, k, R, bwd, flush_at);
+    size_t gates = 0;
+    for (const LinIns& n : s.ins) gates += n.op != OP_EXCHANGE;
+    if (gates != g.size()) return false;
+    if (best.cost < 0.0 || s.cost < best.cost) best = std::move(s);
+  }
+  return true;
+}
+
+// Appends a sweep's instructions (and its exchange tables) to a schedule.
+template <typename SlotFn>
+void append_sweep(const LinearSweep& s, std::vector<LinIns>& out, std::vector<uint32_t>& cols,
+                  SlotFn slot_of) {
+  const int base = (int)cols.size();
+  cols.insert(cols.end(), s.cols.begin(), s.cols.end());
+  for (LinIns n : s.ins) {
+    if (n.op == OP_EXCHANGE) n.arg += base;
+    else if (n.op != OP_CZ) n.slot = slot_of(n.arg);
+    out.push_back(n);
+  }
+}
+
+int append_basis_map(const Basis& B, std::vector<uint8_t>& maps) {
+  const int off = (int)maps.size();
+  for (int q = 0; q < B.n; ++q) {
+    uint8_t at = 0;
+    for (int p = 0; p < B.n; ++p)
+      if (B.b[p] == 1u << q) at = (uint8_t)p;
+    maps.push_back(at);
+  }
+  return off;
+}
+
+// Logical directions (one qubit each) for the register bits of a sweep's start:
+// those that let the first scan take the most gates; ties and the rest by first
+// use, `allowed` the qubits to choose from.
+std::vector<uint32_t> start_qubits(const std::vector<LinGate>& g, int nq, int R, uint32_t allowed) {
+  std::vector<int> pos(g.size()), first(nq, INT_MAX);
+  for (size_t i = 0; i < g.size(); ++i) {
+    pos[i] = (int)i;
+    for (int q = 0; q < nq; ++q)
+      if (((g[i].x >> q) & 1u) && first[q] == INT_MAX) first[q] = (int)i;
+  }
+  const ScanLimits none;
+  Span S;
+  std::vector<uint32_t> dirs;
+  uint32_t used = 0;
+  while ((int)dirs.size() < R) {
+    int best = -1, most = -1;
+    for (int q = 0; q < nq; ++q) {
+      if (!((allowed >> q) & 1u) || ((used >> q) & 1u)) continue;
+      Span s = S;
+      s.add(1u << q);
+      const int n = scan_gates(g, pos, s, kTakeAll, none, nullptr, nullptr);
+      if (n > most || (n == most && first[q] < first[best])) {
+        most = n;
+        best = q;
+      }
+    }
+    used |= 1u << best;
+    S.add(1u << best);
+    dirs.push_back(1u << best);
+  }
+  return dirs;
+}
+
+// A unit basis near B: units stay, other bits take the qubits left over.
+Basis unit_basis(const Basis& B, int k) {
+  Basis U = B;
+  uint32_t have = 0;
+  for (int p = 0; p < B.n; ++p)
+    if (!(B.b[p] & (B.b[p] - 1u))) have |= B.b[p];
+  uint32_t space = 0;
+  for (int p = 0; p < k; ++p) space |= B.b[p];
+  for (int p = 0; p < k; ++p)
+    if (B.b[p] & (B.b[p] - 1u)) {
+      const uint32_t left = space & ~have;
+      U.b[p] = left & (0u - left);
+      have |= U.b[p];
+    }
+  U.invert();
+  return U;
+}
+
+// Both sweeps of a resident circuit (the gates of `skip` left out: the product
+// head, whose adjoint ends in a unit basis).
+int plan_linear_resident(Plan& plan, const std::vector<char>* skip, LinSchedule& out,
+                         std::string& msg) {
+  const int nq = plan.nq, k = plan.k, R = plan.R;
+  std::vector<uint32_t> wfull;
+  const std::vector<LinGate> g = linear_gates(plan, skip, wfull);
+  Basis start;
+  start.n = nq;
+  const std::vector<uint32_t> regs = start_qubits(g, nq, R, (1u << nq) - 1u);
+  uint32_t used = 0;
+  for (int r = 0; r < R; ++r) used |= start.b[r] = regs[r];
+  int p = R;
+  for (int q = 0; q < nq; ++q)
+    if (!((used >> q) & 1u)) start.b[p++] = 1u << q;
+  start.invert();
+  LinearSweep f, b;
+  const std::vector<LinGate> rev(g.rbegin(), g.rend());
+  if (!best_sweep(g, start, k, R, false, f) || !best_sweep(rev, f.end, k, R, true, b)) {
+    msg = "internal: a gate was not scheduled";
+    return VQC_ERR_UNSUPPORTED;
+  }
+  if (skip && !b.end.unit()) linear_exchange(b, unit_basis(b.end, k), k, R, true);
+  auto slot_of = [&](int occ) { return plan.occ_slot[occ]; };
+  append_sweep(f, out.f, plan.cols, slot_of);
+  append_sweep(b, out.b, plan.cols, slot_of);
+  out.start_off = append_basis_map(start, plan.maps);
+  out.bwd_end_off = append_basis_map(b.end, plan.maps);
+  for (int q = 0; q < plan.n; ++q) out.zrow.push_back(f.end.row(wfull[q]));
+  for (int i = 0; i < k; ++i) {
+    uint32_t c = 0;
+    for (int q = 0; q < plan.n; ++q) c |= odd(wfull[q] & f.end.b[i]) << q;
+    out.lcol.push_back(c);
+  }
+  return 0;
+}
+
+// ---------------------------------------------------------------- streaming
+struct LinearPass {
+  std::vector<uint32_t> V;  // k vectors: the local space
+  std::vector<LinGate> g;
+};
+
+// Pass partition: the first pass's local space is spanned by k qubits (it
+// starts from |0...0>, a product state or a caller's state in logical order),
+// found by dropping one qubit at a time; every later pass grows its space
+// along the directions that let it run the most gates.  Rotations after a CNOT
+// ring need no qubit of the ring on chip but their own direction, so that a
+// pass runs two to three layers of a 16-qubit ring circuit on 12 dimensions
+// (5 passes per direction instead of the 10 that run the CNOTs as gates).
+bool partition_linear(const std::vector<LinGate>& all, int nq, int k, const ScanLimits& cap,
+                      std::vector<LinearPass>& passes) {
+  std::vector<int> pos(all.size());
+  for (size_t i = 0; i < all.size(); ++i) pos[i] = (int)i;
+  do {
+    LinearPass lp;
+    Span S;
+    if (passes.empty()) {
+      std::vector<int> first(nq, INT_MAX);
+      for (size_t i = 0; i < all.size(); ++i)
+        for (int q = 0; q < nq; ++q)
+          if (((all[i].x >> q) & 1u) && first[q] == INT_MAX) first[q] = (int)i;
+      uint32_t in = (1u << nq) - 1u;
+      auto span_of = [&](uint32_t m) {
+        Span s;
+        for (int q = 0; q < nq; ++q)
+          if ((m >> q) & 1u) s.add(1u << q);
+        return s;
+      };
+      for (int drop = 0; drop < nq - k; ++drop) {
+        int best = -1, most = -1;
+        for (int q = 0; q < nq; ++q) {
+          if (!((in >> q) & 1u)) continue;
+          const int n = scan_gates(all, pos, span_of(in & ~(1u << q)), kTakeAll, cap, nullptr,
+                                   nullptr);
+          if (n > most || (n == most && first[q] >= first[best])) {
+            most = n;
+            best = q;
+          }
+        }
+        in &= ~(1u << best);
+      }
+      S = span_of(in);
+      for (int q = 0; q < nq; ++q)
+        if ((in >> q) & 1u) lp.V.push_back(1u << q);
+    } else {
+      for (uint32_t d : choose_directions(all, pos, k, kTakeAll, cap))
+        if (S.add(d)) lp.V.push_back(d);
+      for (uint32_t v : passes.back().V)  // shared with the pass before: longer runs of addresses
+        if (S.dim < k && S.add(v)) lp.V.push_back(v);
+      for (int q = 0; q < nq && S.dim < k; ++q)
+        if (S.add(1u << q)) lp.V.push_back(1u << q);
+    }
+    std::vector<int> took, left;
+    scan_gates(all, pos, S, kTakeAll, cap, &took, nullptr);
+    if (took.empty() && !pos.empty() && !passes.empty()) return false;
+    size_t t = 0;
+    for (int i : pos) {
+      if (t < took.size() && took[t] == i) ++t;
+      else left.push_back(i);
+    }
+    for (int i : took) lp.g.push_back(all[i]);
+    pos.swap(left);
+    passes.push_back(std::move(lp));
+  } while (!pos.empty());
+  return true;
+}
+
+// The memory layout between a pass with local space V and one with local space
+// W: a basis over the address bits in which both are spanned by address bits.
+// Their intersection takes the low bits (consecutive lanes then touch
+// consecutive addresses on both sides), and where it can be the directions the
+// passes want on their register bits there (dV, dW) are basis vectors.
+Basis boundary_basis(const std::vector<uint32_t>& V, const std::vector<uint32_t>& W,
+                     const std::vector<uint32_t>& dV, const std::vector<uint32_t>& dW, int nq) {
+  Span sV;
+  for (uint32_t v : V) sV.add(v);
+  std::vector<uint32_t> inter;
+  {
+    std::vector<std::pair<uint32_t, uint32_t>> rows;  // (residue mod V, vector of W)
+    for (uint32_t w : W) {
+      uint32_t r = sV.residue(w), c = w;
+      for (const auto& e : rows)
+        if (r & (1u << (31 - __builtin_clz(e.first)))) {
+          r ^= e.first;
+          c ^= e.second;
+        }
+      if (!r) inter.push_back(c);
+      else {
+        rows.push_back({r, c});
+        std::sort(rows.begin(), rows.end(),
+                  [](const std::pair<uint32_t, uint32_t>& a,
+                     const std::pair<uint32_t, uint32_t>& b) { return a.first > b.first; });
+      }
+    }
+  }
+  Span sI;
+  for (uint32_t v : inter) sI.add(v);
+  // extensions of the intersection to V and to W, the wanted directions first
+  Span low;  // wanted directions (or what they leave) inside the intersection
+  std::vector<uint32_t> low_want;
+  auto extend = [&](const std::vector<uint32_t>& space, const std::vector<uint32_t>& want) {
+    Span t = sI;
+    std::vector<uint32_t> ext;
+    for (uint32_t d : want) {
+      if (t.add(d)) {
+        ext.push_back(d);
+        continue;
+      }
+      for (uint32_t s = 0; s < (1u << ext.size()); ++s) {
+        uint32_t c = d;
+        for (size_t j = 0; j < ext.size(); ++j)
+          if ((s >> j) & 1u) c ^= ext[j];
+        if (sI.holds(c)) {
+          if (low.add(c)) low_want.push_back(c);
+          break;
+        }
+      }
+    }
+    for (uint32_t v : space)
+      if (t.add(v)) ext.push_back(v);
+    return ext;
+  };
+  const std::vector<uint32_t> extV = extend(V, dV), extW = extend(W, dW);
+  Basis M;
+  M.n = nq;
+  int at = 0;
+  Span s = low;
+  for (uint32_t v : inter)
+    if (s.add(v)) M.b[at++] = v;
+  for (uint32_t v : low_want) M.b[at++] = v;
+  Span all;
+  for (int i = 0; i < at; ++i) all.add(M.b[i]);
+  auto put = [&](uint32_t v) {
+    if (at < nq && all.add(v)) M.b[at++] = v;
+  };
+  for (uint32_t v : extV) put(v);
+  for (uint32_t v : extW) put(v);
+  for (int q = 0; q < nq; ++q) put(1u << q);
+  M.invert();
+  return M;
+}
+
+// A pass's tile basis at a boundary: its register bits get the wanted
+// directions that are vectors of the layout M (then its highest address bits),
+// its thread bits the other local vectors by ascending address, and the tile
+// index the qubits that complete its space.
+bool tile_basis(const Basis& M, const std::vector<uint32_t>& V, const std::vector<uint32_t>& want,
+                int k, int R, Basis& B) {
+  Span s;
+  for (uint32_t v : V) s.add(v);
+  std::vector<uint32_t> local;
+  for (int a = 0; a < M.n; ++a)
+    if (s.holds(M.b[a])) local.push_back(M.b[a]);
+  if ((int)local.size() != k) return false;
+  std::vector<uint32_t> regs;
+  for (uint32_t d : want)
+    if ((int)regs.size() < R && std::find(regs.begin(), regs.end(), d) == regs.end() &&
+        std::find(local.begin(), local.end(), d) != local.end())
+      regs.push_back(d);
+  for (size_t i = local.size(); i-- > 0 && (int)regs.size() < R;)
+    if (std::find(regs.begin(), regs.end(), local[i]) == regs.end()) regs.push_back(local[i]);
+  B = Basis();
+  B.n = M.n;
+  int at = 0;
+  for (uint32_t v : regs) B.b[at++] = v;
+  for (uint32_t v : local)
+    if (std::find(regs.begin(), regs.end(), v) == regs.end()) B.b[at++] = v;
+  for (int q = 0; q < M.n; ++q)
+    if (s.add(1u << q)) B.b[at++] = 1u << q;
+  return at == M.n && B.invert();
+}
+
+// The k + ng address columns of a tile in basis B under layout M: thread bits,
+// register bits, then the tile index bits.  The local columns are single bits
+// (M is a basis of the local space); a tile index bit's may be any.
+void push_linear_io(const Basis& B, const Basis& M, int k, int R, std::vector<uint32_t>& cols) {
+  for (int p = R; p < k; ++p) cols.push_back(M.coord(B.b[p]));
+  for (int p = 0; p < R; ++p) cols.push_back(M.coord(B.b[p]));
+  for (int p = k; p < B.n; ++p) cols.push_back(M.coord(B.b[p]));
+}
+
+int plan_linear_stream(Plan& plan, std::string& msg) {
+  const int nq = plan.nq, k = plan.k;
+  std::vector<uint32_t> wfull;
+  const std::vector<LinGate> all = linear_gates(plan, nullptr, wfull);
+  const ScanLimits cap{plan.slot_cap, &plan.occ_slot};
+  std::vector<LinearPass> ps;
+  auto internal = [&](const char* what) {
+    msg = std::string("internal: ") + what;
+    return VQC_ERR_UNSUPPORTED;
+  };
+  if (!partition_linear(all, nq, k, cap, ps)) return internal("streaming pass made no progress");
+  const size_t nf = ps.size();
+  plan.cols.clear();
+  plan.maps.clear();
+  plan.pslots.clear();
+  plan.fpass.clear();
+  plan.bpass.clear();
+  plan.max_pass_slots = 0;
+  plan.lin = LinSchedule();
+  auto finish = [&](PassPlan& pp, const LinearSweep& s, std::vector<LinIns>& out, const Basis& in,
+                    const Basis& in_layout, const Basis& out_layout) {
+    std::map<int, int> local_slot;
+    std::vector<int32_t> slots;
+    auto slot_of = [&](int occ) -> int {
+      const int sl = plan.occ_slot[occ];
+      if (sl < 0) return -1;
+      auto it = local_slot.find(sl);
+      if (it != local_slot.end()) return it->second;
+      local_slot[sl] = (int)slots.size();
+      slots.push_back(sl);
+      return (int)slots.size() - 1;
+    };
+    const int R = &out == &plan.lin.f ? plan.Rf : plan.Rb;
+    pp.ins_off = (int)out.size();
+    append_sweep(s, out, plan.cols, slot_of);
+    pp.n_ins = (int)out.size() - pp.ins_off;
+    pp.start_off = append_basis_map(in, plan.maps);
+    pp.end_off = append_basis_map(s.end, plan.maps);
+    pp.io_off = pp.io_lin_off = (int)plan.cols.size();
+    push_linear_io(in, in_layout, k, R, plan.cols);
+    pp.io_out_off = (int)plan.cols.size();
+    push_linear_io(s.end, out_layout, k, R, plan.cols);
+    pp.io_lout_off = (int)plan.cols.size();
+    for (int i = 0; i < nq; ++i) {
+      const int p = i < k - R ? R + i : i < k ? i - (k - R) : i;
+      uint32_t c = 0;
+      for (int q = 0; q < plan.n; ++q) c |= odd(wfull[q] & s.end.b[p]) << q;
+      plan.cols.push_back(c);
+    }
+    pp.slots_off = (int)plan.pslots.size();
+    pp.n_slots = (int)slots.size();
+    plan.pslots.insert(plan.pslots.end(), slots.begin(), slots.end());
+    plan.max_pass_slots = std::max(plan.max_pass_slots, pp.n_slots);
+  };
+  const ScanLimits none;
+  auto first_directions = [&](const std::vector<LinGate>& g, int R) {
+    std::vector<int> pos(g.size());
+    for (size_t i = 0; i < g.size(); ++i) pos[i] = (int)i;
+    return choose_directions(g, pos, R, kTakeAll, none);
+  };
+  // layout[i]: what pass i reads; layout[i + 1]: what it writes
+  std::vector<Basis> layout(nf + 1), starts(nf), stores(nf);
+  layout[0].n = nq;
+  for (int q = 0; q < nq; ++q) layout[0].b[q] = 1u << q;
+  layout[0].invert();
+  uint32_t space0 = 0;
+  for (uint32_t v : ps[0].V) space0 |= v;
+  std::vector<uint32_t> want = start_qubits(ps[0].g, nq, plan.Rf, space0);
+  std::vector<std::vector<uint32_t>> want_in(nf), want_out(nf);
+  for (size_t i = 0; i < nf; ++i) {
+    want_in[i] = want;
+    if (!tile_basis(layout[i], ps[i].V, want, k, plan.Rf, starts[i]))
+      return internal("tile basis");
+    LinearSweep s;
+    if (!best_sweep(ps[i].g, starts[i], k, plan.Rf, false, s))
+      return internal("a gate was not scheduled");
+    const std::vector<uint32_t> last(s.end.b, s.end.b + plan.Rf);
+    want_out[i] = last;
+    if (i + 1 < nf) {
+      want = first_directions(ps[i + 1].g, plan.Rf);
+      layout[i + 1] = boundary_basis(ps[i].V, ps[i + 1].V, last, want, nq);
+      if (!tile_basis(layout[i + 1], ps[i].V, last, k, plan.Rf, stores[i]))
+        return internal("tile basis");
+      if (!stores[i].same(s.end)) linear_exchange(s, stores[i], k, plan.Rf, false);
+    } else {
+      // only its own mirror reads the last output: any basis of its space does
+      layout[nf].n = nq;
+      int at = 0;
+      for (int p = plan.Rf; p < k; ++p) layout[nf].b[at++] = s.end.b[p];
+      for (int p = 0; p < plan.Rf; ++p) layout[nf].b[at++] = s.end.b[p];
+      for (int p = k; p < nq; ++p) layout[nf].b[at++] = s.end.b[p];
+      layout[nf].invert();
+      stores[i] = s.end;
+      for (int q = 0; q < plan.n; ++q) plan.lin.zrow.push_back(s.end.row(wfull[q]));
+    }
+    PassPlan pp;
+    if (i == 0) pp.flags |= PF_INIT;
+    if (i + 1 == nf) pp.flags |= PF_ZPART;
+    finish(pp, s, plan.lin.f, starts[i], layout[i], layout[i + 1]);
+    plan.fpass.push_back(pp);
+  }
+  // the adjoint: each pass mirrored, from the layout its forward pass wrote to
+  // the one it read
+  for (size_t j = 0; j < nf; ++j) {
+    const size_t i = nf - 1 - j;
+    Basis in;
+    if (!tile_basis(layout[i + 1], ps[i].V, want_out[i], k, plan.Rb, in))
+      return internal("tile basis");
+    if (j == 0)
+      for (int q = 0; q < plan.n; ++q) plan.lin.zrow_b.push_back(in.row(wfull[q]));
+    const std::vector<LinGate> rev(ps[i].g.rbegin(), ps[i].g.rend());
+    LinearSweep s;
+    if (!best_sweep(rev, in, k, plan.Rb, true, s)) return internal("a gate was not scheduled");
+    if (i > 0 || plan.product_head) {
+      Basis to;
+      if (!tile_basis(layout[i], ps[i].V, want_in[i], k, plan.Rb, to))
+        return internal("tile basis");
+      if (!to.same(s.end) && (i > 0 || !s.end.unit()))
+        linear_exchange(s, to, k, plan.Rb, true);
+    }
+    PassPlan pp;
+    if (j == 0) pp.flags |= PF_MAKE_LAMBDA;
+    if (i == 0) pp.flags |= PF_LAST_ADJ;
+    finish(pp, s, plan.lin.b, in, layout[i + 1], i > 0 ? layout[i] : layout[0]);
+    plan.bpass.push_back(pp);
+  }
+  return 0;
+}

@@ -768,6 +768,8 @@ void lower_gate(const HostOp& o, Plan& plan) {
   }
 }
 
+#include "linear_plan.h"
+
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 }  // namespace
@@ -868,7 +870,7 @@ void stream_lds(Plan& plan) {
 }
 
 int build_plan(const std::vector<HostOp>& ops, int n, int P, int F, int path, int reg_bits,
-               Plan& plan, std::string& msg, bool lane_gates, int tile_qubits) {
+               Plan& plan, std::string& msg, bool lane_gates, int tile_qubits, bool linear) {
   if (n < 1 || n > kMaxQubits) {
     msg = "n_qubits must be in [1, " + std::to_string(kMaxQubits) + "]";
     return n < 1 ? VQC_ERR_INVALID_ARG : VQC_ERR_TOO_LARGE;
@@ -1051,7 +1053,42 @@ int build_plan(const std::vector<HostOp>& ops, int n, int P, int F, int path, in
           " bytes of LDS needed (limit " + std::to_string(kLdsBytes) + ")";
     return VQC_ERR_TOO_LARGE;
   }
-  return 0;
+  plan.gate_passes = plan.fpass.size() + plan.bpass.size();
+  return lane_gates && linear ? build_linear_plan(plan, msg) : 0;
+}
+
+// The generated kernels with one sample per workgroup run no CNOTs.  With 4
+// amplitudes per thread (8 qubits) they keep the schedule with gates on lane
+// bits, whose pairs need single lane bits.
+int build_linear_plan(Plan& plan, std::string& msg) {
+  plan.linear = plan.path == VQC_PATH_STREAM || (plan.S == 1 && plan.R >= 3);
+  if (!plan.linear) return 0;
+  if (plan.path == VQC_PATH_STREAM) {
+    // a pass may hold more slots than a pass of the schedule above, while its
+    // accumulators fit
+    const int groups = (1 << (plan.k - plan.Rb)) / 64;
+    const int fit = (int)(((size_t)kLdsBytes - plan.lds_fwd) / (4 * (size_t)groups)) - 4;
+    plan.slot_cap = std::max(plan.max_pass_slots, std::min(256, fit));
+    const int rc = plan_linear_stream(plan, msg);
+    if (rc < 0) return rc;
+    stream_lds(plan);
+    return 0;
+  }
+  std::vector<char> in_head(plan.occ_src.size(), 0);
+  for (const auto& hq : plan.head)
+    for (const Prim& g : hq) in_head[g.occ] = 1;
+  int rc = plan_linear_resident(plan, nullptr, plan.lin, msg);
+  if (rc < 0) return rc;
+  plan.start_off = plan.lin.start_off;  // where Psi_0's amplitudes go
+  return plan_linear_resident(plan, &in_head, plan.lin_step, msg);
+}
+
+// Streaming passes per direction of the linear schedule (0: internal failure).
+size_t linear_passes(const Plan& plan) {
+  std::vector<uint32_t> wfull;
+  std::vector<LinearPass> ps;
+  const ScanLimits cap{std::max(plan.max_pass_slots, 256), &plan.occ_slot};
+  return partition_linear(linear_gates(plan, nullptr, wfull), plan.nq, plan.k, cap, ps) ? ps.size() : 0;
 }
 
 // The streaming training step's plan: the passes of `full` planned again
@@ -1079,15 +1116,8 @@ int build_step_plan(const Plan& full, Plan& step, std::string& msg) {
     if (!(g.occ >= 0 && in_head[g.occ])) step.prims.push_back(g);
   step.fwd.clear();
   step.bwd.clear();
-  step.cols.clear();
-  step.maps.clear();
-  step.pslots.clear();
-  step.fpass.clear();
-  step.bpass.clear();
-  step.fwd_exchanges = step.bwd_exchanges = 0;
-  step.max_pass_slots = 0;
   step.product_head = true;
-  const int rc = plan_stream_both(step, msg);
+  const int rc = plan_linear_stream(step, msg);
   if (rc < 0) return rc;
   stream_lds(step);
   if (step.lds_bwd > (size_t)kLdsBytes) {

@@ -51,13 +51,16 @@ __device__ __forceinline__ void by_reg(int p, F&& f) {
 
 // ------------------------------------------------------------------ gates
 // R_P(t) = exp(-i t P / 2) with c = cos(t/2), s = sin(t/2); the adjoint uses -s.
+// Masks over the register index u: X pairs u with u ^ X; Z gives the sign,
+// z = +1 where parity(u & Z) is even.  One qubit on register bit p has X = Z =
+// 1 << p; the linear schedules use other masks (parity(X & Z) odd for RY).
 
-template <int R, int P>
+template <int R, int X>
 __device__ __forceinline__ void rx_reg(St<R>& a, float c, float s) {
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
-    if (u & (1 << P)) continue;
-    const int v = u | (1 << P);
+    const int v = u ^ X;
+    if (v < u) continue;
     const float xr = a.r[u], xi = a.i[u], yr = a.r[v], yi = a.i[v];
     // [c, -is; -is, c]
     a.r[u] = c * xr + s * yi;
@@ -67,12 +70,12 @@ __device__ __forceinline__ void rx_reg(St<R>& a, float c, float s) {
   }
 }
 
-template <int R, int P>
+template <int R, int X, int Z>
 __device__ __forceinline__ void ry_reg(St<R>& a, float c, float s) {
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
-    if (u & (1 << P)) continue;
-    const int v = u | (1 << P);
+    if (__builtin_parity(u & Z)) continue;
+    const int v = u ^ X;
     const float xr = a.r[u], xi = a.i[u], yr = a.r[v], yi = a.i[v];
     // [c, -s; s, c]
     a.r[u] = c * xr - s * yr;
@@ -82,12 +85,12 @@ __device__ __forceinline__ void ry_reg(St<R>& a, float c, float s) {
   }
 }
 
-// diag(c - is, c + is) on register bit P
-template <int R, int P>
+// diag(c - is, c + is): the sign of z per amplitude
+template <int R, int Z>
 __device__ __forceinline__ void rz_reg(St<R>& a, float c, float s) {
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
-    const float ss = (u & (1 << P)) ? s : -s;
+    const float ss = __builtin_parity(u & Z) ? s : -s;
     const float xr = a.r[u], xi = a.i[u];
     a.r[u] = c * xr - ss * xi;
     a.i[u] = c * xi + ss * xr;
@@ -204,12 +207,12 @@ __device__ __forceinline__ void negate_if(St<R>& a, uint32_t bit) {
 
 template <int R>
 __device__ __forceinline__ void apply_rx(St<R>& a, int p, float c, float s) {
-  by_reg<R>(p, [&](auto P) { rx_reg<R, decltype(P)::value>(a, c, s); });
+  by_reg<R>(p, [&](auto P) { rx_reg<R, 1 << decltype(P)::value>(a, c, s); });
 }
 
 template <int R>
 __device__ __forceinline__ void apply_ry(St<R>& a, int p, float c, float s) {
-  by_reg<R>(p, [&](auto P) { ry_reg<R, decltype(P)::value>(a, c, s); });
+  by_reg<R>(p, [&](auto P) { ry_reg<R, 1 << decltype(P)::value, 1 << decltype(P)::value>(a, c, s); });
 }
 
 // RZ on physical bit p: register bit, or a thread / tile bit (uniform phase)
@@ -219,7 +222,7 @@ __device__ __forceinline__ void apply_rz(St<R>& a, int p, float c, float s, uint
     phase_all<R>(a, c, ((tb >> (p - R)) & 1u) ? s : -s);
     return;
   }
-  by_reg<R>(p, [&](auto P) { rz_reg<R, decltype(P)::value>(a, c, s); });
+  by_reg<R>(p, [&](auto P) { rz_reg<R, 1 << decltype(P)::value>(a, c, s); });
 }
 
 template <int R>
@@ -243,13 +246,13 @@ __device__ __forceinline__ void apply_cnot(St<R>& a, int pc, int pt, uint32_t tb
 // pair keeps only the pair's old values alive.
 // Im(conj(l) a) = l.r a.i - l.i a.r ; Re(conj(l) a) = l.r a.r + l.i a.i
 
-template <int R, int P>
+template <int R, int X>
 __device__ __forceinline__ float adj_rx(St<R>& a, St<R>& l, float c, float s) {
   float acc = 0.f;
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
-    if (u & (1 << P)) continue;
-    const int v = u | (1 << P);
+    const int v = u ^ X;
+    if (v < u) continue;
     const float ar = a.r[u], ai = a.i[u], br = a.r[v], bi = a.i[v];
     const float lr = l.r[u], li = l.i[u], mr = l.r[v], mi = l.i[v];
     // X: <l|X|a> = conj(l0) a1 + conj(l1) a0
@@ -270,13 +273,13 @@ __device__ __forceinline__ float adj_rx(St<R>& a, St<R>& l, float c, float s) {
   return acc;
 }
 
-template <int R, int P>
+template <int R, int X, int Z>
 __device__ __forceinline__ float adj_ry(St<R>& a, St<R>& l, float c, float s) {
   float acc = 0.f;
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
-    if (u & (1 << P)) continue;
-    const int v = u | (1 << P);
+    if (__builtin_parity(u & Z)) continue;
+    const int v = u ^ X;
     const float ar = a.r[u], ai = a.i[u], br = a.r[v], bi = a.i[v];
     const float lr = l.r[u], li = l.i[u], mr = l.r[v], mi = l.i[v];
     // Y a = (-i a1, i a0): Im<l|Y|a> = -Re(conj(l0) a1) + Re(conj(l1) a0)
@@ -297,17 +300,17 @@ __device__ __forceinline__ float adj_ry(St<R>& a, St<R>& l, float c, float s) {
   return acc;
 }
 
-// RZ on register bit P: Im<l|Z|a> and diag(c + is, c - is) on both states
-template <int R, int P>
+// RZ: Im<l|Z|a> and diag(c + is, c - is) on both states
+template <int R, int Z>
 __device__ __forceinline__ float adj_rz(St<R>& a, St<R>& l, float c, float s) {
   float a0 = 0.f, a1 = 0.f;
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
     const float ar = a.r[u], ai = a.i[u], lr = l.r[u], li = l.i[u];
-    float& z = (u & (1 << P)) ? a1 : a0;
+    float& z = __builtin_parity(u & Z) ? a1 : a0;
     z = fmaf(lr, ai, z);
     z = fmaf(-li, ar, z);
-    const float ss = (u & (1 << P)) ? -s : s;  // the inverse phase
+    const float ss = __builtin_parity(u & Z) ? -s : s;  // the inverse phase
     a.r[u] = c * ar - ss * ai;
     a.i[u] = c * ai + ss * ar;
     l.r[u] = c * lr - ss * li;
@@ -342,13 +345,13 @@ __device__ __forceinline__ float adj_rz_uniform(St<R>& a, St<R>& l, float c, flo
 // by rescale) and carry the Paulis P^m as a frame that only flips signs of t,
 // of <Z_q> and of gradients (tables built per sample before the schedule).
 
-// (I - i t X) on the pair (u, u + 2^P)
-template <int R, int P>
+// (I - i t X) on the pairs (u, u ^ X)
+template <int R, int X>
 __device__ __forceinline__ void rx_t(St<R>& a, float t) {
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
-    if (u & (1 << P)) continue;
-    const int v = u | (1 << P);
+    const int v = u ^ X;
+    if (v < u) continue;
     const float xr = a.r[u], xi = a.i[u], yr = a.r[v], yi = a.i[v];
     a.r[u] = fmaf(t, yi, xr);
     a.i[u] = fmaf(-t, yr, xi);
@@ -358,12 +361,12 @@ __device__ __forceinline__ void rx_t(St<R>& a, float t) {
 }
 
 // (I - i t Y) = [1, -t; t, 1]
-template <int R, int P>
+template <int R, int X, int Z>
 __device__ __forceinline__ void ry_t(St<R>& a, float t) {
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
-    if (u & (1 << P)) continue;
-    const int v = u | (1 << P);
+    if (__builtin_parity(u & Z)) continue;
+    const int v = u ^ X;
     const float xr = a.r[u], xi = a.i[u], yr = a.r[v], yi = a.i[v];
     a.r[u] = fmaf(-t, yr, xr);
     a.i[u] = fmaf(-t, yi, xi);
@@ -372,23 +375,12 @@ __device__ __forceinline__ void ry_t(St<R>& a, float t) {
   }
 }
 
-// (I - i t Z) on register bit P: amplitude times (1 - i t z), z = +-1
-template <int R, int P>
+// (I - i t Z): amplitude times (1 - i t z), z = +-1
+template <int R, int Z>
 __device__ __forceinline__ void rz_t(St<R>& a, float t) {
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
-    const float tz = (u & (1 << P)) ? -t : t;
-    const float xr = a.r[u], xi = a.i[u];
-    a.r[u] = fmaf(tz, xi, xr);
-    a.i[u] = fmaf(-tz, xr, xi);
-  }
-}
-
-// every amplitude times (1 - i tz) (RZ on a thread / tile bit, tz = t z)
-template <int R>
-__device__ __forceinline__ void phase_t(St<R>& a, float tz) {
-#pragma unroll
-  for (int u = 0; u < St<R>::N; ++u) {
+    const float tz = __builtin_parity(u & Z) ? -t : t;
     const float xr = a.r[u], xi = a.i[u];
     a.r[u] = fmaf(tz, xi, xr);
     a.i[u] = fmaf(-tz, xr, xi);
@@ -405,13 +397,13 @@ __device__ __forceinline__ void rescale(St<R>& a, float f) {
 }
 
 // Adjoint steps: Im<l| P |a> at the gate's output, then (I + i t P) on both.
-template <int R, int P>
+template <int R, int X>
 __device__ __forceinline__ float adj_rx_t(St<R>& a, St<R>& l, float t) {
   float acc = 0.f;
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
-    if (u & (1 << P)) continue;
-    const int v = u | (1 << P);
+    const int v = u ^ X;
+    if (v < u) continue;
     const float ar = a.r[u], ai = a.i[u], br = a.r[v], bi = a.i[v];
     const float lr = l.r[u], li = l.i[u], mr = l.r[v], mi = l.i[v];
     acc = fmaf(lr, bi, acc);
@@ -430,13 +422,13 @@ __device__ __forceinline__ float adj_rx_t(St<R>& a, St<R>& l, float t) {
   return acc;
 }
 
-template <int R, int P>
+template <int R, int X, int Z>
 __device__ __forceinline__ float adj_ry_t(St<R>& a, St<R>& l, float t) {
   float acc = 0.f;
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
-    if (u & (1 << P)) continue;
-    const int v = u | (1 << P);
+    if (__builtin_parity(u & Z)) continue;
+    const int v = u ^ X;
     const float ar = a.r[u], ai = a.i[u], br = a.r[v], bi = a.i[v];
     const float lr = l.r[u], li = l.i[u], mr = l.r[v], mi = l.i[v];
     acc = fmaf(-lr, br, acc);
@@ -455,16 +447,16 @@ __device__ __forceinline__ float adj_ry_t(St<R>& a, St<R>& l, float t) {
   return acc;
 }
 
-template <int R, int P>
+template <int R, int Z>
 __device__ __forceinline__ float adj_rz_t(St<R>& a, St<R>& l, float t) {
   float a0 = 0.f, a1 = 0.f;
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
     const float ar = a.r[u], ai = a.i[u], lr = l.r[u], li = l.i[u];
-    float& z = (u & (1 << P)) ? a1 : a0;
+    float& z = __builtin_parity(u & Z) ? a1 : a0;
     z = fmaf(lr, ai, z);
     z = fmaf(-li, ar, z);
-    const float tz = (u & (1 << P)) ? t : -t;  // the inverse: (1 + i t z)
+    const float tz = __builtin_parity(u & Z) ? t : -t;  // the inverse: (1 + i t z)
     a.r[u] = fmaf(tz, ai, ar);
     a.i[u] = fmaf(-tz, ar, ai);
     l.r[u] = fmaf(tz, li, lr);
@@ -473,36 +465,18 @@ __device__ __forceinline__ float adj_rz_t(St<R>& a, St<R>& l, float t) {
   return a0 - a1;
 }
 
-// RZ on a thread / tile bit of value `one`: uniform z
-template <int R>
-__device__ __forceinline__ float adj_phase_t(St<R>& a, St<R>& l, float t, uint32_t one) {
-  float acc = 0.f;
-  const float tz = one ? t : -t;  // the inverse phase (1 + i t z)
-#pragma unroll
-  for (int u = 0; u < St<R>::N; ++u) {
-    const float ar = a.r[u], ai = a.i[u], lr = l.r[u], li = l.i[u];
-    acc = fmaf(lr, ai, acc);
-    acc = fmaf(-li, ar, acc);
-    a.r[u] = fmaf(tz, ai, ar);
-    a.i[u] = fmaf(-tz, ar, ai);
-    l.r[u] = fmaf(tz, li, lr);
-    l.i[u] = fmaf(-tz, lr, li);
-  }
-  return one ? -acc : acc;
-}
-
 template <int R>
 __device__ __forceinline__ float adjoint_rotation(int op, St<R>& a, St<R>& l, int p, float c,
                                                   float s, uint32_t tb) {
   float g = 0.f;
   if (op == OP_RX) {
-    by_reg<R>(p, [&](auto P) { g = adj_rx<R, decltype(P)::value>(a, l, c, s); });
+    by_reg<R>(p, [&](auto P) { g = adj_rx<R, 1 << decltype(P)::value>(a, l, c, s); });
   } else if (op == OP_RY) {
-    by_reg<R>(p, [&](auto P) { g = adj_ry<R, decltype(P)::value>(a, l, c, s); });
+    by_reg<R>(p, [&](auto P) { g = adj_ry<R, 1 << decltype(P)::value, 1 << decltype(P)::value>(a, l, c, s); });
   } else if (p >= R) {
     g = adj_rz_uniform<R>(a, l, c, s, (tb >> (p - R)) & 1u);
   } else {
-    by_reg<R>(p, [&](auto P) { g = adj_rz<R, decltype(P)::value>(a, l, c, s); });
+    by_reg<R>(p, [&](auto P) { g = adj_rz<R, 1 << decltype(P)::value>(a, l, c, s); });
   }
   return g;
 }
@@ -920,45 +894,24 @@ __device__ __forceinline__ void exchange_at(St<R>& a, float* xbuf, uint32_t plan
   __syncthreads();
 }
 
-// fo: byte offset XORed into every write address, which resolves a swap frame
-// (register index u holds position u ^ f: its slot is that of u, XOR the
-// columns of f's bits)
 template <int R>
 __device__ __forceinline__ void exchange(St<R>& a, float* xbuf, uint32_t plane,
-                                         const uint32_t* col, int k, int t, int stid, int sl,
-                                         uint32_t fo = 0u) {
+                                         const uint32_t* col, int k, int t, int stid, int sl) {
   uint32_t bw, br;
   exchange_bases<R>(col, k, t, stid, sl, bw, br);
-  exchange_at<R>(a, xbuf, plane, col, k, bw ^ fo, br);
+  exchange_at<R>(a, xbuf, plane, col, k, bw, br);
 }
 
 // The same permutation of two states (the adjoint's psi and lambda), one after
 // the other through the buffer, with the slot bases formed once.
 template <int R>
 __device__ __forceinline__ void exchange2(St<R>& a, St<R>& l, float* xbuf, uint32_t plane,
-                                          const uint32_t* col, int k, int t, int stid, int sl,
-                                          uint32_t fo = 0u) {
+                                          const uint32_t* col, int k, int t, int stid, int sl) {
   uint32_t bw, br;
   exchange_bases<R>(col, k, t, stid, sl, bw, br);
-  exchange_at<R>(a, xbuf, plane, col, k, bw ^ fo, br);
-  exchange_at<R>(l, xbuf, plane, col, k, bw ^ fo, br);
+  exchange_at<R>(a, xbuf, plane, col, k, bw, br);
+  exchange_at<R>(l, xbuf, plane, col, k, bw, br);
 }
-
-// ------------------------------------------------------------ swap frame
-// In the generated kernels (tangent form) a CNOT whose control sits on a
-// thread / tile bit c and whose target sits on register bit r does not move
-// data: the thread records that its registers along bit r are swapped iff c
-// is set (a frame F = X_r^c, kept as a sign mask fs_r = c << 31), and the
-// state held is F times the true one.  A later gate G then runs as F G F:
-// RY and RZ on bit r with the angle negated (X RY X = RY(-theta), likewise
-// RZ), RX and everything on other bits unchanged, a register CNOT from r to
-// r' adds the frame X_r' (F CNOT = CNOT F X_r'); the adjoint's gradient of a
-// negated rotation is negated (Im <lambda| X P X |psi> = -Im <lambda|P|psi>
-// for P = Y, Z).  The frame is resolved where the positions matter: folded
-// into the write addresses of an LDS exchange (register u goes to position
-// u ^ f; the addresses are XOR-linear in u), or, before anything else that
-// reads positions (lane swaps, CZs, epilogues, stores), by one conditional
-// swap per frame bit.
 
 // ------------------------------------------------------- schedule runner
 
@@ -1228,6 +1181,8 @@ struct InterpSched {
   // forward pass starts from the product state, the last adjoint pass writes
   // the head partials
   static constexpr bool kProductStart = false, kHeadPartials = false;
+  // whether the final basis states are given by a linear map (logical())
+  static constexpr bool kLinear = false;
   // physical bits of qubit q's measured Z-string under the mapping the epilogue /
   // lambda use (zm: the logical strings, or null for Z_q itself)
   __device__ __forceinline__ static uint32_t zmask(const uint8_t* phys, const uint32_t* zm,
@@ -1462,7 +1417,11 @@ template <int WG, int R, typename Sched>
 __device__ __forceinline__ void resident_probs(const St<R>& a, const TileArgs& A, const Walk& w) {
   const int N = 1 << A.n;
   const uint32_t xm = frame_xmask(Sched::esigns(w), A.n);
-  const LogicalIndex<R> li = logical_index<R>(A.end_phys, A.n, A.k, w.tb, A.pcol);
+  LogicalIndex<R> li;
+  if constexpr (Sched::kLinear)
+    li = Sched::template logical<R>(w.tb);
+  else
+    li = logical_index<R>(A.end_phys, A.n, A.k, w.tb, A.pcol);
   float* pb = w.xbuf;
   __syncthreads();  // the exchange buffer may still be read
   if (!li.pt) {
@@ -1924,28 +1883,51 @@ __device__ __forceinline__ void resident_step_body(const TileArgs& A, unsigned c
 // ordered by address bit) is r = stid + 2^(k-R) j, so consecutive lanes touch
 // consecutive addresses.  Addresses are the XOR of per-bit columns (io_*).
 
+// The columns of the thread and register bits are distinct single address
+// bits; a tile index bit's column may be any set of bits (a linear schedule's
+// layouts), so the tile's part (tile, uniform over the workgroup) is split: its
+// bits among the registers' go to their offsets, the rest to the base.
+__device__ __forceinline__ uint32_t tile_address(const uint32_t* io, int k, int ng, int g) {
+  uint32_t t = 0;
+  for (int i = 0; i < ng; ++i)
+    if ((g >> i) & 1) t ^= io[k + i];
+  return t;
+}
+
+template <int R>
+__device__ __forceinline__ void register_offsets(const uint32_t (&c)[R], uint32_t tile,
+                                                 uint32_t& mask, uint32_t (&off)[1 << R]) {
+  mask = 0;
+#pragma unroll
+  for (int b = 0; b < R; ++b) mask |= c[b];
+#pragma unroll
+  for (int j = 0; j < (1 << R); ++j) off[j] = xor_cols<R>(j, c) ^ (tile & mask);
+}
+
+__device__ __forceinline__ uint32_t lane_address(const uint32_t* io, int nt, int stid) {
+  uint32_t base = 0;
+#pragma unroll
+  for (int i = 0; i < kMaxTileQubits - 2; ++i)
+    if (i < nt && ((stid >> i) & 1)) base ^= io[i];
+  return base;
+}
+
 template <int R>
 __device__ __forceinline__ void io_offsets(const uint32_t* io, int k, int ng, int stid, int g,
                                            uint32_t& base, uint32_t (&off)[1 << R]) {
   const int nt = k - R;
-  base = 0;
-#pragma unroll
-  for (int i = 0; i < kMaxTileQubits - 2; ++i)
-    if (i < nt && ((stid >> i) & 1)) base ^= io[i];
-  for (int i = 0; i < ng; ++i)
-    if ((g >> i) & 1) base ^= io[k + i];
-  uint32_t c[R];
+  const uint32_t tile = tile_address(io, k, ng, g);
+  uint32_t c[R], mask;
 #pragma unroll
   for (int b = 0; b < R; ++b) c[b] = io[nt + b];
-#pragma unroll
-  for (int j = 0; j < (1 << R); ++j) off[j] = xor_cols<R>(j, c);
+  register_offsets<R>(c, tile, mask, off);
+  base = lane_address(io, nt, stid) ^ (tile & ~mask);
 }
 
 // A sample's state as a raw buffer (base: its first amplitude, `bytes` its
-// size; an access beyond it reads zero and stores nothing).  The load and
-// store columns are single address bits, distinct over the tile's ranks and
-// global bits, so a lane's bits (base) and a register's (off, uniform over the
-// workgroup) never overlap and their XOR is their sum: the lane's byte offset
+// size; an access beyond it reads zero and stores nothing).  A lane's bits
+// (base) and a register's (off, uniform over the workgroup) never overlap, so
+// their XOR is their sum: the lane's byte offset
 // is the access's vector offset and the register's its scalar offset, with no
 // address arithmetic per amplitude.
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
@@ -2083,6 +2065,7 @@ __device__ __forceinline__ void stream_body(const PassArgs& A, unsigned char* sm
   uint32_t oc[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) oc[r] = A.io_out[A.k - R + r];
+  const uint32_t otile = tile_address(A.io_out, A.k, A.ng, g);
   St<R> a, l;
   if (!BWD && (flags & PF_INIT)) {
     if constexpr (Sched::kProductStart) {
@@ -2112,9 +2095,9 @@ __device__ __forceinline__ void stream_body(const PassArgs& A, unsigned char* sm
   Sched::template run<R, BWD, true>(a, l, w, A.ins, A.n_ins);
 
   // the stores, in the layout this pass writes
-  io_offsets<R>(A.io_out, A.k, A.ng, tid, g, base, off);
-#pragma unroll
-  for (int j = 0; j < NA; ++j) off[j] = xor_cols<R>(j, oc);
+  uint32_t omask;
+  register_offsets<R>(oc, otile, omask, off);
+  base = lane_address(A.io_out, A.k - R, tid) ^ (otile & ~omask);
   const uint32_t base_b = opaque(base) << 3;
   // the adjoint stores lambda only (its psi is the state the forward saved at
   // this pass's start), and nothing at all in its last pass

@@ -41,6 +41,27 @@ struct Prim {
   int occ;     // angle occurrence index for rotations, -1 otherwise
 };
 
+// One instruction of the generated kernels' linear schedules (linear_plan.h):
+// masks over the physical bits (register bits, thread bits, tile index bits).
+struct LinIns {
+  int op = 0;          // OP_RX, OP_RY, OP_RZ, OP_CZ or OP_EXCHANGE
+  uint32_t x = 0;      // RX, RY: amplitude y pairs with y ^ x (register bits only)
+  uint32_t z = 0;      // RY, RZ: the sign's parity mask; CZ: its first Z-string
+  uint32_t z2 = 0;     // CZ: its second Z-string
+  int arg = -1;        // angle occurrence, or the exchange's columns
+  int slot = -1;       // gradient accumulator (-1: constant angle)
+  bool lam = false;    // exchange of lambda alone (nothing reads psi after it)
+};
+
+struct LinSchedule {
+  std::vector<LinIns> f, b;
+  // parity masks of the measured Z-strings in the forward's last basis, and in
+  // the adjoint's first when that differs (streaming)
+  std::vector<uint32_t> zrow, zrow_b;
+  std::vector<uint32_t> lcol;   // resident: logical image of each physical bit at the end
+  int start_off = 0, bwd_end_off = 0;  // resident: unit bases as mappings in `maps`
+};
+
 struct Plan {
   int n = 0, nq = 0, k = 0, t = 0, WG = 0, S = 0, G = 0;
   int R = kDefaultRegBits;                // register bits of the resident kernels
@@ -71,6 +92,14 @@ struct Plan {
   std::vector<uint32_t> fwd, bwd;         // instruction pairs
   std::vector<uint32_t> cols;             // exchange / tile I/O column tables
   std::vector<uint8_t> maps;              // logical -> phys tables (nq bytes each)
+  // Generated kernels with one sample per workgroup and at least 8 amplitudes
+  // per thread run these schedules (fwd / bwd then describe the same circuit
+  // with its CNOTs as instructions).  lin_step: the resident training step's,
+  // without the heads' rotations.
+  bool linear = false;
+  LinSchedule lin, lin_step;
+  size_t gate_passes = 0;                 // streaming passes with the CNOTs as gates (both ways)
+  int slot_cap = 0;                       // gradient slots a streaming pass may hold
   std::vector<int32_t> pslots;            // pass-local -> global gradient slots
   std::vector<PassPlan> fpass, bpass;     // streaming passes
   int start_off = 0, end_off = 0;         // resident: forward start / end mapping in `maps`
@@ -90,9 +119,14 @@ struct HostOp {
 constexpr int kNumGateKinds = 32;  // VQC_RX .. VQC_CSWAP
 // lane_gates: the schedule may put RX / RY / CNOT targets on lane bits (only
 // the generated kernels run such schedules).
-// tile_qubits: streaming tile size (0 = default).
+// tile_qubits: streaming tile size (0 = default).  linear: plan the generated
+// kernels' linear schedules too (build_linear_plan).
 int build_plan(const std::vector<HostOp>& ops, int n, int P, int F, int path, int reg_bits,
-               Plan& plan, std::string& msg, bool lane_gates, int tile_qubits = 0);
+               Plan& plan, std::string& msg, bool lane_gates, int tile_qubits = 0,
+               bool linear = true);
+// The generated kernels' linear schedules of a plan (linear_plan.h).
+int build_linear_plan(Plan& plan, std::string& msg);
+size_t linear_passes(const Plan& plan);
 // Gradient slots (P + F) up to which the streaming training step runs a plan
 // without the heads (its head kernel holds a row of them in LDS).
 constexpr int kMaxStepSlots = 8192;

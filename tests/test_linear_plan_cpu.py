@@ -1,0 +1,37 @@
+"""Host logic of the linear schedules (CNOTs as a change of basis): tests/
+linear_replay.cpp builds plans of random circuits (entangler-poor to dense, and
+the whole gate library), replays every instruction, LDS exchange and tile
+address in double precision and compares the measured <Z>, the probabilities
+and the adjoint's walk back with the circuit's gates applied one by one.  The
+replay also checks that exchanges are permutations without bank conflicts and
+that a tile's local address columns are distinct single bits."""
+import os
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2607_11985_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def replay(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("replay") / "linear_replay")
+    subprocess.check_call(["g++", "-std=c++17", "-O2", "-Wall", "-I", os.path.join(ROOT, "include"),
+                           "-I", CSRC, os.path.join(ROOT, "tests", "linear_replay.cpp"),
+                           os.path.join(CSRC, "planner.cpp"), "-o", exe])
+    return exe
+
+
+# (n, circuits, gates, tile_qubits, reg_bits): resident with 8 and 16 amplitudes
+# per thread, streaming with one to several global qubits and every tile size,
+# 32 amplitudes per thread, and circuits with no gate at all
+@pytest.mark.parametrize("n,count,gates,tile,rb", [
+    (9, 16, 60, 0, 0), (10, 8, 120, 0, 0), (11, 8, 3, 0, 0), (12, 8, 90, 0, 0), (12, 4, 60, 0, 3),
+    (13, 4, 80, 0, 0), (14, 8, 80, 12, 0), (14, 4, 80, 13, 0), (14, 4, 60, 14, 0),
+    (15, 4, 100, 12, 0), (15, 4, 100, 12, 5), (16, 4, 150, 12, 0), (17, 4, 60, 13, 0),
+    (18, 2, 60, 12, 0), (16, 4, 0, 12, 0)])
+def test_replay(replay, n, count, gates, tile, rb):
+    out = subprocess.run([replay, str(n), "0", str(count), str(gates), str(tile), str(rb)],
+                         capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout.endswith("ok\n"), out.stdout[-500:] + out.stderr
