@@ -171,6 +171,16 @@ __device__ __forceinline__ float flip_sign(float x, uint32_t m) {
   return __uint_as_float(__float_as_uint(x) ^ m);
 }
 
+// A parity, in bit 0 of p (the other bits are anything).
+struct Odd {
+  uint32_t p;
+};
+
+// x negated when the parity is odd: one shift-and-add on the sign bit
+__device__ __forceinline__ float flip_sign(float x, Odd o) {
+  return __uint_as_float(__float_as_uint(x) + (o.p << 31));
+}
+
 // CZ between register positions P and Q
 template <int R, int P, int Q>
 __device__ __forceinline__ void cz_rr(St<R>& a) {
@@ -944,6 +954,27 @@ struct Walk {
 // makes them keep values alive across it (and compile slowly).
 __device__ __forceinline__ void gate_boundary(const Walk& w) {
   if (w.never) asm volatile("");
+}
+
+// The double a lane holds.
+__device__ __forceinline__ double lane_double(double v, uint32_t lane) {
+  const int lo = __builtin_amdgcn_ds_bpermute((int)(lane << 2), __double2loint(v));
+  const int hi = __builtin_amdgcn_ds_bpermute((int)(lane << 2), __double2hiint(v));
+  return __hiloint2double(hi, lo);
+}
+
+// Products over a wave: returns that of f over the lanes before this one, all
+// that over the 64 lanes.  Every lane takes part.
+__device__ __forceinline__ double block_scan(double f, uint32_t lane, double& all) {
+  double p = f;
+#pragma unroll
+  for (uint32_t d = 1; d < 64; d <<= 1) {
+    const double q = lane_double(p, (lane - d) & 63u);
+    p *= lane >= d ? q : 1.0;
+  }
+  all = lane_double(p, 63u);
+  const double q = lane_double(p, (lane - 1u) & 63u);
+  return lane ? q : 1.0;
 }
 
 // Angle table of a one-sample workgroup held in registers: lane j of the
@@ -1966,7 +1997,7 @@ __device__ __forceinline__ void load_tile(St<R>& a, __amdgpu_buffer_rsrc_t src, 
 // The per-sample tables of the streaming passes (generated kernels, tangent
 // form): one workgroup per sample computes the angle table and the frame
 // signs of every occurrence (Sched::prepare over all of them) once, and
-// writes (t, cos phi'), the adjoint's gradient signs and the <Z> signs for
+// writes (t, gradient factor), the blocks' factors and the <Z> signs for
 // every pass of the call to read (so that no pass repeats the sincos, the
 // divisions and the parity sums).
 template <int WG, typename Sched>
@@ -1982,14 +2013,8 @@ __device__ __forceinline__ void table_body(const PassArgs& A, unsigned char* sme
                      A.fd_slots, A.fd_h, A.fd_base);
   __syncthreads();
   Sched::prepare(w, tid, WG, pre);  // ends with a barrier
-  const float* gm = reinterpret_cast<const float*>(smem + Sched::kOffGm);
   const float* es = Sched::esigns(w);
-  float2* T = reinterpret_cast<float2*>(A.tabs) + b * A.n_occ;
-  float* Gs = A.gsig + b * A.n_occ;
-  for (int i = tid; i < A.n_occ; i += WG) {
-    T[i] = w.tab[i];
-    Gs[i] = gm[i];
-  }
+  Sched::store(w, A, b, tid, WG, pre);
   for (int q = tid; q < A.n; q += WG) A.esig[b * A.n + q] = es[q];
   if (A.gpart) {
     // the training step's gradient partials of this sample, cleared for its adjoint
