@@ -127,9 +127,15 @@ size_t stream_end(const Plan& p, int64_t batch, int mode) {
 // stream and one on a side stream, so that one half's passes fill the CUs the
 // other's leave idle (the tail of each pass; in the training step also the
 // HBM-bound forward of one half beside the VALU-bound adjoint of the other).
-// Each half has a layout of its own: [half 0 | half 1].
+// Each half has a layout of its own: [half 0 | half 1].  Below 2048 tiles a
+// call stays on one stream: its passes are short and the second half's launches
+// and the fork and join cost more than they fill (measured: 17-qubit QAOA
+// ansatz, 8 samples, 256 tiles of 13 qubits, autograd pass 206-228 us split,
+// 126 us not; 20-qubit ring, 3 samples, 768 tiles, step 192 and 187 us; 16-qubit
+// ring, 256 samples, 4096 tiles, step 979 and 1034 us).
+constexpr int64_t kSplitTiles = 2048;
 bool split_batch(const Plan& p, int64_t batch) {
-  return p.path == VQC_PATH_STREAM && batch >= 2;
+  return p.path == VQC_PATH_STREAM && batch >= 2 && (batch << p.ng) >= kSplitTiles;
 }
 int64_t first_half(int64_t batch) { return (batch + 1) / 2; }
 size_t second_half_offset(const Plan& p, int64_t batch, int mode) {
