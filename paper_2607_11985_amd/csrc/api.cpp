@@ -407,6 +407,7 @@ int stream_forward(const vqc_circuit* c, int64_t batch, const float* params, con
     set_tables(a, ws, L);
     a.psi_src = ws + (keep ? L.ck(i ? i - 1 : 0) : L.ck((i + 1) % 2));
     a.psi_dst = ws + (keep ? L.ck(i) : L.ck(i % 2));
+    if (!keep && i + 1 == p.fpass.size()) a.psi_dst = nullptr;  // nothing reads the last state
     if (psi0 && (a.flags & vqc::PF_INIT)) {
       if (p.product_head) return fail(VQC_ERR_UNSUPPORTED, "internal: Psi_0 with a product head");
       a.flags &= ~vqc::PF_INIT;

@@ -829,17 +829,20 @@ int plan_linear_stream(Plan& plan, std::string& msg) {
   plan.bpass.clear();
   plan.max_pass_slots = 0;
   plan.lin = LinSchedule();
+  std::set<int32_t> seen_f, seen_b;  // slots of the passes before
   auto finish = [&](PassPlan& pp, const LinearSweep& s, std::vector<LinIns>& out, const Basis& in,
                     const Basis& in_layout, const Basis& out_layout) {
     std::map<int, int> local_slot;
     std::vector<int32_t> slots;
+    std::set<int32_t>& before = &out == &plan.lin.f ? seen_f : seen_b;
     auto slot_of = [&](int occ) -> int {
       const int sl = plan.occ_slot[occ];
       if (sl < 0) return -1;
       auto it = local_slot.find(sl);
       if (it != local_slot.end()) return it->second;
       local_slot[sl] = (int)slots.size();
-      slots.push_back(sl);
+      // complemented: no earlier pass adds to the slot
+      slots.push_back(before.insert(sl).second ? ~sl : sl);
       return (int)slots.size() - 1;
     };
     const int R = &out == &plan.lin.f ? plan.Rf : plan.Rb;

@@ -1214,6 +1214,10 @@ struct InterpSched {
   static constexpr bool kProductStart = false, kHeadPartials = false;
   // whether the final basis states are given by a linear map (logical())
   static constexpr bool kLinear = false;
+  // generated passes: the tile's address columns compiled in, whether the pass
+  // may start from |0...0> or the product state, and whether every gradient
+  // accumulator is written before it is read
+  static constexpr bool kFixedIo = false, kMayInit = true, kAccWritten = false;
   // physical bits of qubit q's measured Z-string under the mapping the epilogue /
   // lambda use (zm: the logical strings, or null for Z_q itself)
   __device__ __forceinline__ static uint32_t zmask(const uint8_t* phys, const uint32_t* zm,
@@ -1918,10 +1922,12 @@ __device__ __forceinline__ void resident_step_body(const TileArgs& A, unsigned c
 // bits; a tile index bit's column may be any set of bits (a linear schedule's
 // layouts), so the tile's part (tile, uniform over the workgroup) is split: its
 // bits among the registers' go to their offsets, the rest to the base.
-__device__ __forceinline__ uint32_t tile_address(const uint32_t* io, int k, int ng, int g) {
+template <typename Col>
+__device__ __forceinline__ uint32_t tile_address(Col&& col, int k, int ng, int g) {
   uint32_t t = 0;
+#pragma unroll
   for (int i = 0; i < ng; ++i)
-    if ((g >> i) & 1) t ^= io[k + i];
+    if ((g >> i) & 1) t ^= col(k + i);
   return t;
 }
 
@@ -1935,24 +1941,25 @@ __device__ __forceinline__ void register_offsets(const uint32_t (&c)[R], uint32_
   for (int j = 0; j < (1 << R); ++j) off[j] = xor_cols<R>(j, c) ^ (tile & mask);
 }
 
-__device__ __forceinline__ uint32_t lane_address(const uint32_t* io, int nt, int stid) {
+template <typename Col>
+__device__ __forceinline__ uint32_t lane_address(Col&& col, int nt, int stid) {
   uint32_t base = 0;
 #pragma unroll
   for (int i = 0; i < kMaxTileQubits - 2; ++i)
-    if (i < nt && ((stid >> i) & 1)) base ^= io[i];
+    if (i < nt && ((stid >> i) & 1)) base ^= col(i);
   return base;
 }
 
-template <int R>
-__device__ __forceinline__ void io_offsets(const uint32_t* io, int k, int ng, int stid, int g,
+template <int R, typename Col>
+__device__ __forceinline__ void io_offsets(Col&& col, int k, int ng, int stid, int g,
                                            uint32_t& base, uint32_t (&off)[1 << R]) {
   const int nt = k - R;
-  const uint32_t tile = tile_address(io, k, ng, g);
+  const uint32_t tile = tile_address(col, k, ng, g);
   uint32_t c[R], mask;
 #pragma unroll
-  for (int b = 0; b < R; ++b) c[b] = io[nt + b];
+  for (int b = 0; b < R; ++b) c[b] = col(nt + b);
   register_offsets<R>(c, tile, mask, off);
-  base = lane_address(io, nt, stid) ^ (tile & ~mask);
+  base = lane_address(col, nt, stid) ^ (tile & ~mask);
 }
 
 // A sample's state as a raw buffer (base: its first amplitude, `bytes` its
@@ -1982,17 +1989,21 @@ __device__ __forceinline__ void amp_store(__amdgpu_buffer_rsrc_t r, uint32_t bas
   __builtin_amdgcn_raw_buffer_store_b64(v, r, base_b, so, 0);
 }
 
-// All loads are issued before the first split, so that they overlap.
+// A tile's loads, issued together, and taken (split) later.
 template <int R>
-__device__ __forceinline__ void load_tile(St<R>& a, __amdgpu_buffer_rsrc_t src, uint32_t base,
-                                          const uint32_t (&off)[1 << R]) {
-  const uint32_t base_b = base << 3;
+struct TileLoad {
   float2 v[1 << R];
+  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t src, uint32_t base,
+                                        const uint32_t (&off)[1 << R]) {
+    const uint32_t base_b = base << 3;
 #pragma unroll
-  for (int j = 0; j < (1 << R); ++j) v[j] = amp_load(src, base_b, off[j]);
+    for (int j = 0; j < (1 << R); ++j) v[j] = amp_load(src, base_b, off[j]);
+  }
+  __device__ __forceinline__ void take(St<R>& a) const {
 #pragma unroll
-  for (int j = 0; j < (1 << R); ++j) split(v[j], a.r[j], a.i[j]);
-}
+    for (int j = 0; j < (1 << R); ++j) split(v[j], a.r[j], a.i[j]);
+  }
+};
 
 // The per-sample tables of the streaming passes (generated kernels, tangent
 // form): one workgroup per sample computes the angle table and the frame
@@ -2021,6 +2032,13 @@ __device__ __forceinline__ void table_body(const PassArgs& A, unsigned char* sme
     float* gp = A.gpart + (b << A.ng) * A.n_slots;
     for (int i = tid; i < (A.n_slots << A.ng); i += WG) gp[i] = 0.f;
   }
+}
+
+// The tile index bits of a pass.
+template <typename Sched>
+__device__ __forceinline__ int pass_ng(const PassArgs& A) {
+  if constexpr (Sched::kFixedIo) return Sched::kNG;
+  else return A.ng;
 }
 
 template <bool BWD, int R, int K, typename Sched>
@@ -2056,10 +2074,46 @@ __device__ __forceinline__ void stream_body(const PassArgs& A, unsigned char* sm
   w.smem = smem;
   w.tb = (uint32_t)tid | ((uint32_t)g << w.t);
 
+  // A generated pass knows its flags (all but PF_INIT, which a caller's Psi_0
+  // clears): a runtime branch between forming lambda and loading it would have
+  // the compiler copy the whole gate sequence into both arms.
+  const uint32_t flags = Sched::kFixedFlags >= 0
+                             ? (A.flags & PF_INIT) | (uint32_t)Sched::kFixedFlags
+                             : A.flags;
+  const bool init = !BWD && Sched::kMayInit && (flags & PF_INIT);
+  // Psi_0 is read in logical order; the passes' own states in their layouts (a
+  // generated first pass reads in logical order anyway)
+  const bool logical_in = !BWD && !(flags & PF_INIT) && A.psi0_in;
+  const int ng = pass_ng<Sched>(A);
+  const auto in = [&](int i) {
+    if constexpr (Sched::kFixedIo) return Sched::in_col(i);
+    else return (logical_in ? A.io_lin : A.io)[i];
+  };
+  const auto out = [&](int i) {
+    if constexpr (Sched::kFixedIo) return Sched::out_col(i);
+    else return A.io_out[i];
+  };
+  uint32_t base, off[NA];
+  io_offsets<R>(in, K, ng, tid, g, base, off);
+  const size_t sbase = (size_t)b << (K + ng);
+  const uint32_t sbytes = 8u << (K + ng);
+  // the register columns of the layout this pass writes, read before the gate
+  // sequence (its barriers would make a later read a per-lane one)
+  uint32_t oc[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) oc[r] = out(K - R + r);
+  const uint32_t otile = tile_address(out, K, ng, g);
+  // the tile's loads go out before the tables', so that their latencies overlap
+  TileLoad<R> la, ll;
+  if (!init)
+    la.issue(state_rsrc(reinterpret_cast<const float2*>(A.psi_src) + sbase, sbytes), base, off);
+  if (BWD && !(flags & PF_MAKE_LAMBDA))
+    ll.issue(state_rsrc(reinterpret_cast<const float2*>(A.lam_src) + sbase, sbytes), base, off);
+
   if constexpr (Sched::kLoadTables) {
     // the sample's tables, written once per call by the table kernel
     Sched::load_tables(w, A, b, tid, WG);
-    if (BWD)
+    if (BWD && !Sched::kAccWritten)
       for (int i = tid; i < A.n_pslots * G; i += WG) acc[i] = 0.f;
     __syncthreads();
   } else {
@@ -2073,26 +2127,8 @@ __device__ __forceinline__ void stream_body(const PassArgs& A, unsigned char* sm
     Sched::prepare(w, tid, WG, pre);
   }
 
-  // A generated pass knows its flags (all but PF_INIT, which a caller's Psi_0
-  // clears): a runtime branch between forming lambda and loading it would have
-  // the compiler copy the whole gate sequence into both arms.
-  const uint32_t flags = Sched::kFixedFlags >= 0
-                             ? (A.flags & PF_INIT) | (uint32_t)Sched::kFixedFlags
-                             : A.flags;
-  uint32_t base, off[NA];
-  // Psi_0 is read in logical order; the passes' own states in their layouts
-  const bool logical_in = !BWD && !(flags & PF_INIT) && A.psi0_in;
-  io_offsets<R>(logical_in ? A.io_lin : A.io, A.k, A.ng, tid, g, base, off);
-  const size_t sbase = (size_t)b << (A.k + A.ng);
-  const uint32_t sbytes = 8u << (A.k + A.ng);
-  // the register columns of the layout this pass writes, read before the gate
-  // sequence (its barriers would make a later read a per-lane one)
-  uint32_t oc[R];
-#pragma unroll
-  for (int r = 0; r < R; ++r) oc[r] = A.io_out[A.k - R + r];
-  const uint32_t otile = tile_address(A.io_out, A.k, A.ng, g);
   St<R> a, l;
-  if (!BWD && (flags & PF_INIT)) {
+  if (init) {
     if constexpr (Sched::kProductStart) {
       Sched::template product_start<R>(a, w);  // the state after the heads
     } else {
@@ -2104,17 +2140,14 @@ __device__ __forceinline__ void stream_body(const PassArgs& A, unsigned char* sm
       if (tid == 0 && g == 0) a.r[0] = 1.f;
     }
   } else {
-    load_tile<R>(a, state_rsrc(reinterpret_cast<const float2*>(A.psi_src) + sbase, sbytes), base,
-                 off);
+    la.take(a);
   }
   if (BWD) {
-    if (flags & PF_MAKE_LAMBDA) {
+    if (flags & PF_MAKE_LAMBDA)
       make_lambda<R, Sched>(l, a, A.grad_out + b * A.n, A.n, A.start_phys, A.zmask, w.tb, true,
                             Sched::esigns(w));
-    } else {
-      load_tile<R>(l, state_rsrc(reinterpret_cast<const float2*>(A.lam_src) + sbase, sbytes),
-                   base, off);
-    }
+    else
+      ll.take(l);
   }
 
   Sched::template run<R, BWD, true>(a, l, w, A.ins, A.n_ins);
@@ -2122,11 +2155,12 @@ __device__ __forceinline__ void stream_body(const PassArgs& A, unsigned char* sm
   // the stores, in the layout this pass writes
   uint32_t omask;
   register_offsets<R>(oc, otile, omask, off);
-  base = lane_address(A.io_out, A.k - R, tid) ^ (otile & ~omask);
+  base = lane_address(out, K - R, tid) ^ (otile & ~omask);
   const uint32_t base_b = opaque(base) << 3;
   // the adjoint stores lambda only (its psi is the state the forward saved at
-  // this pass's start), and nothing at all in its last pass
-  if (!BWD) {
+  // this pass's start), and nothing at all in its last pass; an inference
+  // forward stores nothing in its last
+  if (!BWD && A.psi_dst) {
     const auto dst = state_rsrc(reinterpret_cast<float2*>(A.psi_dst) + sbase, sbytes);
 #pragma unroll
     for (int j = 0; j < NA; ++j) amp_store(dst, base_b, off[j], a.r[j], a.i[j]);
@@ -2143,10 +2177,15 @@ __device__ __forceinline__ void stream_body(const PassArgs& A, unsigned char* sm
     }
     __syncthreads();
     float* gp = A.gpart + blk * A.n_slots;
+    // a slot no earlier pass added to (complemented) is stored without reading
+    // its cleared partial
     for (int i = tid; i < A.n_pslots; i += WG) {
+      const int slot = A.pslots[i];
       float v = 0.f;
+#pragma unroll
       for (int r = 0; r < G; ++r) v += acc[i * G + r];
-      gp[A.pslots[i]] += v;
+      if (slot < 0) gp[~slot] = v;
+      else gp[slot] += v;
     }
   } else if (flags & PF_ZPART) {
     if (A.probs) {
@@ -2154,7 +2193,8 @@ __device__ __forceinline__ void stream_body(const PassArgs& A, unsigned char* sm
       // state's addresses, so the stores stay coalesced
       const uint32_t xm = frame_xmask(Sched::esigns(w), A.n);
       float* pd = A.probs + sbase;
-      io_offsets<R>(A.io_lout, A.k, A.ng, tid, g, base, off);
+      const auto lout = [&](int i) { return A.io_lout[i]; };
+      io_offsets<R>(lout, K, ng, tid, g, base, off);
 #pragma unroll
       for (int j = 0; j < NA; ++j) pd[(base ^ off[j]) ^ xm] = a.r[j] * a.r[j] + a.i[j] * a.i[j];
     }

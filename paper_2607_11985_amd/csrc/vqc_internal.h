@@ -31,7 +31,7 @@ struct PassPlan {
   int io_lin_off = 0;           // loads in logical order (Psi_0)
   int io_lout_off = 0;          // stores in logical order (probabilities)
   int start_off = 0, end_off = 0;  // nq bytes each: logical qubit -> physical bit
-  int slots_off = 0, n_slots = 0;  // pass-local gradient slot -> global slot
+  int slots_off = 0, n_slots = 0;  // pass-local gradient slot -> global slot (pslots)
   int flags = 0;
 };
 

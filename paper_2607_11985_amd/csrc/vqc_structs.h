@@ -124,7 +124,8 @@ struct PassArgs {
   const uint8_t* start_phys;   // logical -> phys at pass start
   const uint8_t* end_phys;     // logical -> phys at pass end
   const uint32_t* zmask;       // measured Z-strings (as in TileArgs), or null
-  const int32_t* pslots;       // pass-local -> global gradient slot
+  const int32_t* pslots;       // pass-local -> global gradient slot, complemented when
+                               // no earlier pass adds to it
   int32_t n_pslots;
   int32_t flags;
   int32_t psi0_in;             // 1: this (first forward) pass reads Psi_0, logical order
