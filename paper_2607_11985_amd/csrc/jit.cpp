@@ -1215,12 +1215,16 @@ struct LinUnit {
   int block;                 // the block it belongs to (rotations)
   bool ends;                 // the block's last unit
 };
+struct BlockEntry {
+  int occ;
+  int unit;  // the index in the block of the first rotation of its unit
+  bool neg;  // its Pauli has a minus sign
+};
 struct LinStream {
   std::vector<LinUnit> units;
   std::vector<int> rots;     // rotations in the order they run
-  // per block its rotations, and for each the index in the block of the first
-  // rotation of its unit
-  std::vector<std::vector<std::pair<int, int>>> blocks;
+  // per block its rotations
+  std::vector<std::vector<BlockEntry>> blocks;
 };
 
 LinStream linear_stream(const Plan& p, const LinIns* ins, int n_ins, bool bwd, int R, bool tan) {
@@ -1249,7 +1253,7 @@ LinStream linear_stream(const Plan& p, const LinIns* ins, int n_ins, bool bwd, i
     std::vector<int> occ;
     if (!u.gate)
       for (const RzItem& it : u.run) occ.push_back(it.occ);
-    else if (u.gate->op == OP_RX || u.gate->op == OP_RY || u.gate->op == OP_RZ)
+    else if (u.gate->op != OP_EXCHANGE)
       occ.push_back(u.gate->arg);
     if (occ.empty()) continue;
     if (s.blocks.empty() || (int)(s.blocks.back().size() + occ.size()) > kBlock) {
@@ -1259,7 +1263,7 @@ LinStream linear_stream(const Plan& p, const LinIns* ins, int n_ins, bool bwd, i
     u.block = (int)s.blocks.size() - 1;
     const int at = (int)s.blocks.back().size();
     for (int o : occ) {
-      s.blocks.back().push_back({o, at});
+      s.blocks.back().push_back({o, at, u.gate && u.gate->neg});
       s.rots.push_back(o);
     }
     last = &u;
@@ -1318,20 +1322,10 @@ void emit_linear(std::ostringstream& o, const Plan& p, const LinStream& s, bool 
       else emit_exchange_code(E, (uint32_t)n.arg, k, {"a"});
       continue;
     }
-    if (n.op == OP_CZ) {
-      std::vector<CzItem> run;
-      size_t end = i;
-      for (; end < s.units.size() && s.units[end].gate && s.units[end].gate->op == OP_CZ; ++end)
-        run.push_back({s.units[end].gate->z, s.units[end].gate->z2});
-      emit_cz_run(E, run);
-      i = end - 1;
-      continue;
-    }
     const std::string kind = n.op == OP_RX ? "rx" : n.op == OP_RY ? "ry" : "rz";
-    const std::string masks = n.op == OP_RX ? std::to_string(n.x)
-                              : n.op == OP_RY ? std::to_string(n.x) + ", " + std::to_string(n.z & regs)
-                                              : std::to_string(n.z & regs);
-    const uint32_t thr = n.op == OP_RX ? 0u : n.z >> R;
+    const std::string masks = (n.op == OP_RZ ? "" : std::to_string(n.x) + ", ") +
+                              std::to_string(n.z & regs);
+    const uint32_t thr = n.z >> R;
     emit_slot_ready(E, n.slot);
     o << "  { ";
     if (tan) {
@@ -1341,7 +1335,8 @@ void emit_linear(std::ostringstream& o, const Plan& p, const LinStream& s, bool 
     } else {
       o << "const float2 cs = w.tab[" << n.arg << "]; ";
     }
-    const std::string from = tan ? "tc.x" : "cs.y";
+    // (a minus sign is in the tables' entries)
+    const std::string from = tan ? "tc.x" : n.neg ? "-cs.y" : "cs.y";
     if (thr) o << "const auto fs = " << E.sign(thr) << "; const float t = flip_sign(" << from
                << ", fs); ";
     else o << "const float t = " << from << "; ";
@@ -1352,7 +1347,7 @@ void emit_linear(std::ostringstream& o, const Plan& p, const LinStream& s, bool 
       o << "float g = adj_" << kind << (tan ? "_t<R, " : "<R, ") << masks << ">(a, l, " << tail;
       if (thr) o << " g = flip_sign(g, fs);";
       if (tan) o << " g *= tc.y;";
-      else o << occ_scale(p, (uint32_t)n.arg);
+      else o << (n.neg ? " g = -g;" : "") << occ_scale(p, (uint32_t)n.arg);
       emit_collect(E, n.slot);
     }
     if (!fac.empty()) emit_block_end(E);
@@ -1378,8 +1373,8 @@ void emit_linear(std::ostringstream& o, const Plan& p, const LinStream& s, bool 
 // stream: the table kernel, which writes the entries in the passes' order
 // (place) and the factors for the passes to read; head: rotations left exact.
 void emit_linear_tables(std::ostringstream& o, const Plan& p, const TanMode& t, const Frame& fr,
-                        const std::vector<std::vector<std::pair<int, int>>>& fwd,
-                        const std::vector<std::vector<std::pair<int, int>>>& adj, int nt,
+                        const std::vector<std::vector<BlockEntry>>& fwd,
+                        const std::vector<std::vector<BlockEntry>>& adj, int nt,
                         const std::vector<char>* head, const std::vector<int>* place) {
   const int nocc = (int)p.occ_src.size(), W = t.W, nw = nt / 64;
   std::vector<uint32_t> words, rows, erows;
@@ -1388,8 +1383,10 @@ void emit_linear_tables(std::ostringstream& o, const Plan& p, const TanMode& t, 
     for (const auto& blk : *list)
       for (int l = 0; l < 64; ++l) {
         const bool live = l < (int)blk.size();
-        const int k = live ? blk[l].first : blk[0].first;
-        words.push_back((uint32_t)k | (live ? (uint32_t)blk[l].second << 16 | 1u << 31 : 0u));
+        const BlockEntry& e = blk[live ? l : 0];
+        const int k = e.occ;
+        words.push_back((uint32_t)k |
+                        (live ? (uint32_t)e.unit << 16 | (uint32_t)e.neg << 30 | 1u << 31 : 0u));
         for (int j = 0; j < W; ++j)
           rows.push_back(j < fr.words ? fr.arow[(size_t)k * fr.words + j] : 0u);
         muls.push_back(p.affine && p.occ_src[k] != kSrcConst ? p.occ_ma[2 * k] : 1.f);
@@ -1498,7 +1495,7 @@ void emit_linear_tables(std::ostringstream& o, const Plan& p, const TanMode& t, 
       << "    const bool live = word >> 31;\n"
       // the sign: another wave may have set it already, which t * t does not see
       << "    const float t = tab[k].x;\n"
-      << "    uint32_t par = 0u;\n"
+      << "    uint32_t par = (word >> 30) & 1u;\n"
       << "#pragma unroll\n"
       << "    for (int j = 0; j < " << W << "; ++j) par ^= __builtin_popcount(bits[j] & "
       << (pre ? "pre.r[r * " + W_ + " + j]" : "kArow[(blk * 64 + lane) * " + W_ + " + j]") << ");\n"
@@ -1563,7 +1560,7 @@ struct StreamTables {
   std::vector<LinStream> f, b;              // per forward pass (b: its mirror)
   std::vector<int> fac_f, fac_b;            // each pass's first factor
   // the forward blocks of the longer passes, then every adjoint block
-  std::vector<std::vector<std::pair<int, int>>> fblocks, bblocks;
+  std::vector<std::vector<BlockEntry>> fblocks, bblocks;
 };
 
 StreamTables stream_tables(const Plan& p) {
@@ -1760,7 +1757,7 @@ std::string own_tables(const Plan& p, const Frame& fr, const TanMode& tm, const 
   std::ostringstream o;
   o << "static constexpr bool kLoadTables = false;\n";
   if (tm.on && (f || b)) {
-    const std::vector<std::vector<std::pair<int, int>>> none;
+    const std::vector<std::vector<BlockEntry>> none;
     emit_linear_tables(o, p, tm, fr, f ? f->blocks : none, b ? b->blocks : none, nt, head, nullptr);
     emit_esigns(o, tm);
   } else {

@@ -3,13 +3,17 @@
 //
 // Entanglers as a change of basis.  A CNOT permutes basis states linearly over
 // GF(2), so it need not run: the state is kept as if no CNOT had been applied,
-// and every later gate is the Pauli rotation (or pair of Z-strings, for a CZ)
-// that the CNOTs before it turn it into.  In these fixed coordinates y in
-// GF(2)^n qubit q's X acts as y -> y ^ v_q and its Z reads parity(w_q & y);
-// CNOT(c, t) maps v_c ^= v_t, w_t ^= w_c.  A rotation is then a pair (x, z):
-// RX pairs y with y ^ x, RY does so with the sign of parity(z & y), RZ and CZ
-// are diagonal in parities, and two gates commute when their symplectic product
-// is even, which lets more gates pass a waiting one than disjoint qubits do.
+// and every later gate is the Pauli rotation that the CNOTs before it turn it
+// into.  In these fixed coordinates y in GF(2)^n qubit q's X acts as y -> y ^ v_q
+// and its Z reads parity(w_q & y); CNOT(c, t) maps v_c ^= v_t, w_t ^= w_c.  A CZ
+// does not run either: it is the sign of a product of two parities, every output
+// is diagonal, so it only matters to the later RX and RY, whose Pauli T_x Z_z (T_x
+// |y> = |y ^ x>) it takes to T_x Z_z', z' = z ^ (w_b x) w_a ^ (w_a x) w_b, times
+// the sign of (w_a x)(w_b x).  A rotation is then a pair (x, z) and a sign: RX and
+// RY pair y with y ^ x under the sign of parity(z & y), RZ is diagonal, and two
+// gates commute when their symplectic product is even, which lets more gates
+// pass a waiting one than disjoint qubits do.  Constant rotations by pi are
+// Paulis, which the tangent form's frame carries anyway: they do not run.
 //
 // A layout of the register tile is any basis of GF(2)^n: physical bit p moves
 // along vector b[p].  A gate runs where its x lies in the span of the register
@@ -91,33 +95,57 @@ struct Waiting {
 };
 static_assert(2 * kMaxQubits < 64, "a basis of the waiting Paulis leaves room for another row");
 
-// A gate in the fixed coordinates: kind P_RX, P_RY, P_RZ (x = 0) or P_CZ (z, z2).
+// A rotation in the fixed coordinates: kind P_RX (parity(x & z) even), P_RY (odd)
+// or P_RZ (x = 0).
 struct LinGate {
   int kind;
-  uint32_t x, z, z2;
+  uint32_t x, z;
   int occ;
-  bool held;  // a diagonal gate taken in runs: a CZ, or an RZ whose angle varies
+  bool neg;   // its Pauli has a minus sign
+  bool held;  // a diagonal gate taken in runs: an RZ whose angle varies
 };
+
+// Whether a constant rotation is a Pauli or the identity (up to a phase) to
+// the last bit of its (cos, sin) pair.
+bool constant_pauli(const Plan& plan, int occ) {
+  return plan.occ_src[occ] == VQC_SRC_CONST &&
+         std::min(std::fabs(plan.occ_cs[2 * occ]), std::fabs(plan.occ_cs[2 * occ + 1])) < 1e-15f;
+}
+
+// Whether the generated kernels' tables are sure to fit in LDS after `base`
+// bytes (they then use the tangent form and its frame).
+bool tables_fit(const Plan& plan, size_t base) {
+  const size_t nocc = plan.occ_src.size();
+  return base + nocc / 8 + 2 * nocc * 4 + (size_t)plan.n * 4 + 128 <= (size_t)kLdsBytes;
+}
 
 // The circuit's gates (those of `skip` left out), and the rows of every
 // measured qubit's Z after the whole circuit, the folded trailing entanglers
-// included.
+// included.  tangent: constant Paulis are left to the frame.
 std::vector<LinGate> linear_gates(const Plan& plan, const std::vector<char>* skip,
-                                  std::vector<uint32_t>& wfull) {
+                                  std::vector<uint32_t>& wfull, bool tangent) {
   uint32_t v[kMaxQubits], w[kMaxQubits];
   for (int q = 0; q < kMaxQubits; ++q) v[q] = w[q] = 1u << q;
   std::vector<LinGate> g;
+  std::vector<std::pair<uint32_t, uint32_t>> cz;
   for (const Prim& p : plan.prims) {
     switch (p.kind) {
       case P_CNOT:
         v[p.q0] ^= v[p.q1];
         w[p.q1] ^= w[p.q0];
         break;
-      case P_CZ: g.push_back({P_CZ, 0u, w[p.q0], w[p.q1], -1, true}); break;
-      default:
-        if (skip && (*skip)[p.occ]) break;
-        g.push_back({p.kind, p.kind == P_RZ ? 0u : v[p.q0], p.kind == P_RX ? 0u : w[p.q0], 0u,
-                     p.occ, p.kind == P_RZ && plan.occ_src[p.occ] != VQC_SRC_CONST});
+      case P_CZ: cz.push_back({w[p.q0], w[p.q1]}); break;
+      default: {
+        if ((skip && (*skip)[p.occ]) || (tangent && constant_pauli(plan, p.occ))) break;
+        LinGate e{p.kind, p.kind == P_RZ ? 0u : v[p.q0], p.kind == P_RX ? 0u : w[p.q0], p.occ, false,
+                  p.kind == P_RZ && plan.occ_src[p.occ] != VQC_SRC_CONST};
+        for (const auto& c : cz) {
+          const uint32_t a = odd(c.first & e.x), b = odd(c.second & e.x);
+          e.z ^= (b ? c.first : 0u) ^ (a ? c.second : 0u);
+          e.neg ^= (a & b) != 0u;
+        }
+        g.push_back(e);
+      }
     }
   }
   for (const Prim& p : plan.tail)
@@ -155,7 +183,7 @@ int scan_gates(const std::vector<LinGate>& g, const std::vector<int>& pos, const
   for (size_t j = 0; j < end && stopped < kGiveUp; ++j) {
     const int i = pos[j];
     const LinGate& e = g[i];
-    bool stop = wait.blocks(e.x, e.z) || (e.kind == P_CZ && wait.blocks(0u, e.z2));
+    bool stop = wait.blocks(e.x, e.z);
     if (!stop) stop = mode == kTakeEager ? e.held : mode == kTakeDiagonal ? e.x != 0u : false;
     if (!stop && cap.occ_slot && e.occ >= 0) {
       const int s = (*cap.occ_slot)[e.occ];
@@ -180,7 +208,6 @@ int scan_gates(const std::vector<LinGate>& g, const std::vector<int>& pos, const
     }
     ++stopped;
     wait.add(e.x, e.z);
-    if (e.kind == P_CZ) wait.add(0u, e.z2);
   }
   return count;
 }
@@ -409,8 +436,7 @@ void linear_exchange(LinearSweep& s, const Basis& to, int k, int R, bool lam) {
   s.end = to;
 }
 
-// One register-level sweep over `g` from basis `start`.  Variable RZs and CZs
-// wait until at least `flush_at` other gates on the present register bits wait
+// One register-level sweep over `g` from basis `start`.  Variable RZs wait until at least `flush_at` other gates on the present register bits wait
 // for them (or nothing else can run): a run of diagonals costs about as much as
 // one of them, an exchange more.  The cost is an instruction count per wave:
 // per exchange and state the LDS accesses and addresses of 2^R amplitudes, per
@@ -429,10 +455,10 @@ LinearSweep linear_sweep(const std::vector<LinGate>& g, const Basis& start, int 
     for (int i : took) {
       const LinGate& e = g[i];
       LinIns n;
-      n.op = e.kind == P_RX ? OP_RX : e.kind == P_RY ? OP_RY : e.kind == P_RZ ? OP_RZ : OP_CZ;
+      n.op = e.kind == P_RX ? OP_RX : e.kind == P_RY ? OP_RY : OP_RZ;
       n.x = s.end.coord(e.x);
       n.z = s.end.row(e.z);
-      n.z2 = s.end.row(e.z2);
+      n.neg = e.neg;
       n.arg = e.occ;
       s.ins.push_back(n);
     }
@@ -466,7 +492,7 @@ LinearSweep linear_sweep(const std::vector<LinGate>& g, const Basis& start, int 
       for (uint32_t d : dirs) flush = flush && S.holds(d);
     }
     if (flush) {
-      std::vector<int> diag, fixed, cz, rz;  // (all commute)
+      std::vector<int> diag, fixed, rz;  // (all commute)
       scan_gates(g, pos, S, kTakeDiagonal, none, &diag, nullptr);
       if (diag.empty()) {  // only gates off the register bits are left to run
         dirs = choose_directions(g, pos, R, kTakeAll, none);
@@ -474,13 +500,11 @@ LinearSweep linear_sweep(const std::vector<LinGate>& g, const Basis& start, int 
       } else {
         int held = 0;
         for (int i : diag) {
-          (g[i].held && g[i].kind == P_RZ ? rz : g[i].held ? cz : fixed).push_back(i);
-          if (g[i].kind == P_RZ && g[i].held) ++held;
+          (g[i].held ? rz : fixed).push_back(i);
+          if (g[i].held) ++held;
         }
-        if (!cz.empty()) s.cost += states * 2 * N + 60;
         s.cost += std::min(held * states * (bwd ? 3.0 : 2.0) * N,
                            states * 4 * N + (bwd ? 3 * N : 0.0) + 60 + 3 * held);
-        fixed.insert(fixed.end(), cz.begin(), cz.end());
         fixed.insert(fixed.end(), rz.begin(), rz.end());
         emit_gates(fixed);
         fresh = false;
@@ -521,7 +545,7 @@ void append_sweep(const LinearSweep& s, std::vector<LinIns>& out, std::vector<ui
   cols.insert(cols.end(), s.cols.begin(), s.cols.end());
   for (LinIns n : s.ins) {
     if (n.op == OP_EXCHANGE) n.arg += base;
-    else if (n.op != OP_CZ) n.slot = slot_of(n.arg);
+    else n.slot = slot_of(n.arg);
     out.push_back(n);
   }
 }
@@ -594,7 +618,8 @@ int plan_linear_resident(Plan& plan, const std::vector<char>* skip, LinSchedule&
                          std::string& msg) {
   const int nq = plan.nq, k = plan.k, R = plan.R;
   std::vector<uint32_t> wfull;
-  const std::vector<LinGate> g = linear_gates(plan, skip, wfull);
+  const std::vector<LinGate> g =
+      linear_gates(plan, skip, wfull, tables_fit(plan, std::max(plan.lds_step, plan.lds_bwd)));
   Basis start;
   start.n = nq;
   const std::vector<uint32_t> regs = start_qubits(g, nq, R, (1u << nq) - 1u);
@@ -813,7 +838,12 @@ void push_linear_io(const Basis& B, const Basis& M, int k, int R, std::vector<ui
 int plan_linear_stream(Plan& plan, std::string& msg) {
   const int nq = plan.nq, k = plan.k;
   std::vector<uint32_t> wfull;
-  const std::vector<LinGate> all = linear_gates(plan, nullptr, wfull);
+  // (the table kernel holds all entries, a pass at most the slots' accumulators)
+  const size_t acc = (size_t)plan.slot_cap * ((1u << (plan.k - plan.Rb)) / 64u) * 4;
+  const std::vector<LinGate> all =
+      linear_gates(plan, nullptr, wfull,
+                   tables_fit(plan, plan.occ_src.size() * 8) &&
+                       tables_fit(plan, plan.lds_fwd + acc + 16));
   const ScanLimits cap{plan.slot_cap, &plan.occ_slot};
   std::vector<LinearPass> ps;
   auto internal = [&](const char* what) {

@@ -1088,7 +1088,7 @@ size_t linear_passes(const Plan& plan) {
   std::vector<uint32_t> wfull;
   std::vector<LinearPass> ps;
   const ScanLimits cap{std::max(plan.max_pass_slots, 256), &plan.occ_slot};
-  return partition_linear(linear_gates(plan, nullptr, wfull), plan.nq, plan.k, cap, ps) ? ps.size() : 0;
+  return partition_linear(linear_gates(plan, nullptr, wfull, true), plan.nq, plan.k, cap, ps) ? ps.size() : 0;
 }
 
 // The streaming training step's plan: the passes of `full` planned again

@@ -53,20 +53,22 @@ __device__ __forceinline__ void by_reg(int p, F&& f) {
 // R_P(t) = exp(-i t P / 2) with c = cos(t/2), s = sin(t/2); the adjoint uses -s.
 // Masks over the register index u: X pairs u with u ^ X; Z gives the sign,
 // z = +1 where parity(u & Z) is even.  One qubit on register bit p has X = Z =
-// 1 << p; the linear schedules use other masks (parity(X & Z) odd for RY).
+// 1 << p (Z = 0 for RX); the linear schedules use other masks, parity(X & Z) odd
+// for RY and even for RX.
 
-template <int R, int X>
+template <int R, int X, int Z = 0>
 __device__ __forceinline__ void rx_reg(St<R>& a, float c, float s) {
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
     const int v = u ^ X;
     if (v < u) continue;
+    const float sz = __builtin_parity(u & Z) ? -s : s;
     const float xr = a.r[u], xi = a.i[u], yr = a.r[v], yi = a.i[v];
     // [c, -is; -is, c]
-    a.r[u] = c * xr + s * yi;
-    a.i[u] = c * xi - s * yr;
-    a.r[v] = c * yr + s * xi;
-    a.i[v] = c * yi - s * xr;
+    a.r[u] = c * xr + sz * yi;
+    a.i[u] = c * xi - sz * yr;
+    a.r[v] = c * yr + sz * xi;
+    a.i[v] = c * yi - sz * xr;
   }
 }
 
@@ -256,29 +258,30 @@ __device__ __forceinline__ void apply_cnot(St<R>& a, int pc, int pt, uint32_t tb
 // pair keeps only the pair's old values alive.
 // Im(conj(l) a) = l.r a.i - l.i a.r ; Re(conj(l) a) = l.r a.r + l.i a.i
 
-template <int R, int X>
+template <int R, int X, int Z = 0>
 __device__ __forceinline__ float adj_rx(St<R>& a, St<R>& l, float c, float s) {
   float acc = 0.f;
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
     const int v = u ^ X;
     if (v < u) continue;
+    const float sz = __builtin_parity(u & Z) ? -s : s;
     const float ar = a.r[u], ai = a.i[u], br = a.r[v], bi = a.i[v];
     const float lr = l.r[u], li = l.i[u], mr = l.r[v], mi = l.i[v];
     // X: <l|X|a> = conj(l0) a1 + conj(l1) a0
-    acc = fmaf(lr, bi, acc);
-    acc = fmaf(-li, br, acc);
-    acc = fmaf(mr, ai, acc);
-    acc = fmaf(-mi, ar, acc);
+    acc = fmaf(__builtin_parity(u & Z) ? -lr : lr, bi, acc);
+    acc = fmaf(__builtin_parity(u & Z) ? li : -li, br, acc);
+    acc = fmaf(__builtin_parity(u & Z) ? -mr : mr, ai, acc);
+    acc = fmaf(__builtin_parity(u & Z) ? mi : -mi, ar, acc);
     // RX(-theta) = [c, is; is, c]
-    a.r[u] = c * ar - s * bi;
-    a.i[u] = c * ai + s * br;
-    a.r[v] = c * br - s * ai;
-    a.i[v] = c * bi + s * ar;
-    l.r[u] = c * lr - s * mi;
-    l.i[u] = c * li + s * mr;
-    l.r[v] = c * mr - s * li;
-    l.i[v] = c * mi + s * lr;
+    a.r[u] = c * ar - sz * bi;
+    a.i[u] = c * ai + sz * br;
+    a.r[v] = c * br - sz * ai;
+    a.i[v] = c * bi + sz * ar;
+    l.r[u] = c * lr - sz * mi;
+    l.i[u] = c * li + sz * mr;
+    l.r[v] = c * mr - sz * li;
+    l.i[v] = c * mi + sz * lr;
   }
   return acc;
 }
@@ -356,17 +359,18 @@ __device__ __forceinline__ float adj_rz_uniform(St<R>& a, St<R>& l, float c, flo
 // of <Z_q> and of gradients (tables built per sample before the schedule).
 
 // (I - i t X) on the pairs (u, u ^ X)
-template <int R, int X>
+template <int R, int X, int Z = 0>
 __device__ __forceinline__ void rx_t(St<R>& a, float t) {
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
     const int v = u ^ X;
     if (v < u) continue;
+    const float tz = __builtin_parity(u & Z) ? -t : t;
     const float xr = a.r[u], xi = a.i[u], yr = a.r[v], yi = a.i[v];
-    a.r[u] = fmaf(t, yi, xr);
-    a.i[u] = fmaf(-t, yr, xi);
-    a.r[v] = fmaf(t, xi, yr);
-    a.i[v] = fmaf(-t, xr, yi);
+    a.r[u] = fmaf(tz, yi, xr);
+    a.i[u] = fmaf(-tz, yr, xi);
+    a.r[v] = fmaf(tz, xi, yr);
+    a.i[v] = fmaf(-tz, xr, yi);
   }
 }
 
@@ -407,27 +411,28 @@ __device__ __forceinline__ void rescale(St<R>& a, float f) {
 }
 
 // Adjoint steps: Im<l| P |a> at the gate's output, then (I + i t P) on both.
-template <int R, int X>
+template <int R, int X, int Z = 0>
 __device__ __forceinline__ float adj_rx_t(St<R>& a, St<R>& l, float t) {
   float acc = 0.f;
 #pragma unroll
   for (int u = 0; u < St<R>::N; ++u) {
     const int v = u ^ X;
     if (v < u) continue;
+    const float tz = __builtin_parity(u & Z) ? -t : t;
     const float ar = a.r[u], ai = a.i[u], br = a.r[v], bi = a.i[v];
     const float lr = l.r[u], li = l.i[u], mr = l.r[v], mi = l.i[v];
-    acc = fmaf(lr, bi, acc);
-    acc = fmaf(-li, br, acc);
-    acc = fmaf(mr, ai, acc);
-    acc = fmaf(-mi, ar, acc);
-    a.r[u] = fmaf(-t, bi, ar);
-    a.i[u] = fmaf(t, br, ai);
-    a.r[v] = fmaf(-t, ai, br);
-    a.i[v] = fmaf(t, ar, bi);
-    l.r[u] = fmaf(-t, mi, lr);
-    l.i[u] = fmaf(t, mr, li);
-    l.r[v] = fmaf(-t, li, mr);
-    l.i[v] = fmaf(t, lr, mi);
+    acc = fmaf(__builtin_parity(u & Z) ? -lr : lr, bi, acc);
+    acc = fmaf(__builtin_parity(u & Z) ? li : -li, br, acc);
+    acc = fmaf(__builtin_parity(u & Z) ? -mr : mr, ai, acc);
+    acc = fmaf(__builtin_parity(u & Z) ? mi : -mi, ar, acc);
+    a.r[u] = fmaf(-tz, bi, ar);
+    a.i[u] = fmaf(tz, br, ai);
+    a.r[v] = fmaf(-tz, ai, br);
+    a.i[v] = fmaf(tz, ar, bi);
+    l.r[u] = fmaf(-tz, mi, lr);
+    l.i[u] = fmaf(tz, mr, li);
+    l.r[v] = fmaf(-tz, li, mr);
+    l.i[v] = fmaf(tz, lr, mi);
   }
   return acc;
 }

@@ -44,10 +44,10 @@ struct Prim {
 // One instruction of the generated kernels' linear schedules (linear_plan.h):
 // masks over the physical bits (register bits, thread bits, tile index bits).
 struct LinIns {
-  int op = 0;          // OP_RX, OP_RY, OP_RZ, OP_CZ or OP_EXCHANGE
+  int op = 0;          // OP_RX, OP_RY, OP_RZ or OP_EXCHANGE
   uint32_t x = 0;      // RX, RY: amplitude y pairs with y ^ x (register bits only)
-  uint32_t z = 0;      // RY, RZ: the sign's parity mask; CZ: its first Z-string
-  uint32_t z2 = 0;     // CZ: its second Z-string
+  uint32_t z = 0;      // the sign's parity mask
+  bool neg = false;    // the rotation's Pauli has a minus sign
   int arg = -1;        // angle occurrence, or the exchange's columns
   int slot = -1;       // gradient accumulator (-1: constant angle)
   bool lam = false;    // exchange of lambda alone (nothing reads psi after it)

@@ -29,8 +29,9 @@ uint32_t odd(uint32_t v) { return (uint32_t)__builtin_parity(v); }
 
 // exp(-i th/2 P) on the pairs (y, y ^ x) with the sign of parity(z & y)
 void rotate(State& s, int op, uint32_t x, uint32_t z, double th) {
-  const double c = std::cos(th / 2), sn = std::sin(th / 2);
+  const double c = std::cos(th / 2), s0 = std::sin(th / 2);
   for (uint32_t y = 0; y < s.size(); ++y) {
+    const double sn = op == OP_RX && odd(z & y) ? -s0 : s0;
     if (op == OP_RZ) {
       s[y] *= C(c, odd(z & y) ? sn : -sn);
       continue;
@@ -97,12 +98,9 @@ bool run(State& a, State* l, const Plan& p, const std::vector<LinIns>& ins, int 
     }
     for (State* s : {&a, l}) {
       if (!s) continue;
-      if (e.op == OP_CZ) sign_flip(*s, e.z, e.z2);
-      else {
-        if (e.op != OP_RZ && (e.x == 0 || e.x >> R)) return false;
-        if (e.op == OP_RY && !odd(e.z & e.x)) return false;
-        rotate(*s, e.op, e.x, e.z, bwd ? -th[e.arg] : th[e.arg]);
-      }
+      if (e.op != OP_RZ && (e.x == 0 || e.x >> R)) return false;
+      if (e.op != OP_RZ && odd(e.z & e.x) != (e.op == OP_RY)) return false;
+      rotate(*s, e.op, e.x, e.z, bwd != e.neg ? -th[e.arg] : th[e.arg]);
     }
   }
   return true;
@@ -187,6 +185,12 @@ int check(int n, int seed, int gates, int tile, int rb) {
   if (!full.linear) return fail("no linear schedule", n, seed);
   std::vector<double> th(full.occ_src.size());
   for (double& t : th) t = std::uniform_real_distribution<double>(-3, 3)(rng);
+  // constant Paulis do not run (the tables' frame carries them): as identities
+  // they are absent from both sides here
+  for (size_t k = 0; k < th.size(); ++k)
+    if (full.occ_src[k] == VQC_SRC_CONST &&
+        std::min(std::fabs(full.occ_cs[2 * k]), std::fabs(full.occ_cs[2 * k + 1])) < 1e-15f)
+      th[k] = 0;
   for (int step = 0; step < 2; ++step) {
     Plan p = full;
     if (step && path == VQC_PATH_STREAM) {
