@@ -20,7 +20,14 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# the current stream's handle without a Stream object around it: 0.1 us instead of
+# 1.9 us of the 13 us that a small circuit's call takes on the host
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device):
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
     return torch.cuda.current_stream(device).cuda_stream
 
 
@@ -80,6 +87,19 @@ class Circuit:
         if self.P == 0:
             return None
         return _as_rows(params.reshape(1, -1), 1, self.P, self.device, "params").reshape(-1)
+
+    # Gradient outputs: float32 rows like the checked, contiguous inputs
+    # (empty_like takes 1.2 us, empty with its arguments 1.7 us).
+    def _param_grads(self, params, B):
+        if type(params) is torch.Tensor:
+            return torch.empty_like(params)
+        return torch.empty((self.P,) if self.shared else (B, self.P), dtype=torch.float32,
+                           device=self.device)
+
+    def _input_grads(self, inputs, B):
+        if type(inputs) is torch.Tensor:
+            return torch.empty_like(inputs)
+        return torch.empty((B, self.F), dtype=torch.float32, device=self.device)
 
     def _batch(self, params, inputs):
         if inputs is not None and (self.shared or params is None):
@@ -154,10 +174,9 @@ class Circuit:
         inputs = _as_rows(inputs, B, self.F, self.device, "inputs")
         grad_out = _as_rows(grad_out, B, self.n, self.device, "grad_out")
         if dparams is None:
-            shape = (self.P,) if self.shared else (B, self.P)
-            dparams = torch.empty(shape, dtype=torch.float32, device=self.device)
+            dparams = self._param_grads(params, B)
         if dinputs is None:
-            dinputs = torch.empty((B, self.F), dtype=torch.float32, device=self.device)
+            dinputs = self._input_grads(inputs, B)
         _lib.vqc_backward(self.handle, B, _ptr(params), _ptr(inputs), grad_out.data_ptr(),
                           workspace.data_ptr(), workspace.numel(),
                           dparams.data_ptr() if self.P else None,
@@ -176,9 +195,8 @@ class Circuit:
             y = _as_rows(y.reshape(B, 1), B, 1, self.device, "y")
         E = torch.empty((B, self.n), dtype=torch.float32, device=self.device)
         g = torch.empty_like(E) if want_cot else None
-        dparams = torch.empty((self.P,) if self.shared else (B, self.P), dtype=torch.float32,
-                              device=self.device)
-        dinputs = torch.empty((B, self.F), dtype=torch.float32, device=self.device)
+        dparams = self._param_grads(params, B)
+        dinputs = self._input_grads(inputs, B)
         nb = _lib.vqc_workspace_bytes(self.handle, B, 2)
         if workspace is None and nb > 0:
             workspace = torch.empty(nb, dtype=torch.uint8, device=self.device)
@@ -196,9 +214,8 @@ class Circuit:
         params = self._params(params, B)
         inputs = _as_rows(inputs, B, self.F, self.device, "inputs")
         grad_out = _as_rows(grad_out, B, self.n, self.device, "grad_out")
-        dparams = torch.empty((self.P,) if self.shared else (B, self.P), dtype=torch.float32,
-                              device=self.device)
-        dinputs = torch.empty((B, self.F), dtype=torch.float32, device=self.device)
+        dparams = self._param_grads(params, B)
+        dinputs = self._input_grads(inputs, B)
         nb = _lib.vqc_workspace_bytes(self.handle, B, 3)
         ws = torch.empty(max(nb, 1), dtype=torch.uint8, device=self.device)
         _lib.vqc_fd_backward(self.handle, B, _ptr(params), _ptr(inputs), grad_out.data_ptr(),
