@@ -1500,7 +1500,7 @@ void emit_linear_tables(std::ostringstream& o, const Plan& p, const TanMode& t, 
       << "    for (int j = 0; j < " << W << "; ++j) par ^= __builtin_popcount(bits[j] & "
       << (pre ? "pre.r[r * " + W_ + " + j]" : "kArow[(blk * 64 + lane) * " + W_ + " + j]") << ");\n"
       << "    double all, before = block_scan(live ? 1.0 / fma((double)t, (double)t, 1.0) : 1.0, "
-         "lane, all);\n";
+         "all);\n";
     if (!adj.empty()) {
       o << "    before = lane_double(before, (word >> 16) & 63u);\n"
         << "    if (live && blk >= " << fwd.size() << ")\n"
