@@ -152,8 +152,9 @@ struct PassArgs {
   int32_t fd_slots, fd_base;   // slots fd_base .. fd_base + fd_slots - 1, or fd_slots 0
   float fd_h;
   // per-sample tables of the generated kernels' tangent form, written once per
-  // call by the table kernel and read by every pass: (t, cos phi') pairs
-  // [B][n_occ][2], the adjoint's gradient signs [B][n_occ], the <Z> signs [B][n]
+  // call by the table kernel and read by every pass: (t, gradient factor) pairs in
+  // the passes' order, then the heads' (cos, sin) [B][n_occ][2], the blocks'
+  // factors [B][n_occ] (at most one per rotation), the <Z> signs [B][n]
   float* tabs;
   float* gsig;
   float* esig;
