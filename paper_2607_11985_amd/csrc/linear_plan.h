@@ -721,6 +721,42 @@ bool partition_linear(const std::vector<LinGate>& all, int nq, int k, const Scan
   return true;
 }
 
+// The passes of the schedule that runs the CNOTs as gates, as linear passes: each
+// one's local space is spanned by its local qubits' directions at its start, in
+// which it runs at least the same gates.  Rarely these are fewer than the greedy
+// ones, and a training call keeps a state per pass: the fewer are taken, so that no
+// call needs more workspace than with the CNOTs as gates.  False when the slot
+// cap leaves gates over or there is no gate.
+bool partition_like_gates(const Plan& plan, const std::vector<LinGate>& all, const ScanLimits& cap,
+                          std::vector<LinearPass>& passes) {
+  std::vector<StreamGroup> groups;
+  std::string msg;
+  if (partition_stream(plan.prims, plan.nq, plan.ng, groups, msg) < 0) return false;
+  uint32_t v[kMaxQubits];
+  for (int q = 0; q < kMaxQubits; ++q) v[q] = 1u << q;
+  std::vector<int> pos(all.size());
+  for (size_t i = 0; i < all.size(); ++i) pos[i] = (int)i;
+  for (const StreamGroup& grp : groups) {
+    LinearPass lp;
+    Span S;
+    for (int q = 0; q < plan.nq; ++q)
+      if (!((grp.glob >> q) & 1u) && S.add(v[q])) lp.V.push_back(v[q]);
+    std::vector<int> took, left;
+    scan_gates(all, pos, S, kTakeAll, cap, &took, nullptr);
+    size_t t = 0;
+    for (int i : pos) {
+      if (t < took.size() && took[t] == i) ++t;
+      else left.push_back(i);
+    }
+    for (int i : took) lp.g.push_back(all[i]);
+    pos.swap(left);
+    if (!took.empty()) passes.push_back(std::move(lp));
+    for (const Prim& p : grp.prims)
+      if (p.kind == P_CNOT) v[p.q0] ^= v[p.q1];
+  }
+  return pos.empty() && !passes.empty();
+}
+
 // The memory layout between a pass with local space V and one with local space
 // W: a basis over the address bits in which both are spanned by address bits.
 // Their intersection takes the low bits (consecutive lanes then touch
@@ -851,6 +887,10 @@ int plan_linear_stream(Plan& plan, std::string& msg) {
     return VQC_ERR_UNSUPPORTED;
   };
   if (!partition_linear(all, nq, k, cap, ps)) return internal("streaming pass made no progress");
+  if (2 * ps.size() + 4 > plan.gate_passes) {  // not clearly fewer
+    std::vector<LinearPass> like;
+    if (partition_like_gates(plan, all, cap, like) && like.size() < ps.size()) ps.swap(like);
+  }
   const size_t nf = ps.size();
   plan.cols.clear();
   plan.maps.clear();

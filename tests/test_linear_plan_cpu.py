@@ -35,3 +35,11 @@ def test_replay(replay, n, count, gates, tile, rb):
     out = subprocess.run([replay, str(n), "0", str(count), str(gates), str(tile), str(rb)],
                          capture_output=True, text=True)
     assert out.returncode == 0 and out.stdout.endswith("ok\n"), out.stdout[-500:] + out.stderr
+
+
+def test_replay_more_greedy_passes(replay):
+    """A circuit whose greedy linear passes outnumber those with the CNOTs as
+    gates: the replay refuses more passes, so the fewer have to be taken."""
+    out = subprocess.run([replay, "16", "1009", "1", "150", "12", "0"], capture_output=True,
+                         text=True)
+    assert out.returncode == 0 and out.stdout.endswith("ok\n"), out.stdout[-500:] + out.stderr
