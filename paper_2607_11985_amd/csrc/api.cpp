@@ -950,7 +950,8 @@ int vqc_train_step_noalloc(const vqc_circuit* c, int64_t batch, const float* par
                            void* stream) {
   int rc = check_step_args(c, batch, params, inputs, loss_kind, target, expvals);
   if (rc || batch == 0) return rc;
-  const size_t need = required_bytes(c, batch, 2);
+  // the step's own layout: no other call uses the scratch
+  const size_t need = required_bytes(c->step ? c->step : c, batch, 2);
   if (need > (size_t)VQC_NOALLOC_SCRATCH_BYTES)
     return fail(VQC_ERR_TOO_LARGE,
                 "the step needs " + std::to_string(need) + " bytes of workspace; the static "
