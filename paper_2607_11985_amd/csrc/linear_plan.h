@@ -725,8 +725,11 @@ bool partition_linear(const std::vector<LinGate>& all, int nq, int k, const Scan
 // one's local space is spanned by its local qubits' directions at its start, in
 // which it runs at least the same gates.  Rarely these are fewer than the greedy
 // ones, and a training call keeps a state per pass: the fewer are taken, so that no
-// call needs more workspace than with the CNOTs as gates.  False when the slot
-// cap leaves gates over or there is no gate.
+// call needs more workspace than with the CNOTs as gates.  A group that runs no
+// rotation needs no pass: its CNOTs are in v.  But the first pass starts in
+// logical order, in a local space spanned by qubits, so when the first that runs
+// rotations has another one the first group stays as a pass of no gates.  False
+// when the slot cap leaves gates over or there is no gate.
 bool partition_like_gates(const Plan& plan, const std::vector<LinGate>& all, const ScanLimits& cap,
                           std::vector<LinearPass>& passes) {
   std::vector<StreamGroup> groups;
@@ -739,8 +742,12 @@ bool partition_like_gates(const Plan& plan, const std::vector<LinGate>& all, con
   for (const StreamGroup& grp : groups) {
     LinearPass lp;
     Span S;
+    uint32_t qubits = 0;
     for (int q = 0; q < plan.nq; ++q)
-      if (!((grp.glob >> q) & 1u) && S.add(v[q])) lp.V.push_back(v[q]);
+      if (!((grp.glob >> q) & 1u) && S.add(v[q])) {
+        lp.V.push_back(v[q]);
+        qubits |= v[q];
+      }
     std::vector<int> took, left;
     scan_gates(all, pos, S, kTakeAll, cap, &took, nullptr);
     size_t t = 0;
@@ -750,7 +757,15 @@ bool partition_like_gates(const Plan& plan, const std::vector<LinGate>& all, con
     }
     for (int i : took) lp.g.push_back(all[i]);
     pos.swap(left);
-    if (!took.empty()) passes.push_back(std::move(lp));
+    if (!took.empty()) {
+      if (passes.empty() && __builtin_popcount(qubits) != plan.k) {
+        LinearPass start;
+        for (int q = 0; q < plan.nq; ++q)
+          if (!((groups[0].glob >> q) & 1u)) start.V.push_back(1u << q);
+        passes.push_back(std::move(start));
+      }
+      passes.push_back(std::move(lp));
+    }
     for (const Prim& p : grp.prims)
       if (p.kind == P_CNOT) v[p.q0] ^= v[p.q1];
   }

@@ -153,14 +153,48 @@ double worst(const std::vector<double>& a, const std::vector<double>& b) {
   return d;
 }
 
+// Entanglers before the random gates, which leave the later rotations few or no
+// directions along single qubits: every pair in order, the last qubit with all
+// others both ways, random CNOTs, SWAPs and CZs; the last three again after a
+// layer of rotations (a product head).
+enum Prefix { kNone, kPairs, kHub, kNetwork, kHeadHub, kHeadNetwork, kHeadPairs };
+
+void add_prefix(std::vector<HostOp>& ops, int prefix, int n, std::mt19937& rng) {
+  auto gate = [&](int kind, int a, int b) {
+    HostOp o{};
+    o.kind = kind;
+    o.w[0] = a;
+    o.w[1] = b;
+    o.src[0] = VQC_SRC_PARAM;
+    o.mul[0] = 1.f;
+    ops.push_back(o);
+  };
+  if (prefix >= kHeadHub)
+    for (int q = 0; q < n; ++q) gate(VQC_RY, q, 0);
+  if (prefix == kPairs || prefix == kHeadPairs)
+    for (int i = 0; i < n; ++i)
+      for (int j = i + 1; j < n; ++j) gate(VQC_CNOT, i, j);
+  if (prefix == kHub || prefix == kHeadHub) {
+    for (int a = 0; a + 1 < n; ++a) gate(VQC_CNOT, n - 1, a);
+    for (int a = 0; a + 1 < n; ++a) gate(VQC_CNOT, a, n - 1);
+  }
+  if (prefix == kNetwork || prefix == kHeadNetwork)
+    for (int i = 40 + (int)(rng() % 41u); i > 0; --i) {
+      const int a = (int)(rng() % (unsigned)n), b = (a + 1 + (int)(rng() % (unsigned)(n - 1))) % n;
+      const int r = (int)(rng() % 10u);
+      gate(r < 8 ? VQC_CNOT : r < 9 ? VQC_SWAP : VQC_CZ, a, b);
+    }
+}
+
 // Every kind of plan of one random circuit: resident (with and without the
 // heads' rotations) or streaming (the same).
-int check(int n, int seed, int gates, int tile, int rb) {
+int check(int n, int seed, int gates, int tile, int rb, int prefix) {
   std::mt19937 rng(seed);
   auto pick = [&](int m) { return (int)(rng() % (unsigned)m); };
   std::vector<HostOp> ops;
-  const int P = gates;
+  const int P = std::max(gates, 1);
   const int style = seed % 4;  // how many entanglers
+  add_prefix(ops, prefix, n, rng);
   for (int i = 0; i < gates; ++i) {
     HostOp o{};
     for (int j = 0; j < 3; ++j) {
@@ -313,9 +347,9 @@ int check(int n, int seed, int gates, int tile, int rb) {
 int main(int argc, char** argv) {
   const int n = std::atoi(argv[1]), first = std::atoi(argv[2]), count = std::atoi(argv[3]);
   const int gates = std::atoi(argv[4]), tile = std::atoi(argv[5]), rb = std::atoi(argv[6]);
-  (void)argc;
+  const int prefix = argc > 7 ? std::atoi(argv[7]) : kNone;
   for (int s = first; s < first + count; ++s)
-    if (check(n, s, gates, tile, rb)) return 1;
+    if (check(n, s, gates, tile, rb, prefix)) return 1;
   std::printf("ok\n");
   return 0;
 }

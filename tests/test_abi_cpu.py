@@ -103,6 +103,18 @@ def test_configs_plan_on_host(idx):
     _lib.vqc_destroy(h)
 
 
+@pytest.mark.parametrize("n,prefix", [
+    (14, [(i, j) for i in range(14) for j in range(i + 1, 14)]),
+    (16, [(15, a) for a in range(15)] + [(a, 15) for a in range(15)])])
+@pytest.mark.parametrize("layer", [1, 11, 16])
+def test_entanglers_before_the_first_rotation_compile(lib, n, prefix, layer):
+    ops = [W.Op("CNOT", p) for p in prefix]
+    ops += [W.Op("RY", (q,), (("param", 0),)) for q in range(min(layer, n))]
+    rc, h = host_compile(ops, n, 1, 0)
+    assert rc == 0, _lib.vqc_last_error()
+    _lib.vqc_destroy(h)
+
+
 def test_host_only_handle_cannot_run(lib):
     w = W.make_config(1, batch=2)
     rc, h = host_compile(w.ops, 4, w.n_params, w.n_inputs)

@@ -50,9 +50,24 @@ def cnot_dense_circuit(n, seed, n_gates):
 @pytest.mark.parametrize("n,path", [(6, "auto"), (9, "auto"), (11, "auto"), (12, "auto"),
                                     (13, "auto"), (14, "stream"), (15, "auto"), (16, "auto")])
 def test_cnot_dense_circuits(torch_mod, n, path):
-    torch = torch_mod
+    check_circuit(torch_mod, *cnot_dense_circuit(n, 28000 + n, 16 * n), n, path)
+
+
+@pytest.mark.parametrize("n,rotations", [(14, 1), (14, 11), (15, 40), (16, 1), (16, 30)])
+@pytest.mark.parametrize("head", [False, True])
+def test_entanglers_before_the_first_rotation(torch_mod, n, rotations, head):
+    """The last qubit entangled with all others both ways before the first
+    rotation (head: after a layer of them, which the training step's plan leaves
+    out): no pass that runs rotations starts in a space spanned by qubits."""
+    ops = [W.Op("RY", (q,), (("input", q),)) for q in range(n)] if head else []
+    ops += [W.Op("CNOT", (n - 1, a)) for a in range(n - 1)]
+    ops += [W.Op("CNOT", (a, n - 1)) for a in range(n - 1)]
+    body, P, F = cnot_dense_circuit(n, 28500 + n, n + rotations)
+    check_circuit(torch_mod, ops + body[n:], P, F, n, "auto")
+
+
+def check_circuit(torch, ops, P, F, n, path):
     from paper_2607_11985_amd.api import Circuit
-    ops, P, F = cnot_dense_circuit(n, 28000 + n, 16 * n)
     B = 3
     params, inputs = W.random_inputs(B, P, F, seed=28100 + n)
     cot = W.random_cotangent(B, n, seed=28200 + n)

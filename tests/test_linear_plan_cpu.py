@@ -43,3 +43,17 @@ def test_replay_more_greedy_passes(replay):
     out = subprocess.run([replay, "16", "1009", "1", "150", "12", "0"], capture_output=True,
                          text=True)
     assert out.returncode == 0 and out.stdout.endswith("ok\n"), out.stdout[-500:] + out.stderr
+
+
+# (prefix, n, circuits, gates, tile_qubits): entanglers before the first rotation
+# (linear_replay.cpp, Prefix), of which the passes that run no rotation go, though
+# a plan's first pass has to start in logical order.  1-3 without a layer of
+# rotations in front, 4-6 with one, which the training step's plan leaves out.
+@pytest.mark.parametrize("prefix", [1, 2, 3, 4, 5, 6])
+@pytest.mark.parametrize("n,count,gates,tile", [
+    (12, 2, 12, 0), (14, 4, 1, 12), (15, 4, 12, 12), (15, 4, 1, 13), (16, 4, 1, 12),
+    (16, 4, 12, 13), (18, 2, 1, 12), (20, 1, 1, 12), (14, 2, 60, 12)])
+def test_replay_entanglers_first(replay, prefix, n, count, gates, tile):
+    out = subprocess.run([replay, str(n), "0", str(count), str(gates), str(tile), "0",
+                          str(prefix)], capture_output=True, text=True)
+    assert out.returncode == 0 and out.stdout.endswith("ok\n"), out.stdout[-500:] + out.stderr
