@@ -127,15 +127,26 @@ size_t stream_end(const Plan& p, int64_t batch, int mode) {
 // stream and one on a side stream, so that one half's passes fill the CUs the
 // other's leave idle (the tail of each pass; in the training step also the
 // HBM-bound forward of one half beside the VALU-bound adjoint of the other).
-// Each half has a layout of its own: [half 0 | half 1].  Below 2048 tiles a
-// call stays on one stream: its passes are short and the second half's launches
-// and the fork and join cost more than they fill (measured: 17-qubit QAOA
-// ansatz, 8 samples, 256 tiles of 13 qubits, autograd pass 206-228 us split,
-// 126 us not; 20-qubit ring, 3 samples, 768 tiles, step 192 and 187 us; 16-qubit
-// ring, 256 samples, 4096 tiles, step 979 and 1034 us).
-constexpr int64_t kSplitTiles = 2048;
-bool split_batch(const Plan& p, int64_t batch) {
-  return p.path == VQC_PATH_STREAM && batch >= 2 && (batch << p.ng) >= kSplitTiles;
+// Each half has a layout of its own: [half 0 | half 1].  A short call stays on one
+// stream: the second half's launches and the fork and join cost more than they
+// fill.  How long a call is goes with its amplitudes times its passes (the step
+// forks once for its forward and adjoint): two streams from 2^25 on.  Measured
+// with one and with two streams, 14 circuits and tile sizes of 512 to 8192 tiles
+// (inference | forward and backward | step, us):
+//   16-qubit ring of 8 layers, 64 samples     141, 134 | 396, 371 | 329, 281
+//   20-qubit ring of 4 layers, 6 samples      127, 125 | 368, 360 | 268, 257
+//   18-qubit HEA of 4 layers, 24 samples       99, 100 | 286, 309 | 208, 201
+//   14 qubits strongly entangling, 384         82,  90 | 243, 260 | 208, 201
+//   14 qubits re-uploading, 256 samples        55,  68 | 165, 192 | 141, 146
+// Over all of them this line costs 0.5, 0.3 and 0.2 % (at most 8.7 %) against the
+// better of the two each time; 2048 tiles of any size 1.5, 0.8 and 1.3 % (17 %),
+// 768 tiles of a long circuit among them (16-qubit ring 267 and 246 us a step).
+constexpr int64_t kSplitAmplitudes = int64_t(1) << 25;
+bool split_batch(const Plan& p, int64_t batch, int mode) {
+  if (p.path != VQC_PATH_STREAM || batch < 2) return false;
+  const int64_t passes = (int64_t)p.fpass.size() + (mode == 2 ? (int64_t)p.bpass.size() : 0);
+  const int64_t sample = passes << p.nq;
+  return batch >= (kSplitAmplitudes + sample - 1) / sample;
 }
 int64_t first_half(int64_t batch) { return (batch + 1) / 2; }
 size_t second_half_offset(const Plan& p, int64_t batch, int mode) {
@@ -146,7 +157,7 @@ size_t second_half_offset(const Plan& p, int64_t batch, int mode) {
 size_t required_bytes_core(const Plan& p, int64_t batch, int mode) {
   if (batch == 0) return 0;
   if (p.path == VQC_PATH_STREAM) {
-    if (split_batch(p, batch))
+    if (split_batch(p, batch, mode))
       return second_half_offset(p, batch, mode) + stream_end(p, batch - first_half(batch), mode);
     return stream_end(p, batch, mode);
   }
@@ -749,7 +760,7 @@ int vqc_forward_ex(const vqc_circuit* c, int64_t batch, const float* params, con
     // a workspace that holds the training layout keeps every pass's state
     const bool keep = workspace_bytes >= required_bytes_core(p, batch, 1);
     unsigned char* ws = static_cast<unsigned char*>(workspace);
-    if (!split_batch(p, batch))
+    if (!split_batch(p, batch, 0))  // (modes 0 and 1 alike)
       return stream_forward(c, batch, params, inputs, expvals, ws, stream, keep, psi0, probs);
     const int64_t P = c->shared ? 0 : p.P, N = (int64_t)1 << p.n;
     const size_t off = second_half_offset(p, batch, keep ? 1 : 0);
@@ -798,7 +809,7 @@ int vqc_backward(const vqc_circuit* c, int64_t batch, const float* params, const
   if (p.path == VQC_PATH_STREAM) {
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     float* dprows = rows ? rows : dp;
-    if (split_batch(p, batch)) {
+    if (split_batch(p, batch, 1)) {
       const int64_t P = c->shared ? 0 : p.P;
       const size_t off = second_half_offset(p, batch, 1);
       rc = on_two_streams(c, batch, stream, [&](int64_t b0, int64_t nb, int h, void* st) {
@@ -886,7 +897,7 @@ int train_step_impl(const vqc_circuit* c, int64_t batch, const float* params,
   if (p.path == VQC_PATH_STREAM) {
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     float* dprows = rows ? rows : dp;
-    if (split && split_batch(p, batch)) {
+    if (split && split_batch(sc->plan, batch, 2)) {
       const int64_t P = c->shared ? 0 : p.P;
       const size_t off = second_half_offset(sc->plan, batch, 2);
       rc = on_two_streams(c, batch, stream, [&](int64_t b0, int64_t nb, int h, void* st) {

@@ -27,6 +27,16 @@ def note(msg):
     sys.stdout.flush()
 
 
+def split_line(info, call):
+    """The first batch whose streaming `call` ("step", or "forward" for the separate
+    calls) runs as two halves on two streams: amplitudes times passes of 2^25."""
+    assert info["path"] == 2
+    passes = info["fwd_passes"]
+    if call == "step":
+        passes = info["step_fwd_passes"] + info["step_bwd_passes"] or 2 * passes
+    return max(2, -(-(1 << 25) // (passes << info["n_qubits"])))
+
+
 def gpu_run(torch, ops, n, P, F, params, inputs, cot=None, path="auto", engine="jit",
             reg_bits=0):
     """Forward (training) and, given a cotangent, backward through the C ABI."""

@@ -1,12 +1,14 @@
-"""Streaming calls run two batch halves on two streams from 2048 tiles on and
-stay on one stream below.  The same samples in a batch on either side of the
-line, and in a batch of a few, give the same rows bit for bit: the training
-step, the separate forward and backward, and the probabilities."""
+"""Streaming calls run two batch halves on two streams from 2^25 amplitudes times
+passes on and stay on one stream below (the step counts the passes of its
+forward and its adjoint, the separate calls their own).  The same samples in
+batches on either side of each line, and in a batch of a few, give the same
+rows bit for bit: the training step, the separate forward and backward, and
+the probabilities."""
 import numpy as np
 import pytest
 
 from paper_2607_11985_amd import workloads as W
-from tests.parity_util import note
+from tests.parity_util import note, split_line
 from tests.test_gpu_parity import torch_mod  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -18,26 +20,22 @@ def test_rows_do_not_depend_on_the_split(torch_mod):
     n = 14
     ops, P, F = W.strongly_entangling_circuit(n, 2)
     c = Circuit(ops, n, P, F, path="stream", tile_qubits=12)
-    at = 2048 >> (n - 12)  # the first batch that splits
-    params, inputs = W.random_inputs(at + 1, P, F, seed=4242)
-    cot = W.random_cotangent(at + 1, n, seed=4243)
+    lines = [split_line(c.info(), "step"), split_line(c.info(), "forward")]
+    assert lines[0] < lines[1]
+    top = lines[1] + 1
+    params, inputs = W.random_inputs(top, P, F, seed=4242)
+    cot = W.random_cotangent(top, n, seed=4243)
     tp, tx, tg = (torch.from_numpy(v).cuda() for v in (params, inputs, cot))
-    want = None
-    for B in (3, at - 1, at, at + 1):
-        note(f"split line n={n} B={B}")
+    below = None
+    for B in (top, lines[1], lines[1] - 1, lines[0], lines[0] - 1, 3):
+        note(f"split lines {lines} n={n} B={B}")
         p, x, g = tp[:B].contiguous(), tx[:B].contiguous(), tg[:B].contiguous()
         E, dp, dx = c.train_step(p, x, "sum")
         E2, pr, ws = c.forward_ex(p, x, probs=True, training=True)
         dp2, dx2 = c.backward(p, x, g, ws)
         torch.cuda.synchronize()
-        rows = [v[:3].cpu().numpy() for v in (E, dp, dx, E2, pr, dp2, dx2)]
-        if want is None:
-            want = rows
-        for w, r in zip(want, rows):
-            assert np.array_equal(w, r)
-        if B >= at - 1:  # every row, against the batch one below the line
-            full = [v[:at - 1].cpu().numpy() for v in (E, dp, dx, E2, dp2, dx2)]
-            if B == at - 1:
-                below = full
-            for w, r in zip(below, full):
-                assert np.array_equal(w, r)
+        rows = [v.cpu().numpy() for v in (E, dp, dx, E2, pr, dp2, dx2)]
+        if below is not None:
+            for w, r in zip(below, rows):
+                assert np.array_equal(w[:B], r)
+        below = rows
