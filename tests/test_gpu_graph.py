@@ -1,20 +1,20 @@
 """vqc_train_step captured into a HIP graph (through torch.cuda.graph) and
-replayed: the streaming step forks to the library's side stream and joins back
-with events, which the capture turns into graph dependencies; the resident
-step is one launch.  Every replay, with the program's own eager work and
+replayed: a long streaming step forks to the library's side stream and joins
+back with events, which the capture turns into graph dependencies; a short one
+stays on one stream; the resident step is one launch.  Every replay, with the program's own eager work and
 synchronizations between replays, reproduces the eager step bit for bit
 (outputs are cleared before each replay)."""
 import numpy as np
 import pytest
 
 from paper_2607_11985_amd import workloads as W
-from tests.parity_util import note
+from tests.parity_util import note, split_line
 from tests.test_gpu_parity import torch_mod  # noqa: F401
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("idx,B", [(5, 4), (4, 6), (2, 16)])
+@pytest.mark.parametrize("idx,B", [(5, 4), (4, 6), (2, 16), (5, 64), (4, 1025)])
 def test_train_step_graph_replays(torch_mod, idx, B):
     torch = torch_mod
     from paper_2607_11985_amd import _lib
@@ -23,6 +23,8 @@ def test_train_step_graph_replays(torch_mod, idx, B):
     n = w.n_qubits
     dev = torch.device("cuda", 0)
     c = Circuit(w.ops, n, w.n_params, w.n_inputs)
+    if B >= 64:
+        assert B >= split_line(c.info(), "step")
     note(f"{w.name} B={B}: graph capture and replays of the training step "
          f"(path {c.info()['path']})")
     p = torch.from_numpy(w.params).to(dev)

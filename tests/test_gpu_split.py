@@ -1,15 +1,18 @@
-"""The streaming training step runs the two halves of its batch on two streams
-(the caller's and the library's side stream).  Checked here: equal bit for bit
-to the separate forward, loss and backward calls (one stream, the whole batch)
-for odd and even batches and every loss head (the MSE heads average over the
-whole batch, not over a half), with shared parameters, and within the oracle's
-bars on sampled rows; and ordered on the caller's stream, so that work queued
-there after the call sees the whole step."""
+"""Long streaming calls run the two halves of their batch on two streams (the
+caller's and the library's side stream).  Checked here, with batches on both
+sides of the line (split_line; the small batches run on one stream, and each
+large one asserts that it splits): the training step equal bit for bit to the
+separate forward, loss and backward calls for odd and even batches and every
+loss head (the MSE heads average over the whole batch, not over a half), with
+shared parameters, and within the oracle's bars on rows of both halves; the
+separate calls, Psi_0 and probabilities among them, against the oracle; and
+every call ordered on the caller's stream, so that work queued there after it
+sees the whole call."""
 import numpy as np
 import pytest
 
 from paper_2607_11985_amd import workloads as W
-from tests.parity_util import check_step, note
+from tests.parity_util import check_step, note, split_line
 from tests.test_gpu_parity import torch_mod  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -26,7 +29,10 @@ def separate(torch, c, p, x, loss, yt):
 
 @pytest.mark.parametrize("n,B,loss,shared", [(14, 2, "mse_z0", False), (14, 3, "mse_meanz", False),
                                              (15, 5, "mean", True), (16, 4, "mse_meanz", False),
-                                             (16, 7, "sum", False)])
+                                             (16, 7, "sum", False),
+                                             (14, 1100, "mse_z0", False),
+                                             (14, 1025, "mse_meanz", False),
+                                             (15, 601, "mean", True), (16, 256, "sum", False)])
 def test_split_step_equals_separate_calls(torch_mod, n, B, loss, shared):
     torch = torch_mod
     from paper_2607_11985_amd.api import Circuit
@@ -38,6 +44,8 @@ def test_split_step_equals_separate_calls(torch_mod, n, B, loss, shared):
     y = np.random.default_rng(21200 + B).uniform(-1, 1, size=B).astype(np.float32)
     c = Circuit(ops, n, P, F, path="stream", shared_params=shared)
     assert c.info()["step_head_rotations"] == 0
+    if B > 7:
+        assert B >= split_line(c.info(), "forward") >= split_line(c.info(), "step")
     note(f"split step n={n} B={B} loss={loss} shared={shared} tiles={c.info()['tile_qubits']}")
     p = torch.from_numpy(np.ascontiguousarray(params[0] if shared else params)).cuda()
     x = torch.from_numpy(inputs).cuda()
@@ -49,7 +57,7 @@ def test_split_step_equals_separate_calls(torch_mod, n, B, loss, shared):
     for name, a, b in zip(("E", "g", "dparams", "dinputs"), got, ref):
         assert np.array_equal(a, b), f"{name} differs from the separate calls"
     if not shared:
-        rows = [0, B - 1]  # one row from each half
+        rows = [0, (B + 1) // 2 - 1, (B + 1) // 2, B - 1] if B > 7 else [0, B - 1]
         check_step(got[0][rows], got[1][rows], got[2][rows], got[3][rows], ops, n,
                    params[rows], inputs[rows], y[rows].astype(np.float64), loss, B)
 
@@ -60,9 +68,10 @@ def test_split_step_ordered_on_caller_stream(torch_mod):
     torch = torch_mod
     from paper_2607_11985_amd import _lib
     from paper_2607_11985_amd.api import Circuit
-    w = W.make_config(5, batch=16)
+    w = W.make_config(5, batch=256)
     B, n = w.batch, w.n_qubits
     c = Circuit(w.ops, n, w.n_params, w.n_inputs)
+    assert B >= split_line(c.info(), "step")
     dev = torch.device("cuda", 0)
     note(f"{w.name} B={B}: step on a side stream of the caller, then a copy on it")
     p = torch.from_numpy(w.params).to(dev)
@@ -86,11 +95,13 @@ def test_split_step_ordered_on_caller_stream(torch_mod):
         assert np.array_equal(a, b)
 
 
-@pytest.mark.parametrize("n,B", [(14, 2), (15, 5), (16, 3)])
+@pytest.mark.parametrize("n,B", [(14, 2), (15, 5), (16, 3), (14, 1201), (16, 300)])
 def test_split_forward_backward(torch_mod, n, B):
     """vqc_forward (inference and training workspaces), vqc_forward_ex with
-    Psi_0 and probabilities, and vqc_backward, each on two streams, against the
-    oracle on every row (B rows span both halves)."""
+    Psi_0 and probabilities, and vqc_backward against the oracle on every row of
+    the small batches, and of the large ones (two streams) on the first and the
+    last row of each half; their other rows against a forward of each half by
+    itself."""
     torch = torch_mod
     import oracle
     from paper_2607_11985_amd.api import Circuit
@@ -98,26 +109,42 @@ def test_split_forward_backward(torch_mod, n, B):
     ops, P, F = W.random_circuit(n, 10 * n, seed=21500 + n + B)
     params, inputs = W.random_inputs(B, P, F, seed=21600 + n + B)
     cot = W.random_cotangent(B, n, seed=21700 + n + B)
-    psi0 = W.random_states(B, n, seed=21800 + n + B)
+    half = (B + 1) // 2
+    rows = list(range(B)) if B <= 5 else [0, half - 1, half, B - 1]
+    states = W.random_states(len(rows), n, seed=21800 + n + B)
     c = Circuit(ops, n, P, F, path="stream")
+    if B > 5:
+        assert B >= split_line(c.info(), "forward")
     note(f"split forward/backward n={n} B={B}")
     p = torch.from_numpy(params).cuda()
     x = torch.from_numpy(inputs).cuda()
+    # the rows that are looked at have states of their own, the others share them
+    psi0 = torch.from_numpy(states).cuda()[torch.arange(B) % len(rows)]
+    psi0[rows] = torch.from_numpy(states).cuda()
     Ei = c.forward(p, x, training=False)
     Et, ws = c.forward(p, x, training=True)
     dp, dx = c.backward(p, x, torch.from_numpy(cot).cuda(), ws)
-    E0, pr, ws0 = c.forward_ex(p, x, torch.from_numpy(psi0).cuda(), probs=True, training=True)
+    E0, pr, ws0 = c.forward_ex(p, x, psi0, probs=True, training=True)
     dp0, dx0 = c.backward(p, x, torch.from_numpy(cot).cuda(), ws0)
     torch.cuda.synchronize()
     assert np.array_equal(Ei.cpu().numpy(), Et.cpu().numpy())
+    if B > 5:
+        for h in (slice(0, half), slice(half, B)):
+            Eh, prh = c.forward_ex(p[h].contiguous(), x[h].contiguous(), psi0[h].contiguous(),
+                                   probs=True)
+            assert torch.equal(Eh, E0[h]) and torch.equal(prh, pr[h])
+
+    def picked(t):
+        return t[rows].cpu().numpy()
+    params, inputs, cot = params[rows], inputs[rows], cot[rows]
     dpr, dxr, Er = oracle.vjp(ops, n, params, inputs, cot)
-    check_E(Et.cpu().numpy(), Er)
-    check_grads({"dp": dp.cpu().numpy(), "dx": dx.cpu().numpy()}, dpr, dxr, cot)
-    dpr0, dxr0, Er0 = oracle.vjp(ops, n, params, inputs, cot, psi0=psi0)
-    check_E(E0.cpu().numpy(), Er0)
-    check_grads({"dp": dp0.cpu().numpy(), "dx": dx0.cpu().numpy()}, dpr0, dxr0, cot)
-    _, st = oracle.forward(ops, n, params, inputs, want_state=True, psi0=psi0)
-    assert float(np.max(np.abs(pr.cpu().numpy() - np.abs(st) ** 2))) <= 1e-5
+    check_E(picked(Et), Er)
+    check_grads({"dp": picked(dp), "dx": picked(dx)}, dpr, dxr, cot)
+    dpr0, dxr0, Er0 = oracle.vjp(ops, n, params, inputs, cot, psi0=states)
+    check_E(picked(E0), Er0)
+    check_grads({"dp": picked(dp0), "dx": picked(dx0)}, dpr0, dxr0, cot)
+    _, st = oracle.forward(ops, n, params, inputs, want_state=True, psi0=states)
+    assert float(np.max(np.abs(picked(pr) - np.abs(st) ** 2))) <= 1e-5
 
 
 def test_split_calls_ordered_on_caller_stream(torch_mod):
@@ -126,9 +153,10 @@ def test_split_calls_ordered_on_caller_stream(torch_mod):
     torch = torch_mod
     from paper_2607_11985_amd import _lib
     from paper_2607_11985_amd.api import Circuit
-    w = W.make_config(5, batch=16)
+    w = W.make_config(5, batch=256)
     B, n = w.batch, w.n_qubits
     c = Circuit(w.ops, n, w.n_params, w.n_inputs)
+    assert B >= split_line(c.info(), "forward")
     dev = torch.device("cuda", 0)
     note(f"{w.name} B={B}: forward and backward on a side stream of the caller, then a copy")
     p = torch.from_numpy(w.params).to(dev)

@@ -8,15 +8,16 @@ calls (which run the heads as gates; both sides against the oracle, and
 within half its E bar of each other): heads of every kind and length, heads
 that end after other qubits' entanglers, constant and affine angles,
 parameters shared between heads and later gates, shared parameters over the
-batch, circuits that are heads only, general gates, odd batches (two halves on
-two streams) and a batch of one, configs 4 and 5 on sampled rows.  Bars as in
+batch, circuits that are heads only, general gates, odd batches, a batch of one
+and batches whose halves run on two streams, configs 4 and 5 on sampled rows.  Bars as in
 test_gpu_parity."""
 import numpy as np
 import pytest
 
 import oracle
 from paper_2607_11985_amd import workloads as W
-from tests.parity_util import G_FLOOR, G_REL, check_E, check_grad, check_grads, check_step, note
+from tests.parity_util import (G_FLOOR, G_REL, check_E, check_grad, check_grads, check_step,
+                               note, split_line)
 from tests.test_gpu_head import head_circuit
 from tests.test_gpu_parity import torch_mod  # noqa: F401
 
@@ -76,6 +77,18 @@ def test_stream_heads_random(torch_mod, n, loss, B):
     ops, P, F = head_circuit(n, 25000 + n)
     note(f"streaming heads n={n} loss={loss} B={B} ops={len(ops)}")
     run_and_check(torch_mod, ops, n, P, F, B, loss, 25100 + n + B)
+
+
+@pytest.mark.parametrize("n,loss,B", [(14, "mse_meanz", 1025), (16, "sum", 256)])
+def test_stream_heads_on_two_streams(torch_mod, n, loss, B):
+    """The first and the last row of each half against the oracle, and every row
+    of the step against the separate calls."""
+    from paper_2607_11985_amd.api import Circuit
+    ops, P, F = head_circuit(n, 25000 + n)
+    assert B >= split_line(Circuit(ops, n, P, F, path="stream").info(), "step")
+    half = (B + 1) // 2
+    note(f"streaming heads on two streams n={n} loss={loss} B={B} ops={len(ops)}")
+    run_and_check(torch_mod, ops, n, P, F, B, loss, 25200 + n, rows=[0, half - 1, half, B - 1])
 
 
 @pytest.mark.parametrize("n,trailing", [(14, False), (14, True), (16, True)])
