@@ -401,7 +401,9 @@ struct StepHead {
 };
 
 // Streaming forward: every pass (the first starts from |0...0> or reads psi0),
-// then the <Z> reduction into expvals; the last pass writes probs.  fd_slots > 0:
+// then the <Z> reduction into expvals; the last pass writes probs, or they go
+// through a state buffer that nothing else needs by then (an inference's next
+// output, a training call's lambda) and are put in order.  fd_slots > 0:
 // the batch is the central differences' shifted copies of slots fd_base ..
 int stream_forward(const vqc_circuit* c, int64_t batch, const float* params, const float* inputs,
                    float* expvals, unsigned char* ws, void* stream, bool keep,
@@ -409,6 +411,10 @@ int stream_forward(const vqc_circuit* c, int64_t batch, const float* params, con
                    int fd_slots = 0, float fd_h = 0.f, const StepHead* step = nullptr) {
   const Plan& p = c->plan;
   const StreamLayout L = stream_layout(p, batch);
+  const size_t last = p.fpass.size() - 1;
+  float* const raw = probs && p.order.on
+                         ? reinterpret_cast<float*>(ws + (keep ? L.l[0] : L.ck(last % 2)))
+                         : nullptr;
   int rc = 0;
   for (const vqc::PassPlan& pp : p.fpass) {
     vqc::PassArgs a = pass_args(c, pp, false, batch);
@@ -418,14 +424,18 @@ int stream_forward(const vqc_circuit* c, int64_t batch, const float* params, con
     set_tables(a, ws, L);
     a.psi_src = ws + (keep ? L.ck(i ? i - 1 : 0) : L.ck((i + 1) % 2));
     a.psi_dst = ws + (keep ? L.ck(i) : L.ck(i % 2));
-    if (!keep && i + 1 == p.fpass.size()) a.psi_dst = nullptr;  // nothing reads the last state
+    if (!keep && i == last) a.psi_dst = nullptr;  // nothing reads the last state
     if (psi0 && (a.flags & vqc::PF_INIT)) {
       if (p.product_head) return fail(VQC_ERR_UNSUPPORTED, "internal: Psi_0 with a product head");
       a.flags &= ~vqc::PF_INIT;
       a.psi_src = psi0;
       a.psi0_in = 1;
     }
-    if (a.flags & vqc::PF_ZPART) a.probs = probs;
+    if (a.flags & vqc::PF_ZPART) a.probs = raw ? raw : probs;
+    if (raw) {
+      a.io_lout = a.io_out;
+      a.probs_raw = 1;
+    }
     a.fd_base = fd_base;
     a.fd_slots = fd_slots;
     a.fd_h = fd_h;
@@ -442,6 +452,10 @@ int stream_forward(const vqc_circuit* c, int64_t batch, const float* params, con
              : vqc::launch_stream_pass(p, false, a, batch << p.ng, stream);
     if (rc) return hip_fail("forward pass launch", rc);
   }
+  if (raw && (rc = vqc::launch_order(p, batch, raw,
+                                     c->jit.tables ? reinterpret_cast<float*>(ws + L.esig) : nullptr,
+                                     probs, stream)))
+    return hip_fail("probability ordering launch", rc);
   if (!expvals) return VQC_OK;
   const float* epart = reinterpret_cast<const float*>(ws + L.epart);
   rc = step ? vqc::launch_reduce_e_loss(batch, p.ng, p.n, epart, expvals, step->kind, step->norm,

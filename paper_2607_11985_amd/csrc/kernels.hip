@@ -3,6 +3,7 @@
 // loss cotangent, and the launchers.  The device code lives in vqc_device.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "vqc.h"
@@ -107,6 +108,71 @@ __global__ void __launch_bounds__(256) sum_rows_kernel(int64_t B, int P,
     __syncthreads();
   }
   if (threadIdx.x == 0) out[p] = part[0];
+}
+
+// The probabilities of a streaming call from the last pass's addresses into logical
+// order: through LDS, a tile spanned by the lowest source bits and by the
+// directions of the lowest destination bits, so that a wave reads and writes 64
+// consecutive floats.  Memory-bound, 8 bytes per amplitude.  Stored by the pass
+// itself, a tile that covers c of the 5 index bits of a 128-byte line writes runs of
+// 2^c floats.  Time that 2^25 probabilities add to a call, us, stored by the pass |
+// this way, by c (entangling layers on 14 to 20 qubits):
+//   0: 362 | 80   1: 188 | 87   2: 161-258 | 61-74   3: 102-140 | 62-92
+//   4: 69 | 85    5: 35-66 | 71-86
+__global__ void __launch_bounds__(1 << (kOrderBits - kOrderRegs)) order_kernel(const OrderArgs A) {
+  __shared__ float lds[1 << kOrderBits];
+  constexpr int R = kOrderRegs, T = kOrderBits - R, N = 1 << R;
+  const int ng = A.n - kOrderBits;
+  const int64_t b = (int64_t)blockIdx.x >> ng;
+  const uint32_t g = blockIdx.x & ((1u << ng) - 1u), tid = threadIdx.x;
+  uint32_t src = 0, dst = 0, wr = 0, rd = 0;
+#pragma unroll
+  for (int i = 0; i < T; ++i) {
+    const uint32_t m = 0u - ((tid >> i) & 1u);
+    src ^= A.src_col[R + i] & m;
+    dst ^= A.dst_col[R + i] & m;
+    wr ^= A.wr[R + i] & m;
+    rd ^= A.rd[R + i] & m;
+  }
+  for (int i = 0; i < ng; ++i) {
+    const uint32_t m = 0u - ((g >> i) & 1u);
+    src ^= A.src_col[kOrderBits + i] & m;
+    dst ^= A.dst_col[kOrderBits + i] & m;
+  }
+  if (A.esig)
+    for (int q = 0; q < A.n; ++q)
+      if (A.esig[b * A.n + q] < 0.f) dst ^= 1u << q;
+  const float* in = A.src + (b << A.n);
+  float* out = A.dst + (b << A.n);
+  float v[N];
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    uint32_t o = src;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if ((j >> r) & 1) o ^= A.src_col[r];
+    v[j] = in[o];
+  }
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    uint32_t o = wr;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if ((j >> r) & 1) o ^= A.wr[r];
+    lds[o] = v[j];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    uint32_t o = rd, d = dst;
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+      if ((j >> r) & 1) {
+        o ^= A.rd[r];
+        d ^= A.dst_col[r];
+      }
+    out[d] = lds[o];
+  }
 }
 
 // Central differences: d L / d slot s of row b = sum_q g[b,q] (E(+h) - E(-h)) / 2h,
@@ -288,6 +354,23 @@ int launch_fd_combine(int64_t batch, int NS, int base, int P, int F, int n, floa
   if (batch * NS == 0) return 0;
   hipLaunchKernelGGL(fd_combine_kernel, dim3(grid_1d(batch * NS, 256)), dim3(256), 0,
                      (hipStream_t)stream, batch, NS, base, P, F, n, h, ev, g, dparams, dinputs);
+  return (int)hipGetLastError();
+}
+
+int launch_order(const Plan& plan, int64_t batch, const float* src, const float* esig, float* dst,
+                 void* stream) {
+  const ProbOrder& o = plan.order;
+  OrderArgs a = {};
+  std::copy(o.src_col.begin(), o.src_col.end(), a.src_col);
+  std::copy(o.dst_col.begin(), o.dst_col.end(), a.dst_col);
+  std::copy(o.wr.begin(), o.wr.end(), a.wr);
+  std::copy(o.rd.begin(), o.rd.end(), a.rd);
+  a.n = plan.n;
+  a.src = src;
+  a.dst = dst;
+  a.esig = esig;
+  hipLaunchKernelGGL(order_kernel, dim3((unsigned)(batch << (plan.n - kOrderBits))),
+                     dim3(1 << (kOrderBits - kOrderRegs)), 0, (hipStream_t)stream, a);
   return (int)hipGetLastError();
 }
 

@@ -886,6 +886,73 @@ void push_linear_io(const Basis& B, const Basis& M, int k, int R, std::vector<ui
   for (int p = k; p < B.n; ++p) cols.push_back(M.coord(B.b[p]));
 }
 
+// The probabilities' way into logical order from the last pass's layout M: its
+// address bits' images (rows of the measured Z-strings) give the destination.  A
+// tile of the last pass covers the 128-byte lines of the destination in runs of
+// 2^c floats, c of the 5 lowest bits; from c = 4 on the pass stores them itself,
+// below they go through order_kernel, where the times on both sides stand.
+bool order_probs(const Basis& M, const std::vector<uint32_t>& wfull, const std::vector<uint32_t>& V,
+                 ProbOrder& out) {
+  constexpr int kLineBits = 5, k = kOrderBits, R = kOrderRegs;
+  Basis img;  // the image of each address bit
+  img.n = M.n;
+  for (int a = 0; a < M.n; ++a)
+    for (int q = 0; q < M.n; ++q) img.b[a] |= odd(wfull[q] & M.b[a]) << q;
+  if (!img.invert()) return false;
+  auto image = [&](uint32_t v) {
+    uint32_t o = 0;
+    for (int q = 0; q < M.n; ++q) o |= odd(wfull[q] & v) << q;
+    return o;
+  };
+  Span lines;
+  for (uint32_t v : V) lines.add(image(v) >> kLineBits);
+  out = ProbOrder();
+  if ((int)V.size() - lines.dim >= 4) return true;
+  // in address coordinates: 64 consecutive addresses, the directions of 64
+  // consecutive destinations, further addresses up to a tile's dimension
+  Basis A, B;
+  A.n = B.n = M.n;
+  Span s;
+  std::vector<uint32_t> local;
+  auto take = [&](uint32_t v) {
+    if ((int)local.size() < k && s.add(v)) local.push_back(v);
+  };
+  for (int i = 0; i < 6; ++i) take(1u << i);
+  for (int i = 0; i < 6; ++i) take(img.coord(1u << i));
+  for (int a = 6; a < M.n; ++a) take(1u << a);
+  auto place = [&](Basis& T, const std::vector<uint32_t>& v) {  // v: its lanes first
+    for (int i = 0; i < k; ++i) T.b[i < k - R ? R + i : i - (k - R)] = v[i];
+  };
+  place(A, local);
+  std::vector<uint32_t> lanes;
+  Span t;
+  for (int i = 0; i < 6; ++i)
+    if (t.add(img.coord(1u << i))) lanes.push_back(img.coord(1u << i));
+  for (uint32_t v : local)
+    if (t.add(v)) lanes.push_back(v);
+  place(B, lanes);
+  int at = k;
+  for (int a = 0; a < M.n; ++a)
+    if (s.add(1u << a)) {
+      A.b[at] = B.b[at] = 1u << a;
+      ++at;
+    }
+  if (at != M.n || !A.invert() || !B.invert()) return false;
+  std::vector<uint32_t> cols;
+  emit_linear_exchange(A, B, k, R, cols);
+  out.wr.assign(cols.begin(), cols.begin() + k);
+  out.rd.assign(cols.begin() + k, cols.begin() + 2 * k);
+  for (int p = 0; p < M.n; ++p) {
+    uint32_t d = 0;
+    for (int a = 0; a < M.n; ++a)
+      if ((B.b[p] >> a) & 1u) d ^= img.b[a];
+    out.src_col.push_back(A.b[p]);
+    out.dst_col.push_back(d);
+  }
+  out.on = true;
+  return true;
+}
+
 int plan_linear_stream(Plan& plan, std::string& msg) {
   const int nq = plan.nq, k = plan.k;
   std::vector<uint32_t> wfull;
@@ -992,6 +1059,8 @@ int plan_linear_stream(Plan& plan, std::string& msg) {
       layout[nf].invert();
       stores[i] = s.end;
       for (int q = 0; q < plan.n; ++q) plan.lin.zrow.push_back(s.end.row(wfull[q]));
+      if (!order_probs(layout[nf], wfull, ps[i].V, plan.order))
+        return internal("order of the probabilities");
     }
     PassPlan pp;
     if (i == 0) pp.flags |= PF_INIT;

@@ -2208,9 +2208,9 @@ __device__ __forceinline__ void stream_body(const PassArgs& A, unsigned char* sm
     }
   } else if (flags & PF_ZPART) {
     if (A.probs) {
-      // the tile's rows are in logical order: a permutation of the stored
-      // state's addresses, so the stores stay coalesced
-      const uint32_t xm = frame_xmask(Sched::esigns(w), A.n);
+      // A linear schedule's lanes may lie anywhere in logical order: where a tile
+      // covers few of a line's entries it stores at its own addresses (probs_raw)
+      const uint32_t xm = A.probs_raw ? 0u : frame_xmask(Sched::esigns(w), A.n);
       float* pd = A.probs + sbase;
       const auto lout = [&](int i) { return A.io_lout[i]; };
       io_offsets<R>(lout, K, ng, tid, g, base, off);

@@ -62,6 +62,13 @@ struct LinSchedule {
   int start_off = 0, bwd_end_off = 0;  // resident: unit bases as mappings in `maps`
 };
 
+// How the probabilities a linear schedule's last pass stores in its own layout get
+// into logical order (OrderArgs).
+struct ProbOrder {
+  bool on = false;
+  std::vector<uint32_t> src_col, dst_col, wr, rd;
+};
+
 struct Plan {
   int n = 0, nq = 0, k = 0, t = 0, WG = 0, S = 0, G = 0;
   int R = kDefaultRegBits;                // register bits of the resident kernels
@@ -98,6 +105,7 @@ struct Plan {
   // without the heads' rotations.
   bool linear = false;
   LinSchedule lin, lin_step;
+  ProbOrder order;                        // streaming
   size_t gate_passes = 0;                 // streaming passes with the CNOTs as gates (both ways)
   int slot_cap = 0;                       // gradient slots a streaming pass may hold
   std::vector<int32_t> pslots;            // pass-local -> global gradient slots
@@ -151,6 +159,9 @@ int launch_reduce_e_loss(int64_t batch, int ng, int n, const float* epart, float
                          int64_t norm, const float* y, float* g, void* stream);
 int launch_reduce_grad(int64_t batch, int ng, int n_slots, int P, int F, const float* gpart,
                        float* dparams, float* dinputs, void* stream);
+// src [batch][2^n] into logical order at dst; esig as in PassArgs, or null
+int launch_order(const Plan& plan, int64_t batch, const float* src, const float* esig, float* dst,
+                 void* stream);
 int launch_fill_zero(float* p, int64_t count, void* stream);
 // slots base .. base + NS - 1 of the central differences; ev [batch][NS][2][n]
 int launch_fd_combine(int64_t batch, int NS, int base, int P, int F, int n, float h,

@@ -120,7 +120,7 @@ struct PassArgs {
   const uint32_t* io;          // tile I/O columns (k + ng): loads, in the layout read
   const uint32_t* io_out;      // stores, in the layout written
   const uint32_t* io_lin;      // loads in logical order (Psi_0)
-  const uint32_t* io_lout;     // stores in logical order (probabilities)
+  const uint32_t* io_lout;     // stores of the probabilities
   const uint8_t* start_phys;   // logical -> phys at pass start
   const uint8_t* end_phys;     // logical -> phys at pass end
   const uint32_t* zmask;       // measured Z-strings (as in TileArgs), or null
@@ -147,7 +147,10 @@ struct PassArgs {
   float* gpart;                // [B * 2^ng, n_slots] gradient partial sums
   const float* grad_out;
   uint32_t lds_tab, lds_acc;
-  float* probs;                // (last forward pass) [B][2^n] probabilities, or null
+  float* probs;                // (last forward pass) [B][2^n] probabilities, or null:
+                               // in logical order, or with probs_raw at io_lout's
+                               // addresses as they are (order_kernel sorts them)
+  int32_t probs_raw;
   // central differences: B counts shifted copies, 2 per slot of the chunk
   int32_t fd_slots, fd_base;   // slots fd_base .. fd_base + fd_slots - 1, or fd_slots 0
   float fd_h;
@@ -165,5 +168,19 @@ struct PassArgs {
   float* vpart;
   float* dparams;
   float* dinputs;
+};
+
+// The rearrangement of one array of 2^n floats per sample by a linear map of the
+// index bits (ProbOrder), 2^kOrderBits of them per workgroup.
+constexpr int kOrderBits = 12, kOrderRegs = 4;
+struct OrderArgs {
+  // per index bit of a workgroup's items (registers, threads, workgroup): the
+  // address bits read and written
+  uint32_t src_col[kMaxQubits], dst_col[kMaxQubits];
+  uint32_t wr[kOrderBits], rd[kOrderBits];  // LDS slots when storing and when reading
+  int32_t n;
+  const float* src;
+  float* dst;
+  const float* esig;           // [B][n]: the destination bits flipped where negative, or null
 };
 }  // namespace vqc

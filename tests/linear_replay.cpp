@@ -9,6 +9,7 @@
 #include <complex>
 #include <cstdio>
 #include <cstdlib>
+#include <map>
 #include <random>
 
 #include "vqc.h"
@@ -151,6 +152,52 @@ double worst(const std::vector<double>& a, const std::vector<double>& b) {
   double d = a.size() == b.size() ? 0 : 1;
   for (size_t i = 0; i < a.size() && i < b.size(); ++i) d = std::max(d, std::fabs(a[i] - b[i]));
   return d;
+}
+
+// The probabilities' way out of the last pass: a tile stores at least 16 consecutive
+// floats of a 128-byte line itself (lo: its logical addresses), or they are stored
+// at its own addresses (out) and put in order by tiles whose waves read and write
+// 64 consecutive floats and hit every LDS bank.
+bool probability_stores(const Plan& p, const std::vector<uint32_t>& lo,
+                        const std::vector<uint32_t>& out, const State& a, const State& ref) {
+  std::map<uint32_t, int> line;
+  for (uint32_t y = 0; y < 1u << p.k; ++y) ++line[lo[y] >> 5];
+  const ProbOrder& o = p.order;
+  if (!o.on) return line.begin()->second >= 16;
+  if (line.begin()->second >= 16) return false;
+  std::vector<double> raw(a.size()), got(a.size(), -1);
+  for (uint32_t y = 0; y < a.size(); ++y) raw[out[y]] = std::norm(a[y]);
+  const int K = kOrderBits, R = kOrderRegs;
+  for (uint32_t g = 0; g < a.size() >> K; ++g) {
+    std::vector<double> lds(1u << K, -1);
+    for (int side = 0; side < 2; ++side)
+      for (uint32_t y = 0; y < 1u << K; ++y) {
+        const uint32_t i = y | g << K;
+        const uint32_t at = xor_cols(side ? o.dst_col : o.src_col, 0, i);
+        const uint32_t slot = xor_cols(side ? o.rd : o.wr, 0, y);
+        if (slot >> K || at >= a.size()) return false;
+        if (side) {
+          if (got[at] >= 0 || lds[slot] < 0) return false;
+          got[at] = lds[slot];
+        } else {
+          if (lds[slot] >= 0) return false;
+          lds[slot] = raw[at];
+        }
+      }
+  }
+  for (const auto* c : {&o.src_col, &o.dst_col}) {
+    uint32_t all = 0;
+    for (int i = 0; i < 6; ++i) all |= (*c)[R + i] == 1u << i ? 1u << i : 0u;
+    if (all != 63u) return false;
+  }
+  for (const auto* c : {&o.wr, &o.rd}) {
+    uint32_t banks = 0;
+    for (uint32_t l = 0; l < 32; ++l) banks |= 1u << (xor_cols(*c, R, l) & 31u);
+    if (banks != ~0u) return false;
+  }
+  double d = 0;
+  for (size_t x = 0; x < got.size(); ++x) d = std::max(d, std::fabs(got[x] - std::norm(ref[x])));
+  return d <= 1e-10;
 }
 
 // Entanglers before the random gates, which leave the later rotations few or no
@@ -310,6 +357,7 @@ int check(int n, int seed, int gates, int tile, int rb, int prefix) {
         for (uint32_t y = 0; y < a.size(); ++y)
           d = std::max(d, std::fabs(std::norm(a[y]) - std::norm(ref[lo[y]])));
         if (d > 1e-10) return fail("probabilities", n, seed);
+        if (!probability_stores(p, lo, out, a, ref)) return fail("probability stores", n, seed);
       }
     }
     State lm = ck.back();

@@ -38,6 +38,9 @@ int launch_reduce_grad(int64_t, int, int, int, int, const float*, float*, float*
   no_device("reduce_grad");
 }
 int launch_fill_zero(float*, int64_t, void*) { no_device("fill"); }
+int launch_order(const Plan&, int64_t, const float*, const float*, float*, void*) {
+  no_device("order");
+}
 int launch_fd_combine(int64_t, int, int, int, int, int, float, const float*, const float*, float*,
                       float*, void*) {
   no_device("fd");

@@ -104,6 +104,29 @@ def test_streaming_psi0_probs(torch_mod, n, B, path):
     check(r["probs"], np.abs(st) ** 2, P_TOL, "probs")
 
 
+@pytest.mark.parametrize("n,layers,B", [(14, 4, 5), (16, 4, 3), (17, 3, 2), (20, 2, 2)])
+def test_streaming_probs_out_of_order(torch_mod, n, layers, B):
+    """Entangled circuits whose last pass covers few entries of a line of the
+    probabilities (order_kernel puts them in order), from an inference and from a
+    training call, whose backward then runs, with and without Psi_0."""
+    torch = torch_mod
+    ops, P, F = W.strongly_entangling_circuit(n, layers)
+    p, x = W.random_inputs(B, P, F, seed=390 + n)
+    cot = W.random_cotangent(B, n, seed=391 + n)
+    for s0 in (None, W.random_states(B, n, seed=392 + n)):
+        note(f"ordered probs n={n} layers={layers} B={B} psi0={s0 is not None}")
+        dpr, _, Er = oracle.vjp(ops, n, p, x, cot, psi0=s0)
+        _, st = oracle.forward(ops, n, p, x, want_state=True, psi0=s0)
+        for training in (False, True):
+            r = run_ex(torch, ops, n, P, F, p, x, s0, path="stream", training=training)
+            check(r["E"], Er, E_TOL, "E")
+            check(r["probs"], np.abs(st) ** 2, P_TOL, "probs")
+        dp, _ = r["circ"].backward(r["p"], r["x"], torch.from_numpy(cot).cuda(), r["ws"])
+        err = np.max(np.abs(dp.cpu().numpy() - dpr), axis=1)
+        assert np.all(err <= G_REL * np.max(np.abs(dpr), axis=1)
+                      + G_FLOOR * np.sum(np.abs(cot), axis=1)), err
+
+
 @pytest.mark.parametrize("n,path", [(5, "auto"), (10, "auto"), (14, "stream")])
 def test_interpreter_psi0_probs(torch_mod, n, path):
     ops, P, F = W.random_circuit(n, 10 * n, seed=380 + n)
