@@ -227,7 +227,8 @@ void vqc_destroy(vqc_circuit *c);
  *   training = 0: an inference vqc_forward;
  *   training = 1: a training vqc_forward (the saved final states) and the
  *                 vqc_backward calls that use it (plus their scratch);
- *   training = 2: vqc_train_step;
+ *   training = 2: vqc_train_step (never less than training = 1 needs, though
+ *                 the step itself may take fewer passes and use less);
  *   training = 3: vqc_fd_backward.
  * 0 means no workspace is needed.  Returns (size_t)-1 on invalid arguments.
  *
@@ -351,8 +352,8 @@ int vqc_train_step(const vqc_circuit *c, int64_t batch, const float *params, con
  * VQC_NOALLOC_SCRATCH_BYTES that the library holds on every GPU it runs on
  * until the process ends; the call itself allocates and frees nothing.
  * Arguments, results and errors as vqc_train_step without the workspace, plus
- * VQC_ERR_TOO_LARGE when vqc_workspace_bytes(c, batch, 2) exceeds
- * VQC_NOALLOC_SCRATCH_BYTES (e.g. 16 qubits on the streaming path: about 1.5
+ * VQC_ERR_TOO_LARGE when what the step uses of vqc_workspace_bytes(c, batch, 2)
+ * exceeds VQC_NOALLOC_SCRATCH_BYTES (e.g. 16 qubits on the streaming path: about 1.5
  * MiB per sample).  Every call on one GPU uses that GPU's single array and
  * finds there what the last call left (the call clears what must start at
  * zero): calls that overlap on one GPU, from other streams or threads, race

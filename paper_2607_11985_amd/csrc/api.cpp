@@ -195,16 +195,10 @@ size_t fd_rows_bytes(const Plan& p, int64_t batch) {
          align_up((size_t)batch * 2 * fd_chunk(p, batch) * p.n * 4, 256);
 }
 
+// What a call of `mode` uses (mode 2: the training step, which runs the step
+// circuit where there is one).
 size_t required_bytes(const vqc_circuit* c, int64_t batch, int mode) {
-  if (mode == 2 && c->step) {
-    // the training step runs the step circuit; its workspace also holds the
-    // other calls' (the whole circuit may take more passes, hence states)
-    vqc_circuit* const step = c->step;
-    size_t whole = required_bytes_core(c->plan, batch, 1) + (size_t)batch * c->plan.n * 4;
-    if (c->shared) whole = align_up(whole, 256) + (size_t)batch * c->plan.P * 4;
-    return std::max(batch ? whole : 0, required_bytes(step, batch, mode));
-  }
-  const Plan& p = c->plan;
+  const Plan& p = mode == 2 && c->step ? c->step->plan : c->plan;
   if (batch == 0) return 0;
   if (mode == 3) return fd_rows_bytes(p, batch) + (c->shared ? (size_t)batch * p.P * 4 : 0);
   if (!c->shared || mode == 0 || p.P == 0) return required_bytes_core(p, batch, mode);
@@ -735,7 +729,12 @@ void vqc_destroy(vqc_circuit* c) { delete c; }
 
 size_t vqc_workspace_bytes(const vqc_circuit* c, int64_t batch, int32_t training) {
   if (!c || batch < 0 || training < 0 || training > 3) return (size_t)-1;
-  return required_bytes(c, batch, training);
+  if (training != 2 || batch == 0) return required_bytes(c, batch, training);
+  // a step's workspace also serves the separate calls: the whole circuit may take
+  // more passes than the step's, hence states
+  const size_t apart = align_up(required_bytes(c, batch, 1), 256) +
+                       (c->plan.path == VQC_PATH_STREAM ? (size_t)batch * c->plan.n * 4 : 0);
+  return std::max(required_bytes(c, batch, 2), c->step ? apart : 0);
 }
 
 int vqc_forward(const vqc_circuit* c, int64_t batch, const float* params, const float* inputs,
@@ -975,8 +974,7 @@ int vqc_train_step_noalloc(const vqc_circuit* c, int64_t batch, const float* par
                            void* stream) {
   int rc = check_step_args(c, batch, params, inputs, loss_kind, target, expvals);
   if (rc || batch == 0) return rc;
-  // the step's own layout: no other call uses the scratch
-  const size_t need = required_bytes(c->step ? c->step : c, batch, 2);
+  const size_t need = required_bytes(c, batch, 2);
   if (need > (size_t)VQC_NOALLOC_SCRATCH_BYTES)
     return fail(VQC_ERR_TOO_LARGE,
                 "the step needs " + std::to_string(need) + " bytes of workspace; the static "

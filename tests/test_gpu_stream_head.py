@@ -145,3 +145,35 @@ def test_stream_no_step_plan_without_heads(torch_mod):
     torch.cuda.synchronize()
     for a, b in ((E, E2), (dp, dp2), (dx, dx2)):
         assert np.array_equal(a.cpu().numpy(), b.cpu().numpy())
+
+
+def test_step_runs_in_its_own_workspace(torch_mod):
+    """The 16-qubit ring's step takes a pass less than the separate calls: a
+    workspace a state per sample smaller than vqc_workspace_bytes (which serves
+    those too) is enough for it, two states less is refused."""
+    torch = torch_mod
+    from paper_2607_11985_amd import _lib
+    from paper_2607_11985_amd.api import Circuit
+    w = W.make_config(5, batch=3)
+    B, n = w.batch, w.n_qubits
+    c = Circuit(w.ops, n, w.n_params, w.n_inputs)
+    info = c.info()
+    assert info["fwd_passes"] == info["step_fwd_passes"] + 1
+    p, x = torch.from_numpy(w.params).cuda(), torch.from_numpy(w.inputs).cuda()
+    E, dp, dx = c.train_step(p, x, "sum")
+    nb, state = c.workspace_bytes(B, 2), B * 8 << n
+    got = [torch.empty_like(t) for t in (E, dp, dx)]
+
+    def step(nbytes):
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        _lib.vqc_train_step(c.handle, B, p.data_ptr(), x.data_ptr(), _lib.LOSS["sum"], None,
+                            got[0].data_ptr(), None, got[1].data_ptr(), got[2].data_ptr(),
+                            ws.data_ptr(), nbytes, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+    note(f"step in its own workspace, {nb} bytes less {state}")
+    step(nb - state + state // 16)
+    for a, b in zip(got, (E, dp, dx)):
+        assert torch.equal(a, b)
+    with pytest.raises(_lib.VQCError) as e:
+        step(nb - 2 * state)
+    assert e.value.code == _lib.VQC_ERR_WORKSPACE
