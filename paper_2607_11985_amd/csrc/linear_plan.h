@@ -48,63 +48,6 @@ struct Span {
 
 uint32_t odd(uint32_t v) { return (uint32_t)__builtin_parity(v); }
 
-// The Paulis of the gates left waiting in a scan, kept by column (bit r of
-// cx[b]: row r's x has bit b) so that a test costs one XOR per bit of the tested
-// Pauli.  Rows are appended as they come; when all 64 are taken they are
-// replaced by a basis of their span (at most 2 kMaxQubits rows), which blocks
-// the same Paulis.
-struct Waiting {
-  uint64_t cx[32], cz[32];
-  uint64_t row[64];
-  int rows = 0;
-  Waiting() {
-    std::memset(cx, 0, sizeof cx);
-    std::memset(cz, 0, sizeof cz);
-  }
-  void append(uint64_t v) {
-    row[rows] = v;
-    for (uint32_t m = (uint32_t)(v >> 32); m; m &= m - 1u) cx[__builtin_ctz(m)] |= 1ull << rows;
-    for (uint32_t m = (uint32_t)v; m; m &= m - 1u) cz[__builtin_ctz(m)] |= 1ull << rows;
-    ++rows;
-  }
-  void compress() {
-    uint64_t lead[64] = {0}, keep[64];
-    int n = 0;
-    for (int r = 0; r < rows; ++r)
-      for (uint64_t v = row[r]; v;) {
-        const int b = 63 - __builtin_clzll(v);
-        if (!lead[b]) {
-          keep[n++] = lead[b] = v;
-          break;
-        }
-        v ^= lead[b];
-      }
-    *this = Waiting();
-    for (int r = 0; r < n; ++r) append(keep[r]);
-  }
-  void add(uint32_t x, uint32_t z) {
-    if (rows == 64) compress();
-    append((uint64_t)x << 32 | z);
-  }
-  bool blocks(uint32_t x, uint32_t z) const {
-    uint64_t anti = 0;
-    for (; z; z &= z - 1u) anti ^= cx[__builtin_ctz(z)];
-    for (; x; x &= x - 1u) anti ^= cz[__builtin_ctz(x)];
-    return anti != 0;
-  }
-};
-static_assert(2 * kMaxQubits < 64, "a basis of the waiting Paulis leaves room for another row");
-
-// A rotation in the fixed coordinates: kind P_RX (parity(x & z) even), P_RY (odd)
-// or P_RZ (x = 0).
-struct LinGate {
-  int kind;
-  uint32_t x, z;
-  int occ;
-  bool neg;   // its Pauli has a minus sign
-  bool held;  // a diagonal gate taken in runs: an RZ whose angle varies
-};
-
 // Whether a constant rotation is a Pauli or the identity (up to a phase) to
 // the last bit of its (cos, sin) pair.
 bool constant_pauli(const Plan& plan, int occ) {
@@ -165,74 +108,148 @@ struct ScanLimits {
   size_t window = SIZE_MAX;  // gates looked at
 };
 
-// Walks the gates `pos` in order and takes every one that commutes with all
-// gates left waiting before it, may run (mode, slot cap) and moves along a
-// vector of S.  Returns how many of those taken are not diagonal.  cand: the
-// directions outside S of gates that nothing else stops, one per coset.
-int scan_gates(const std::vector<LinGate>& g, const std::vector<int>& pos, const Span& S,
-               ScanMode mode, const ScanLimits& cap, std::vector<int>* took,
-               std::vector<uint32_t>* cand) {
-  constexpr size_t kMaxCand = 16;
-  constexpr int kGiveUp = 128;  // gates stopped in a row: those after them stay for a later scan
-  Waiting wait;
-  std::set<int> slots;
-  int stopped = 0;
-  std::vector<uint32_t> cosets;
-  int count = 0;
-  const size_t end = std::min(pos.size(), cap.window);
-  for (size_t j = 0; j < end && stopped < kGiveUp; ++j) {
-    const int i = pos[j];
-    const LinGate& e = g[i];
-    bool stop = wait.blocks(e.x, e.z);
-    if (!stop) stop = mode == kTakeEager ? e.held : mode == kTakeDiagonal ? e.x != 0u : false;
-    if (!stop && cap.occ_slot && e.occ >= 0) {
-      const int s = (*cap.occ_slot)[e.occ];
-      if (s >= 0 && !slots.count(s)) {
-        if ((int)slots.size() >= cap.cap) stop = true;
-        else if (S.holds(e.x)) slots.insert(s);
-      }
+// Scans over the gates of one list.  Which earlier gates a gate anticommutes with is
+// formed once per list, as bits (anti; the angle table in LDS bounds a list to
+// kLdsBytes / 8 gates, 52 MB), and what a direction leaves outside a span once per
+// span: the many scans that compare candidate directions then cost a few
+// instructions per gate.  Planning one circuit on the host, ms, with both formed in
+// every scan and this way: 12 qubits strongly entangling of 6 layers 12 -> 4.5, of 100
+// layers 300 -> 103; 13-qubit HEA of 6 layers 10 -> 4; 20-qubit ring of 8 layers and
+// its step 32 -> 10, 20 qubits strongly entangling of 4 layers 13 -> 5, of 100 layers
+// 670 -> 190; 10 qubits with 4000 random gates 570 -> 205.
+class Scanner {
+ public:
+  explicit Scanner(const std::vector<LinGate>& gates)
+      : g(gates), words((int)(gates.size() + 63) / 64), res(gates.size()),
+        res_of(gates.size(), 0) {
+    anti.assign((size_t)words * gates.size(), 0);
+    wait.assign(words, 0);
+    std::vector<uint64_t> cx((size_t)words * 32, 0), cz((size_t)words * 32, 0);
+    for (size_t i = 0; i < gates.size(); ++i) {
+      uint64_t* row = anti.data() + i * words;
+      const int end = (int)(i / 64) + 1;
+      auto add = [&](const std::vector<uint64_t>& c, uint32_t bits) {
+        for (; bits; bits &= bits - 1u) {
+          const uint64_t* col = c.data() + (size_t)__builtin_ctz(bits) * words;
+          for (int w = 0; w < end; ++w) row[w] ^= col[w];
+        }
+      };
+      add(cx, gates[i].z);
+      add(cz, gates[i].x);
+      const uint64_t bit = 1ull << (i % 64);
+      for (uint32_t m = gates[i].x; m; m &= m - 1u)
+        cx[(size_t)__builtin_ctz(m) * words + i / 64] |= bit;
+      for (uint32_t m = gates[i].z; m; m &= m - 1u)
+        cz[(size_t)__builtin_ctz(m) * words + i / 64] |= bit;
     }
-    if (!stop) {
-      const uint32_t r = S.residue(e.x);
-      if (!r) {
-        stopped = 0;
-        if (took) took->push_back(i);
-        if (e.x) ++count;
-        continue;
-      }
-      if (cand && cand->size() < kMaxCand &&
-          std::find(cosets.begin(), cosets.end(), r) == cosets.end()) {
-        cosets.push_back(r);
-        cand->push_back(e.x);
-      }
-    }
-    ++stopped;
-    wait.add(e.x, e.z);
   }
-  return count;
-}
+
+  // The span the following scans' gates move in.
+  void span(const Span& s) {
+    S = s;
+    ++span_no;
+  }
+
+  // Walks the gates `pos` in order and takes every one that commutes with all
+  // gates left waiting before it, may run (mode, slot cap) and moves along a
+  // vector of the span, or along `extra` (a residue outside it, 0: none) and one.
+  // Returns how many of those taken are not diagonal.  cand: the directions
+  // outside the span of gates that nothing else stops, one per coset.
+  int scan(const std::vector<int>& pos, uint32_t extra, ScanMode mode, const ScanLimits& cap,
+           std::vector<int>* took, std::vector<uint32_t>* cand) {
+    constexpr size_t kMaxCand = 16;
+    constexpr int kGiveUp = 128;  // gates stopped in a row: those after them stay for a later scan
+    const int lo = pos.empty() ? 0 : pos[0] / 64;
+    int cleared = lo;  // words [lo, cleared) of wait are this scan's
+    int stopped = 0, count = 0, n_slots = 0;
+    ++scan_no;
+    uint32_t cosets[kMaxCand];
+    const size_t end = std::min(pos.size(), cap.window);
+    for (size_t j = 0; j < end && stopped < kGiveUp; ++j) {
+      const int i = pos[j];
+      const LinGate& e = g[i];
+      for (; cleared <= i / 64; ++cleared) wait[cleared] = 0;
+      const uint64_t* row = anti.data() + (size_t)i * words;
+      bool stop = false;
+      for (int w = lo; w <= i / 64 && !stop; ++w) stop = (row[w] & wait[w]) != 0;
+      if (!stop) stop = mode == kTakeEager ? e.held : mode == kTakeDiagonal ? e.x != 0u : false;
+      if (!stop) {
+        if (res_of[i] != span_no) {
+          res[i] = S.residue(e.x);
+          res_of[i] = span_no;
+        }
+        const uint32_t r = res[i];
+        const bool holds = !r || r == extra;
+        if (cap.occ_slot && e.occ >= 0) {
+          const int s = (*cap.occ_slot)[e.occ];
+          if (s >= 0 && !seen(s)) {
+            if (n_slots >= cap.cap) {
+              stop = true;
+            } else if (holds) {
+              slot_scan[s] = scan_no;
+              ++n_slots;
+            }
+          }
+        }
+        if (!stop && holds) {
+          stopped = 0;
+          if (took) took->push_back(i);
+          if (e.x) ++count;
+          continue;
+        }
+        if (!stop && cand && cand->size() < kMaxCand &&
+            std::find(cosets, cosets + cand->size(), r) == cosets + cand->size()) {
+          cosets[cand->size()] = r;
+          cand->push_back(e.x);
+        }
+      }
+      ++stopped;
+      wait[i / 64] |= 1ull << (i % 64);
+    }
+    return count;
+  }
+
+  int scan(const std::vector<int>& pos, const Span& s, ScanMode mode, const ScanLimits& cap,
+           std::vector<int>* took, std::vector<uint32_t>* cand) {
+    span(s);
+    return scan(pos, 0u, mode, cap, took, cand);
+  }
+
+  const std::vector<LinGate>& g;
+
+ private:
+  bool seen(int slot) {
+    if ((size_t)slot >= slot_scan.size()) slot_scan.resize((size_t)slot + 1, 0);
+    return slot_scan[slot] == scan_no;
+  }
+  int words;
+  std::vector<uint64_t> anti, wait;
+  Span S;
+  std::vector<uint32_t> res;
+  std::vector<unsigned> res_of, slot_scan;
+  unsigned span_no = 0, scan_no = 0;
+};
 
 // Up to `dims` independent directions that let a scan take the most gates:
 // grown one at a time, by the count each candidate gives (ties: the earlier
 // gate's), or in circuit order; the better of the two.
-std::vector<uint32_t> choose_directions(const std::vector<LinGate>& g, const std::vector<int>& pos,
-                                        int dims, ScanMode mode, const ScanLimits& cap) {
+std::vector<uint32_t> choose_directions(Scanner& g, const std::vector<int>& pos, int dims,
+                                        ScanMode mode, const ScanLimits& cap) {
   std::vector<uint32_t> best;
   int best_count = -1;
   for (int look = 1; look >= 0; --look) {
     Span S;
     std::vector<uint32_t> dirs;
+    std::vector<uint32_t> cand;
     while ((int)dirs.size() < dims) {
-      std::vector<uint32_t> cand;
-      scan_gates(g, pos, S, mode, cap, nullptr, &cand);
+      cand.clear();
+      g.scan(pos, S, mode, cap, nullptr, &cand);
       if (cand.empty()) break;
       size_t pick = 0;
       if (look && cand.size() > 1) {
         int most = -1;
         for (size_t c = 0; c < cand.size(); ++c) {
-          Span s = S;
-          s.add(cand[c]);
-          const int n = scan_gates(g, pos, s, mode, cap, nullptr, nullptr);
+          const int n = g.scan(pos, S.residue(cand[c]), mode, cap, nullptr, nullptr);
           if (n > most) {
             most = n;
             pick = c;
@@ -242,13 +259,30 @@ std::vector<uint32_t> choose_directions(const std::vector<LinGate>& g, const std
       S.add(cand[pick]);
       dirs.push_back(cand[pick]);
     }
-    const int n = scan_gates(g, pos, S, mode, cap, nullptr, nullptr);
+    const int n = g.scan(pos, S, mode, cap, nullptr, nullptr);
     if (n > best_count) {
       best_count = n;
       best = dirs;
     }
   }
   return best;
+}
+
+// The gates of `pos` without those taken (in the order of pos).
+void drop_taken(std::vector<int>& pos, const std::vector<int>& took) {
+  if (took.empty()) return;
+  size_t t = 0, to = 0, at = 0;
+  for (; t < took.size(); ++at) {
+    if (pos[at] == took[t]) ++t;
+    else pos[to++] = pos[at];
+  }
+  pos.erase(pos.begin() + to, pos.begin() + at);
+}
+
+std::vector<int> every_gate(const std::vector<LinGate>& g) {
+  std::vector<int> pos(g.size());
+  for (size_t i = 0; i < g.size(); ++i) pos[i] = (int)i;
+  return pos;
 }
 
 // A basis of GF(2)^n: physical bit (or address bit) p moves along b[p].
@@ -441,16 +475,16 @@ void linear_exchange(LinearSweep& s, const Basis& to, int k, int R, bool lam) {
 // one of them, an exchange more.  The cost is an instruction count per wave:
 // per exchange and state the LDS accesses and addresses of 2^R amplitudes, per
 // run of diagonals the cheaper of gate by gate and one product.
-LinearSweep linear_sweep(const std::vector<LinGate>& g, const Basis& start, int k, int R, bool bwd,
+LinearSweep linear_sweep(Scanner& scanner, const Basis& start, int k, int R, bool bwd,
                          int flush_at) {
+  const std::vector<LinGate>& g = scanner.g;
   LinearSweep s;
   s.end = start;
   const double N = 1 << R, states = bwd ? 2.0 : 1.0;
   const ScanLimits none;
   ScanLimits near;  // an exchange runs about ten gates: those close by decide
   near.window = 64;
-  std::vector<int> pos(g.size());
-  for (size_t i = 0; i < g.size(); ++i) pos[i] = (int)i;
+  std::vector<int> pos = every_gate(g);
   auto emit_gates = [&](const std::vector<int>& took) {
     for (int i : took) {
       const LinGate& e = g[i];
@@ -462,40 +496,34 @@ LinearSweep linear_sweep(const std::vector<LinGate>& g, const Basis& start, int 
       n.arg = e.occ;
       s.ins.push_back(n);
     }
-    std::vector<int> left;
-    size_t t = 0;
     std::vector<int> sorted(took);
     std::sort(sorted.begin(), sorted.end());
-    for (int i : pos) {
-      if (t < sorted.size() && sorted[t] == i) ++t;
-      else left.push_back(i);
-    }
-    pos.swap(left);
+    drop_taken(pos, sorted);
   };
   bool fresh = false;  // an exchange and nothing since
   while (!pos.empty()) {
     Span S;
     for (int r = 0; r < R; ++r) S.add(s.end.b[r]);
     std::vector<int> took;
-    scan_gates(g, pos, S, kTakeEager, none, &took, nullptr);
+    scanner.scan(pos, S, kTakeEager, none, &took, nullptr);
     if (!took.empty()) {
       emit_gates(took);
       fresh = false;
     }
     if (pos.empty()) break;
-    const int ready = scan_gates(g, pos, S, kTakeAll, none, nullptr, nullptr);
+    const int ready = scanner.scan(pos, S, kTakeAll, none, nullptr, nullptr);
     std::vector<uint32_t> dirs;
     bool flush = ready >= flush_at || (fresh && ready > 0);
     if (!flush) {
-      dirs = choose_directions(g, pos, R, flush_at == INT_MAX ? kTakeEager : kTakeAll, near);
+      dirs = choose_directions(scanner, pos, R, flush_at == INT_MAX ? kTakeEager : kTakeAll, near);
       flush = true;
       for (uint32_t d : dirs) flush = flush && S.holds(d);
     }
     if (flush) {
       std::vector<int> diag, fixed, rz;  // (all commute)
-      scan_gates(g, pos, S, kTakeDiagonal, none, &diag, nullptr);
+      scanner.scan(pos, S, kTakeDiagonal, none, &diag, nullptr);
       if (diag.empty()) {  // only gates off the register bits are left to run
-        dirs = choose_directions(g, pos, R, kTakeAll, none);
+        dirs = choose_directions(scanner, pos, R, kTakeAll, none);
         if (dirs.empty()) break;
       } else {
         int held = 0;
@@ -520,15 +548,18 @@ LinearSweep linear_sweep(const std::vector<LinGate>& g, const Basis& start, int 
   return s;
 }
 
-// The cheapest of the sweeps over a few thresholds; false when a gate never
-// ran.  No threshold wins everywhere (step of 12 qubits, 6 strongly entangling
+// The cheapest of the sweeps over a few thresholds (they differ only where an RZ
+// waits); false when a gate never ran.  No threshold wins everywhere (step of 12 qubits, 6 strongly entangling
 // layers: 493, 495 and 500 us with 1, 3 and none, 481 us with the choice; 14
 // qubits re-uploading: 9.81, 9.61, 9.51 and 9.55 ms).
 bool best_sweep(const std::vector<LinGate>& g, const Basis& start, int k, int R, bool bwd,
                 LinearSweep& best) {
   best.cost = -1.0;
+  Scanner scanner(g);
+  const bool held = std::any_of(g.begin(), g.end(), [](const LinGate& e) { return e.held; });
   for (int flush_at : {1, 3, INT_MAX}) {
-    LinearSweep s = linear_sweep(g, start, k, R, bwd, flush_at);
+    if (best.cost >= 0.0 && !held) break;
+    LinearSweep s = linear_sweep(scanner, start, k, R, bwd, flush_at);
     size_t gates = 0;
     for (const LinIns& n : s.ins) gates += n.op != OP_EXCHANGE;
     if (gates != g.size()) return false;
@@ -565,23 +596,22 @@ int append_basis_map(const Basis& B, std::vector<uint8_t>& maps) {
 // those that let the first scan take the most gates; ties and the rest by first
 // use, `allowed` the qubits to choose from.
 std::vector<uint32_t> start_qubits(const std::vector<LinGate>& g, int nq, int R, uint32_t allowed) {
-  std::vector<int> pos(g.size()), first(nq, INT_MAX);
-  for (size_t i = 0; i < g.size(); ++i) {
-    pos[i] = (int)i;
+  const std::vector<int> pos = every_gate(g);
+  std::vector<int> first(nq, INT_MAX);
+  for (size_t i = 0; i < g.size(); ++i)
     for (int q = 0; q < nq; ++q)
       if (((g[i].x >> q) & 1u) && first[q] == INT_MAX) first[q] = (int)i;
-  }
+  Scanner scanner(g);
   const ScanLimits none;
   Span S;
   std::vector<uint32_t> dirs;
   uint32_t used = 0;
   while ((int)dirs.size() < R) {
     int best = -1, most = -1;
+    scanner.span(S);
     for (int q = 0; q < nq; ++q) {
       if (!((allowed >> q) & 1u) || ((used >> q) & 1u)) continue;
-      Span s = S;
-      s.add(1u << q);
-      const int n = scan_gates(g, pos, s, kTakeAll, none, nullptr, nullptr);
+      const int n = scanner.scan(pos, S.residue(1u << q), kTakeAll, none, nullptr, nullptr);
       if (n > most || (n == most && first[q] < first[best])) {
         most = n;
         best = q;
@@ -651,11 +681,6 @@ int plan_linear_resident(Plan& plan, const std::vector<char>* skip, LinSchedule&
 }
 
 // ---------------------------------------------------------------- streaming
-struct LinearPass {
-  std::vector<uint32_t> V;  // k vectors: the local space
-  std::vector<LinGate> g;
-};
-
 // Pass partition: the first pass's local space is spanned by k qubits (it
 // starts from |0...0>, a product state or a caller's state in logical order),
 // found by dropping one qubit at a time; every later pass grows its space
@@ -665,8 +690,8 @@ struct LinearPass {
 // (5 passes per direction instead of the 10 that run the CNOTs as gates).
 bool partition_linear(const std::vector<LinGate>& all, int nq, int k, const ScanLimits& cap,
                       std::vector<LinearPass>& passes) {
-  std::vector<int> pos(all.size());
-  for (size_t i = 0; i < all.size(); ++i) pos[i] = (int)i;
+  std::vector<int> pos = every_gate(all);
+  Scanner scanner(all);
   do {
     LinearPass lp;
     Span S;
@@ -686,8 +711,8 @@ bool partition_linear(const std::vector<LinGate>& all, int nq, int k, const Scan
         int best = -1, most = -1;
         for (int q = 0; q < nq; ++q) {
           if (!((in >> q) & 1u)) continue;
-          const int n = scan_gates(all, pos, span_of(in & ~(1u << q)), kTakeAll, cap, nullptr,
-                                   nullptr);
+          const int n = scanner.scan(pos, span_of(in & ~(1u << q)), kTakeAll, cap, nullptr,
+                                     nullptr);
           if (n > most || (n == most && first[q] >= first[best])) {
             most = n;
             best = q;
@@ -699,23 +724,18 @@ bool partition_linear(const std::vector<LinGate>& all, int nq, int k, const Scan
       for (int q = 0; q < nq; ++q)
         if ((in >> q) & 1u) lp.V.push_back(1u << q);
     } else {
-      for (uint32_t d : choose_directions(all, pos, k, kTakeAll, cap))
+      for (uint32_t d : choose_directions(scanner, pos, k, kTakeAll, cap))
         if (S.add(d)) lp.V.push_back(d);
       for (uint32_t v : passes.back().V)  // shared with the pass before: longer runs of addresses
         if (S.dim < k && S.add(v)) lp.V.push_back(v);
       for (int q = 0; q < nq && S.dim < k; ++q)
         if (S.add(1u << q)) lp.V.push_back(1u << q);
     }
-    std::vector<int> took, left;
-    scan_gates(all, pos, S, kTakeAll, cap, &took, nullptr);
+    std::vector<int> took;
+    scanner.scan(pos, S, kTakeAll, cap, &took, nullptr);
     if (took.empty() && !pos.empty() && !passes.empty()) return false;
-    size_t t = 0;
-    for (int i : pos) {
-      if (t < took.size() && took[t] == i) ++t;
-      else left.push_back(i);
-    }
     for (int i : took) lp.g.push_back(all[i]);
-    pos.swap(left);
+    drop_taken(pos, took);
     passes.push_back(std::move(lp));
   } while (!pos.empty());
   return true;
@@ -737,8 +757,8 @@ bool partition_like_gates(const Plan& plan, const std::vector<LinGate>& all, con
   if (partition_stream(plan.prims, plan.nq, plan.ng, groups, msg) < 0) return false;
   uint32_t v[kMaxQubits];
   for (int q = 0; q < kMaxQubits; ++q) v[q] = 1u << q;
-  std::vector<int> pos(all.size());
-  for (size_t i = 0; i < all.size(); ++i) pos[i] = (int)i;
+  std::vector<int> pos = every_gate(all);
+  Scanner scanner(all);
   for (const StreamGroup& grp : groups) {
     LinearPass lp;
     Span S;
@@ -748,15 +768,10 @@ bool partition_like_gates(const Plan& plan, const std::vector<LinGate>& all, con
         lp.V.push_back(v[q]);
         qubits |= v[q];
       }
-    std::vector<int> took, left;
-    scan_gates(all, pos, S, kTakeAll, cap, &took, nullptr);
-    size_t t = 0;
-    for (int i : pos) {
-      if (t < took.size() && took[t] == i) ++t;
-      else left.push_back(i);
-    }
+    std::vector<int> took;
+    scanner.scan(pos, S, kTakeAll, cap, &took, nullptr);
     for (int i : took) lp.g.push_back(all[i]);
-    pos.swap(left);
+    drop_taken(pos, took);
     if (!took.empty()) {
       if (passes.empty() && __builtin_popcount(qubits) != plan.k) {
         LinearPass start;
@@ -953,22 +968,28 @@ bool order_probs(const Basis& M, const std::vector<uint32_t>& wfull, const std::
   return true;
 }
 
+// A streaming circuit's gates (the table kernel holds all entries, a pass at most
+// the slots' accumulators).
+std::vector<LinGate> stream_gates(const Plan& plan, std::vector<uint32_t>& wfull) {
+  const size_t acc = (size_t)plan.slot_cap * ((1u << (plan.k - plan.Rb)) / 64u) * 4;
+  return linear_gates(plan, nullptr, wfull,
+                      tables_fit(plan, plan.occ_src.size() * 8) &&
+                          tables_fit(plan, plan.lds_fwd + acc + 16));
+}
+
 int plan_linear_stream(Plan& plan, std::string& msg) {
   const int nq = plan.nq, k = plan.k;
   std::vector<uint32_t> wfull;
-  // (the table kernel holds all entries, a pass at most the slots' accumulators)
-  const size_t acc = (size_t)plan.slot_cap * ((1u << (plan.k - plan.Rb)) / 64u) * 4;
-  const std::vector<LinGate> all =
-      linear_gates(plan, nullptr, wfull,
-                   tables_fit(plan, plan.occ_src.size() * 8) &&
-                       tables_fit(plan, plan.lds_fwd + acc + 16));
+  const std::vector<LinGate> all = stream_gates(plan, wfull);
   const ScanLimits cap{plan.slot_cap, &plan.occ_slot};
   std::vector<LinearPass> ps;
   auto internal = [&](const char* what) {
     msg = std::string("internal: ") + what;
     return VQC_ERR_UNSUPPORTED;
   };
-  if (!partition_linear(all, nq, k, cap, ps)) return internal("streaming pass made no progress");
+  ps.swap(plan.parts);  // from the choice of the tile size
+  if (ps.empty() && !partition_linear(all, nq, k, cap, ps))
+    return internal("streaming pass made no progress");
   if (2 * ps.size() + 4 > plan.gate_passes) {  // not clearly fewer
     std::vector<LinearPass> like;
     if (partition_like_gates(plan, all, cap, like) && like.size() < ps.size()) ps.swap(like);
@@ -1021,9 +1042,8 @@ int plan_linear_stream(Plan& plan, std::string& msg) {
   };
   const ScanLimits none;
   auto first_directions = [&](const std::vector<LinGate>& g, int R) {
-    std::vector<int> pos(g.size());
-    for (size_t i = 0; i < g.size(); ++i) pos[i] = (int)i;
-    return choose_directions(g, pos, R, kTakeAll, none);
+    Scanner scanner(g);
+    return choose_directions(scanner, every_gate(g), R, kTakeAll, none);
   };
   // layout[i]: what pass i reads; layout[i + 1]: what it writes
   std::vector<Basis> layout(nf + 1), starts(nf), stores(nf);

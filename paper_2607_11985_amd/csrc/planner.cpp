@@ -1057,6 +1057,14 @@ int build_plan(const std::vector<HostOp>& ops, int n, int P, int F, int path, in
   return lane_gates && linear ? build_linear_plan(plan, msg) : 0;
 }
 
+// A linear streaming pass may hold more slots than a pass of the schedule with the
+// CNOTs as gates, while its accumulators fit.
+void set_slot_cap(Plan& plan) {
+  const int groups = (1 << (plan.k - plan.Rb)) / 64;
+  const int fit = (int)(((size_t)kLdsBytes - plan.lds_fwd) / (4 * (size_t)groups)) - 4;
+  plan.slot_cap = std::max(plan.max_pass_slots, std::min(256, fit));
+}
+
 // The generated kernels with one sample per workgroup run no CNOTs.  With 4
 // amplitudes per thread (8 qubits) they keep the schedule with gates on lane
 // bits, whose pairs need single lane bits.
@@ -1064,11 +1072,7 @@ int build_linear_plan(Plan& plan, std::string& msg) {
   plan.linear = plan.path == VQC_PATH_STREAM || (plan.S == 1 && plan.R >= 3);
   if (!plan.linear) return 0;
   if (plan.path == VQC_PATH_STREAM) {
-    // a pass may hold more slots than a pass of the schedule above, while its
-    // accumulators fit
-    const int groups = (1 << (plan.k - plan.Rb)) / 64;
-    const int fit = (int)(((size_t)kLdsBytes - plan.lds_fwd) / (4 * (size_t)groups)) - 4;
-    plan.slot_cap = std::max(plan.max_pass_slots, std::min(256, fit));
+    set_slot_cap(plan);
     const int rc = plan_linear_stream(plan, msg);
     if (rc < 0) return rc;
     stream_lds(plan);
@@ -1083,12 +1087,14 @@ int build_linear_plan(Plan& plan, std::string& msg) {
   return plan_linear_resident(plan, &in_head, plan.lin_step, msg);
 }
 
-// Streaming passes per direction of the linear schedule (0: internal failure).
-size_t linear_passes(const Plan& plan) {
+size_t linear_passes(Plan& plan) {
   std::vector<uint32_t> wfull;
-  std::vector<LinearPass> ps;
-  const ScanLimits cap{std::max(plan.max_pass_slots, 256), &plan.occ_slot};
-  return partition_linear(linear_gates(plan, nullptr, wfull, true), plan.nq, plan.k, cap, ps) ? ps.size() : 0;
+  set_slot_cap(plan);
+  plan.parts.clear();
+  if (!partition_linear(stream_gates(plan, wfull), plan.nq, plan.k,
+                        ScanLimits{plan.slot_cap, &plan.occ_slot}, plan.parts))
+    plan.parts.clear();
+  return plan.parts.size();
 }
 
 // The streaming training step's plan: the passes of `full` planned again

@@ -62,6 +62,22 @@ struct LinSchedule {
   int start_off = 0, bwd_end_off = 0;  // resident: unit bases as mappings in `maps`
 };
 
+// A rotation in the fixed coordinates: kind P_RX (parity(x & z) even), P_RY (odd)
+// or P_RZ (x = 0).
+struct LinGate {
+  int kind;
+  uint32_t x, z;
+  int occ;
+  bool neg;   // its Pauli has a minus sign
+  bool held;  // a diagonal gate taken in runs: an RZ whose angle varies
+};
+
+// A streaming pass of a linear schedule.
+struct LinearPass {
+  std::vector<uint32_t> V;  // k vectors: the local space
+  std::vector<LinGate> g;
+};
+
 // How the probabilities a linear schedule's last pass stores in its own layout get
 // into logical order (OrderArgs).
 struct ProbOrder {
@@ -108,6 +124,7 @@ struct Plan {
   ProbOrder order;                        // streaming
   size_t gate_passes = 0;                 // streaming passes with the CNOTs as gates (both ways)
   int slot_cap = 0;                       // gradient slots a streaming pass may hold
+  std::vector<LinearPass> parts;          // linear_passes', until the schedules are planned
   std::vector<int32_t> pslots;            // pass-local -> global gradient slots
   std::vector<PassPlan> fpass, bpass;     // streaming passes
   int start_off = 0, end_off = 0;         // resident: forward start / end mapping in `maps`
@@ -134,7 +151,9 @@ int build_plan(const std::vector<HostOp>& ops, int n, int P, int F, int path, in
                bool linear = true);
 // The generated kernels' linear schedules of a plan (linear_plan.h).
 int build_linear_plan(Plan& plan, std::string& msg);
-size_t linear_passes(const Plan& plan);
+// The greedy linear partition of a streaming plan, kept in it: its passes per
+// direction (0: internal failure).
+size_t linear_passes(Plan& plan);
 // Gradient slots (P + F) up to which the streaming training step runs a plan
 // without the heads (its head kernel holds a row of them in LDS).
 constexpr int kMaxStepSlots = 8192;

@@ -25,12 +25,12 @@ def replay(tmp_path_factory):
 
 # (n, circuits, gates, tile_qubits, reg_bits): resident with 8 and 16 amplitudes
 # per thread, streaming with one to several global qubits and every tile size,
-# 32 amplitudes per thread, and circuits with no gate at all
+# 32 amplitudes per thread, circuits with no gate at all, and long ones
 @pytest.mark.parametrize("n,count,gates,tile,rb", [
     (9, 16, 60, 0, 0), (10, 8, 120, 0, 0), (11, 8, 3, 0, 0), (12, 8, 90, 0, 0), (12, 4, 60, 0, 3),
     (13, 4, 80, 0, 0), (14, 8, 80, 12, 0), (14, 4, 80, 13, 0), (14, 4, 60, 14, 0),
     (15, 4, 100, 12, 0), (15, 4, 100, 12, 5), (16, 4, 150, 12, 0), (17, 4, 60, 13, 0),
-    (18, 2, 60, 12, 0), (16, 4, 0, 12, 0)])
+    (18, 2, 60, 12, 0), (16, 4, 0, 12, 0), (9, 2, 9000, 0, 0)])
 def test_replay(replay, n, count, gates, tile, rb):
     out = subprocess.run([replay, str(n), "0", str(count), str(gates), str(tile), str(rb)],
                          capture_output=True, text=True)
