@@ -3,8 +3,10 @@
 // physical index, exchanges through their LDS slots, streaming passes through
 // their address columns.  Compared with the circuit's primitives (CNOTs
 // included) applied one by one: the measured <Z> and the probabilities of the
-// forward, and the adjoint walking a copy of the final state back through every
-// saved state.  Prints one line per circuit; exits non-zero on a mismatch.
+// forward, the adjoint walking a copy of the final state back through every saved
+// state, and its gradients per slot (unit chain-rule factors).  Constant Paulis,
+// which the tables' frame carries, and the heads' gradients are left to the tests
+// on a GPU.  Prints one line per circuit; exits non-zero on a mismatch.
 #include <cmath>
 #include <complex>
 #include <cstdio>
@@ -88,10 +90,28 @@ bool exchange(State& s, const Plan& p, int off) {
   return true;
 }
 
+// Im <l| P |a>, P the Pauli of a rotation: its gradient at the gate's output
+double im_pauli(const State& l, const State& a, int op, uint32_t x, uint32_t z) {
+  const bool y_kind = op == OP_RY;
+  C v = 0;
+  for (uint32_t y = 0; y < a.size(); ++y) {
+    // P |y> = (-1)^parity(z & y) |y ^ x>, times i for RY (Y = i X Z)
+    const C t = std::conj(l[y ^ x]) * a[y];
+    v += odd(z & y) ? -t : t;
+  }
+  return (y_kind ? C(0, 1) * v : v).imag();
+}
+
+// grad: per gradient accumulator (LinIns::slot) the sum of its rotations' gradients
 bool run(State& a, State* l, const Plan& p, const std::vector<LinIns>& ins, int off, int n_ins,
-         const std::vector<double>& th, bool bwd, int R) {
+         const std::vector<double>& th, bool bwd, int R, std::vector<double>* grad = nullptr) {
   for (int i = off; i < off + n_ins; ++i) {
     const LinIns& e = ins[i];
+    if (grad && e.op != OP_EXCHANGE && e.slot >= 0) {
+      if (e.slot >= (int)grad->size()) return false;
+      const double g = im_pauli(*l, a, e.op, e.x, e.z);
+      (*grad)[e.slot] += e.neg ? -g : g;
+    }
     if (e.op == OP_EXCHANGE) {
       if (!e.lam && !exchange(a, p, e.arg)) return false;
       if (l && !exchange(*l, p, e.arg)) return false;
@@ -146,6 +166,17 @@ std::vector<double> expectations(const State& s, const std::vector<uint32_t>& ro
     e.push_back(v);
   }
   return e;
+}
+
+// The measured Z-strings' sum with the cotangent, applied to a state.
+State observed(const State& s, const std::vector<uint32_t>& rows, const std::vector<double>& cot) {
+  State l(s);
+  for (uint32_t y = 0; y < s.size(); ++y) {
+    double v = 0;
+    for (size_t q = 0; q < rows.size(); ++q) v += odd(rows[q] & y) ? -cot[q] : cot[q];
+    l[y] *= v;
+  }
+  return l;
 }
 
 double worst(const std::vector<double>& a, const std::vector<double>& b) {
@@ -295,6 +326,29 @@ int check(int n, int seed, int gates, int tile, int rb, int prefix) {
     std::vector<uint32_t> bits;
     for (int q = 0; q < n; ++q) bits.push_back(1u << q);
     const std::vector<double> E = expectations(ref, bits);
+    // every slot's gradient (unit chain-rule factors), the circuit walked back gate
+    // by gate
+    std::vector<double> cot, want_g(P, 0), got_g(P, 0);
+    for (int q = 0; q < n; ++q) cot.push_back(std::cos(1.0 + 2.0 * q));
+    {
+      State a = ref, l = observed(ref, bits, cot);
+      auto back = [&](const Prim& g) {
+        const bool rot = g.kind != P_CNOT && g.kind != P_CZ;
+        if (rot && full.occ_slot[g.occ] >= 0)
+          want_g[full.occ_slot[g.occ]] += im_pauli(
+              l, a, g.kind == P_RX ? OP_RX : g.kind == P_RY ? OP_RY : OP_RZ,
+              g.kind == P_RZ ? 0u : 1u << g.q0, g.kind == P_RX ? 0u : 1u << g.q0);
+        std::vector<double> inv;
+        if (rot) inv.assign(th.size(), -th[g.occ]);
+        apply_prim(a, g, inv);
+        apply_prim(l, g, inv);
+      };
+      for (size_t i = full.tail.size(); i-- > 0;) back(full.tail[i]);
+      for (size_t i = full.prims.size(); i-- > 0;) {
+        const Prim& g = full.prims[i];
+        if (!(step && g.occ >= 0 && in_head[g.occ])) back(g);
+      }
+    }
     auto to_tile = [&](const State& s, int map_off) {  // logical order -> a unit basis
       State t(s.size());
       for (uint32_t x = 0; x < s.size(); ++x) {
@@ -315,6 +369,10 @@ int check(int n, int seed, int gates, int tile, int rb, int prefix) {
       for (uint32_t y = 0; y < a.size(); ++y)
         d = std::max(d, std::fabs(std::norm(a[y]) - std::norm(ref[xor_cols(L.lcol, 0, y)])));
       if (d > 1e-10) return fail("probabilities", n, seed);
+      State ag = a, lg = observed(a, L.zrow, cot);
+      if (!run(ag, &lg, p, L.b, 0, (int)L.b.size(), th, true, p.R, &got_g))
+        return fail("adjoint instruction", n, seed);
+      if (worst(got_g, want_g) > 1e-9) return fail("gradients", n, seed);
       State l = a;
       if (!run(a, &l, p, L.b, 0, (int)L.b.size(), th, true, p.R))
         return fail("adjoint instruction", n, seed);
@@ -360,7 +418,8 @@ int check(int n, int seed, int gates, int tile, int rb, int prefix) {
         if (!probability_stores(p, lo, out, a, ref)) return fail("probability stores", n, seed);
       }
     }
-    State lm = ck.back();
+    State lm = ck.back(), gm(lm.size());
+    std::vector<char> added(P, 0);
     for (size_t j = 0; j < p.bpass.size(); ++j) {
       const PassPlan& pp = p.bpass[j];
       const size_t i = p.fpass.size() - 1 - j;
@@ -372,6 +431,28 @@ int check(int n, int seed, int gates, int tile, int rb, int prefix) {
       }
       if (j == 0 && worst(expectations(a, p.lin.zrow_b), E) > 1e-10)
         return fail("adjoint <Z> rows", n, seed);
+      {
+        State ag = a, lg(a.size());
+        if (j == 0) lg = observed(a, p.lin.zrow_b, cot);
+        else
+          for (uint32_t y = 0; y < a.size(); ++y) lg[y] = gm[in[y]];
+        std::vector<double> part(pp.n_slots, 0);
+        if (!run(ag, &lg, p, p.lin.b, pp.ins_off, pp.n_ins, th, true, p.Rb, &part))
+          return fail("adjoint instruction", n, seed);
+        for (int i2 = 0; i2 < pp.n_slots; ++i2) {
+          const int s = p.pslots[pp.slots_off + i2], slot = s < 0 ? ~s : s;
+          // complemented: the first pass to add to the slot, which stores
+          if (slot >= P || (s < 0) != !added[slot]) return fail("slot order", n, seed);
+          added[slot] = 1;
+          got_g[slot] += part[i2];
+        }
+        if (i > 0) {
+          const std::vector<uint32_t> out = addresses(p, pp.io_out_off, p.Rb);
+          for (uint32_t y = 0; y < a.size(); ++y) gm[out[y]] = lg[y];
+        } else if (worst(got_g, want_g) > 1e-9) {
+          return fail("gradients", n, seed);
+        }
+      }
       if (!run(a, &l, p, p.lin.b, pp.ins_off, pp.n_ins, th, true, p.Rb))
         return fail("adjoint instruction", n, seed);
       if (i > 0) {

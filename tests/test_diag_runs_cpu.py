@@ -2,8 +2,10 @@
 kernels (read back from the compile check, no GPU) hold fused runs in the
 forward and the adjoint on every kernel geometry, and the circuits of
 test_gpu_diag_runs reach the forms of a run that its GPU parity tests are
-there for: a product factor for two RZs of one bit, a frame-negated angle,
-and one parameter's partials summed in one pending slot.  Also the planner's
+there for: a product factor for two RZs of one mask, masks of several register
+bits, the thread's sign of an angle, a thread factor, a diagonal of which half
+the entries are formed (the others their conjugates), and one parameter's
+partials summed in one pending slot.  Also the planner's
 list schedule: runs of many RZs, with the exchange counts of circuit order."""
 import os
 import re
@@ -43,12 +45,18 @@ def test_runs_generated(tmp_path, n, path, fwd, bwd):
     assert runs(f) and runs(b), sorted(src)
     assert max(runs(b)) >= 4
     every = "".join(src.values())
-    # two RZs of one register bit in a run: a product factor for that bit
+    # two RZs of one register mask in a run: a product factor for that mask
     assert re.search(r"double F\d+r = 1\.0, F\d+i = ", every)
-    # an RZ on a bit under the swap frame, inside a run (16 amplitudes per
-    # thread; the kernels with lane gates keep no frame)
+    # linear schedules: an RZ whose parity has thread bits takes the thread's sign, one
+    # of several of them, some masks have several register bits, RZs on thread bits
+    # alone form a thread factor, and where there is none a flip may conjugate
     if n > 8:
         assert re.search(r"const float t\d+ = flip_sign\(tc\d+\.x, fs\d\);", every)
+        assert re.search(r"const auto fs\d = Odd\{\(uint32_t\)__builtin_popcount\(", every)
+        several = {3, 5, 6, 7, 9, 10, 11, 12, 13, 14, 15}
+        for form in (r"const double s(\d+) =", r"double F(\d+)r ="):
+            assert several & {int(v) for v in re.findall(form, every)}, form
+        assert "double Tr = 1.0" in every and "(-ei)" in every
     # one parameter read by two RZs of a run: the second partial adds to the pending slot
     blocks = re.findall(r"RZs as one diagonal\n(.*?)gate_boundary", b, re.S)
     assert any(re.search(r"pd(\d+) = g;.*pd\1 \+= g;", blk, re.S) for blk in blocks)

@@ -1,12 +1,13 @@
 """Runs of RZs applied as one diagonal (generated kernels): the forward
 multiplies each amplitude by the run's product once, the adjoint takes every
 gradient of the run from Im(conj(lambda) psi) and multiplies psi and lambda
-by the inverse product once.  Circuits built to reach every form of a run:
-RZs on register and on thread / tile bits, two RZs of one qubit in a row (a
-product factor per bit), RZs on bits under a swap frame (CNOTs with a high
-control and a low target before the layer), one parameter read by several
-RZs of a run (its partials summed in one pending slot), affine angles, and
-constant RZs between them (which stay gate by gate).  Against the oracle:
+by the inverse product once.  Circuits built to reach every form of a run: RZs
+on register and on thread / tile bits, two RZs of one qubit in a row (a product
+factor), RZs that read a parity of several register and thread bits (CNOTs
+before the layer, which the linear schedules take as a change of basis), one
+parameter read by several RZs of a run (its partials summed in one pending
+slot), affine angles, and constant RZs between them (which stay gate by gate);
+test_diag_runs_cpu reads the generated kernels for these forms.  Against the oracle:
 forward, adjoint and training step, on every kernel geometry (4 amplitudes
 per thread with lane gates, 16 resident, 16 streaming with product heads).
 Bars as in test_gpu_parity."""

@@ -1,12 +1,10 @@
-"""The swap frame of the generated kernels: CNOTs whose control sits on a
-thread / tile bit and whose target sits on a register bit only record, per
-thread, that the target bit's registers are swapped; later RY / RZ on that bit
-run with the angle (and the adjoint's gradient) negated, register CNOTs spread
-the frame, and LDS exchanges and pass stores fold it into their addresses,
-CZs and the epilogues resolve it.  Circuits dense in CNOTs (every control /
-target placement), interleaved with rotations of every kind and CZs, against
-the oracle: forward, adjoint, training step (resident and streaming, both
-with product heads), Psi_0 and probabilities.  Bars as in test_gpu_parity."""
+"""CNOT-dense circuits: from 9 qubits on the generated kernels run no CNOT and no
+CZ but schedule every rotation in the basis they change to, as a pairing along a
+mask of register bits under the sign of a parity over all bits; below, CNOTs are
+moves on register, lane and thread bits.  Every control / target placement,
+interleaved with rotations of every kind and CZs, against the oracle: forward,
+adjoint, training step (resident and streaming, both with product heads), Psi_0
+and probabilities.  Bars as in test_gpu_parity."""
 import numpy as np
 import pytest
 
