@@ -149,9 +149,9 @@ typedef struct {
                               rows [B, P] */
     int32_t tile_qubits; /* streaming path: qubits per tile, 12, 13 or 14
                             (0 = the default: with the generated kernels 12,
-                            unless it takes more than a quarter more passes
-                            than 13, with the CNOTs as gates or without, then
-                            13; 14 with the interpreter).  Each qubit less halves a
+                            unless it takes more than half again the passes
+                            of 13, or a quarter more with the CNOTs as gates,
+                            then 13; 14 with the interpreter).  Each qubit less halves a
                             workgroup's LDS, so more workgroups share a CU
                             and one's HBM traffic overlaps another's compute,
                             at the cost of more passes where the circuit

@@ -627,17 +627,26 @@ int vqc_compile(const vqc_op* ops, int32_t n_ops, int32_t n_qubits, int32_t n_pa
     delete c;
     return fail(rc, msg);
   }
-  // Default tiles of the generated kernels: 12 qubits unless they take more
-  // than a quarter more passes than 13, with the CNOTs as gates or without.
-  // Four workgroups per CU instead of two hide more latency (with the CNOTs as
-  // gates 1.6-4 % on the 14-qubit re-uploading workload at the same passes).
+  // Default tiles of the generated kernels: 12 qubits, of which four workgroups share
+  // a CU instead of two and one sample's tiles fill twice the CUs, unless they take
+  // more than half again the linear passes of 13, or a quarter more with the CNOTs as
+  // gates.  Measured at 12 and 13 (inference | forward and backward | step, us; passes
+  // of the whole circuit, linear and as gates, at 12 : 13):
+  //   4 : 3, 5 : 5  17-qubit ring x 4, 8 samples             50, 50 | 123, 134 |  93, 108
+  //   3 : 2, 6 : 6  17-qubit QAOA x 4, 8 samples             43, 44 | 106, 115 |  88, 108
+  //   3 : 2, 6 : 6  the same, 64 samples                    117, 109 | 339, 365 | 257, 320
+  //   2 : 1, 2 : 2  16 qubits, 40 random gates, 8 samples    24, 20 |  55,  50 |  45,  51
+  //   2 : 1, 2 : 2  the same, 64 samples                     45, 26 | 102,  75 |  78,  78
+  //   1 : 1, 2 : 1  14 qubits, 60 random gates, 512 samples  68, 50 | 181, 145 | 145, 148
+  //   3 : 3, 4 : 3  16 qubits entangling x 4, 8 samples      37, 45 |  96, 120 |  82,  99
+  // (the last line is what the second limit costs where the passes are many).
   if (engine == VQC_ENGINE_JIT && tile == 0 && c->plan.path == VQC_PATH_STREAM) {
     Plan p12;
     std::string msg12;
     if (vqc::build_plan(hops, n_qubits, n_params, n_inputs, path, reg_bits, p12, msg12, true, 12,
                         false) == 0 &&
         4 * p12.gate_passes <= 5 * c->plan.gate_passes &&
-        4 * vqc::linear_passes(p12) <= 5 * vqc::linear_passes(c->plan))
+        2 * vqc::linear_passes(p12) <= 3 * vqc::linear_passes(c->plan))
       c->plan = std::move(p12);
   }
   if (engine == VQC_ENGINE_JIT && (rc = vqc::build_linear_plan(c->plan, msg)) != 0) {

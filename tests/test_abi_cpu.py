@@ -115,6 +115,32 @@ def test_entanglers_before_the_first_rotation_compile(lib, n, prefix, layer):
     _lib.vqc_destroy(h)
 
 
+@pytest.mark.parametrize("n,layers,passes,tile", [(17, 4, (4, 3), 12), (16, 8, (6, 6), 12),
+                                                  (17, 0, (3, 2), 12), (16, 0, (2, 1), 13)])
+def test_default_tile(lib, n, layers, passes, tile):
+    """Passes of a 12- and a 13-qubit plan, and the default: 12 up to half again
+    the passes (Rot rings; the QAOA ansatz of a ring; 40 random gates)."""
+    if layers:
+        ops, P, F = W.rot_ring_circuit(n, layers)
+    elif n == 17:
+        ops, P, F = [W.Op("H", (q,)) for q in range(n)], 8, 0
+        for l in range(4):
+            ops += [W.Op("RZZ", (q, (q + 1) % n), (("param", l),)) for q in range(n)]
+            ops += [W.Op("RZ", (q,), (("param", l),)) for q in range(n)]
+            ops += [W.Op("RX", (q,), (("param", 4 + l),)) for q in range(n)]
+    else:
+        ops, P, F = W.random_circuit(n, 40, seed=11, kinds=W.GENERAL_KINDS, p_affine=0.3)
+    got = []
+    for t in (12, 13, 0):
+        opts = _lib.vqc_compile_opts(device=-1, tile_qubits=t)
+        rc, h = _lib.vqc_compile_raw(_lib.encode_ops(ops), len(ops), n, P, F, opts)
+        assert rc == 0
+        got.append(_lib.vqc_circuit_info(h))
+        _lib.vqc_destroy(h)
+    assert (got[0]["fwd_passes"], got[1]["fwd_passes"]) == passes
+    assert got[2]["tile_qubits"] == tile
+
+
 def test_host_only_handle_cannot_run(lib):
     w = W.make_config(1, batch=2)
     rc, h = host_compile(w.ops, 4, w.n_params, w.n_inputs)
