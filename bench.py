@@ -441,7 +441,9 @@ def measure(idx, args, torch, dev, want_cpu, cpu_budget):
         "tile_qubits": info["tile_qubits"] if not resident else None,
         "passes_fwd_bwd": [info["fwd_passes"], info["bwd_passes"]],
         "step_head_rotations": info["step_head_rotations"],
-        "exchanges_fwd_bwd": [info["fwd_exchanges"], info["bwd_exchanges"]],
+        # of the schedule with every CNOT as an instruction (the kernels of 9 or more
+        # qubits run a shorter one)
+        "gate_schedule_exchanges_fwd_bwd": [info["fwd_exchanges"], info["bwd_exchanges"]],
         "compile_s": round(compile_s, 2),
         "value": value, "ms_per_step": ms_per_step, "steps": K,
         "repeats": {"brackets": len(rates), "steps_per_bracket": Kr,

@@ -733,13 +733,11 @@ void emit_rz_run(Emit& E, const std::vector<RzItem>& run, const std::string& fac
   auto fs = [&](uint32_t mask) {
     return "fs" + std::to_string(std::find(thr.begin(), thr.end(), mask) - thr.begin());
   };
-  int nt = 0;
   for (int i = 0; i < L; ++i) {
     const RzItem& it = run[i];
     o << "    const float t" << i << " = ";
     if (it.thr) o << "flip_sign(tc" << i << ".x, " << fs(it.thr) << ");\n";
     else o << "tc" << i << ".x;\n";
-    if (!it.reg) ++nt;
   }
   if (bwd) {
     // the gradients, all from Im(conj(lambda) psi) at the run's output: its

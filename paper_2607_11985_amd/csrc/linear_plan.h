@@ -470,9 +470,10 @@ void linear_exchange(LinearSweep& s, const Basis& to, int k, int R, bool lam) {
   s.end = to;
 }
 
-// One register-level sweep over `g` from basis `start`.  Variable RZs wait until at least `flush_at` other gates on the present register bits wait
-// for them (or nothing else can run): a run of diagonals costs about as much as
-// one of them, an exchange more.  The cost is an instruction count per wave:
+// One register-level sweep over the scanner's gates from basis `start`.  Variable RZs
+// wait until at least `flush_at` other gates on the present register bits wait for
+// them (or nothing else can run): a run of diagonals costs about as much as one of
+// them, an exchange more.  The cost is an instruction count per wave:
 // per exchange and state the LDS accesses and addresses of 2^R amplitudes, per
 // run of diagonals the cheaper of gate by gate and one product.
 LinearSweep linear_sweep(Scanner& scanner, const Basis& start, int k, int R, bool bwd,
