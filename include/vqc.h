@@ -227,8 +227,8 @@ void vqc_destroy(vqc_circuit *c);
  *   training = 0: an inference vqc_forward;
  *   training = 1: a training vqc_forward (the saved final states) and the
  *                 vqc_backward calls that use it (plus their scratch);
- *   training = 2: vqc_train_step (never less than training = 1 needs, though
- *                 the step itself may take fewer passes and use less);
+ *   training = 2: vqc_train_step (enough for it; it may take fewer passes than
+ *                 the calls of training = 1 and then use less than this);
  *   training = 3: vqc_fd_backward.
  * 0 means no workspace is needed.  Returns (size_t)-1 on invalid arguments.
  *

@@ -739,11 +739,13 @@ void vqc_destroy(vqc_circuit* c) { delete c; }
 size_t vqc_workspace_bytes(const vqc_circuit* c, int64_t batch, int32_t training) {
   if (!c || batch < 0 || training < 0 || training > 3) return (size_t)-1;
   if (training != 2 || batch == 0) return required_bytes(c, batch, training);
-  // a step's workspace also serves the separate calls: the whole circuit may take
-  // more passes than the step's, hence states
-  const size_t apart = align_up(required_bytes(c, batch, 1), 256) +
-                       (c->plan.path == VQC_PATH_STREAM ? (size_t)batch * c->plan.n * 4 : 0);
-  return std::max(required_bytes(c, batch, 2), c->step ? apart : 0);
+  // A step's workspace also serves the separate calls, which may take more passes than
+  // the step, hence states -- where the linear passes are fewer than with the CNOTs as
+  // gates; elsewhere that would be more memory than the step took with those.
+  const vqc::Plan& p = c->plan;
+  const bool fewer = c->step && 2 * p.fpass.size() < p.gate_passes;
+  const size_t apart = fewer ? align_up(required_bytes(c, batch, 1), 256) + (size_t)batch * p.n * 4 : 0;
+  return std::max(required_bytes(c, batch, 2), apart);
 }
 
 int vqc_forward(const vqc_circuit* c, int64_t batch, const float* params, const float* inputs,

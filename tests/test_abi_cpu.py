@@ -115,6 +115,23 @@ def test_entanglers_before_the_first_rotation_compile(lib, n, prefix, layer):
     _lib.vqc_destroy(h)
 
 
+def test_step_of_fewer_passes_takes_less(lib):
+    """15 qubits whose heads take a pass of their own: the step, which builds them as
+    a product, takes one pass and less workspace than the separate calls' two."""
+    n = 15
+    ops = [W.Op("RY", (q,), (("param", 0),)) for q in range(n)]
+    ops += [W.Op("CZ", (q, q + 1)) for q in range(0, n - 1, 2)]
+    ops += [W.Op("RX", (q,), (("param", 1),)) for q in range(11)]
+    rc, h = host_compile(ops, n, 2, 0)
+    assert rc == 0
+    info = _lib.vqc_circuit_info(h)
+    assert (info["fwd_passes"], info["step_fwd_passes"]) == (2, 1)
+    apart, step = (_lib.vqc_workspace_bytes(h, 10, mode) for mode in (1, 2))
+    state = 10 * 8 << n
+    assert 3 * state < step < 3 * state + state // 8 and 4 * state < apart
+    _lib.vqc_destroy(h)
+
+
 @pytest.mark.parametrize("n,layers,passes,tile", [(17, 4, (4, 3), 12), (16, 8, (6, 6), 12),
                                                   (17, 0, (3, 2), 12), (16, 0, (2, 1), 13)])
 def test_default_tile(lib, n, layers, passes, tile):
