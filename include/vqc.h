@@ -353,8 +353,9 @@ int vqc_train_step(const vqc_circuit *c, int64_t batch, const float *params, con
  * until the process ends; the call itself allocates and frees nothing.
  * Arguments, results and errors as vqc_train_step without the workspace, plus
  * VQC_ERR_TOO_LARGE when what the step uses of vqc_workspace_bytes(c, batch, 2)
- * exceeds VQC_NOALLOC_SCRATCH_BYTES (e.g. 16 qubits on the streaming path: about 1.5
- * MiB per sample).  Every call on one GPU uses that GPU's single array and
+ * exceeds VQC_NOALLOC_SCRATCH_BYTES (on the streaming path a state of 8 * 2^n
+ * bytes per sample for each pass and two more; 16 qubits in 5 passes: 3.5 MiB
+ * per sample).  Every call on one GPU uses that GPU's single array and
  * finds there what the last call left (the call clears what must start at
  * zero): calls that overlap on one GPU, from other streams or threads, race
  * and must be ordered by the caller.  The whole step runs on `stream` (no side
