@@ -406,7 +406,7 @@ int stream_forward(const vqc_circuit* c, int64_t batch, const float* params, con
   const Plan& p = c->plan;
   const StreamLayout L = stream_layout(p, batch);
   const size_t last = p.fpass.size() - 1;
-  float* const raw = probs && p.order.on
+  float* const raw = probs && p.order.on && (batch << p.nq) >= p.order.from
                          ? reinterpret_cast<float*>(ws + (keep ? L.l[0] : L.ck(last % 2)))
                          : nullptr;
   int rc = 0;

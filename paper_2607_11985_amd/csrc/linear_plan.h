@@ -906,7 +906,11 @@ void push_linear_io(const Basis& B, const Basis& M, int k, int R, std::vector<ui
 // address bits' images (rows of the measured Z-strings) give the destination.  A
 // tile of the last pass covers the 128-byte lines of the destination in runs of
 // 2^c floats, c of the 5 lowest bits; from c = 4 on the pass stores them itself,
-// below they go through order_kernel, where the times on both sides stand.
+// below they go through order_kernel, where the times on both sides stand, in calls
+// large enough to repay its launch (about 3 us): from 2^20 amplitudes, at c = 3 from
+// 2^23.  Time that they add, us, stored by the pass and ordered: c = 0, 2^20 9.0, 7.6;
+// c = 1, 2^21 13.5, 9.9; c = 2, 2^17.6 5.3, 5.4 and 2^20 9.3, 7.1; c = 3, 2^22 5.1, 6.7
+// (20 qubits) and 21, 13 (14 qubits), 2^25 102, 92 and 140, 62.
 bool order_probs(const Basis& M, const std::vector<uint32_t>& wfull, const std::vector<uint32_t>& V,
                  ProbOrder& out) {
   constexpr int kLineBits = 5, k = kOrderBits, R = kOrderRegs;
@@ -922,8 +926,10 @@ bool order_probs(const Basis& M, const std::vector<uint32_t>& wfull, const std::
   };
   Span lines;
   for (uint32_t v : V) lines.add(image(v) >> kLineBits);
+  const int c = (int)V.size() - lines.dim;
   out = ProbOrder();
-  if ((int)V.size() - lines.dim >= 4) return true;
+  if (c >= 4) return true;
+  out.from = int64_t(1) << (c < 3 ? 20 : 23);
   // in address coordinates: 64 consecutive addresses, the directions of 64
   // consecutive destinations, further addresses up to a tile's dimension
   Basis A, B;

@@ -79,9 +79,10 @@ struct LinearPass {
 };
 
 // How the probabilities a linear schedule's last pass stores in its own layout get
-// into logical order (OrderArgs).
+// into logical order (OrderArgs), in calls of at least `from` amplitudes.
 struct ProbOrder {
   bool on = false;
+  int64_t from = 0;
   std::vector<uint32_t> src_col, dst_col, wr, rd;
 };
 

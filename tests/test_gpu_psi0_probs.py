@@ -104,27 +104,44 @@ def test_streaming_psi0_probs(torch_mod, n, B, path):
     check(r["probs"], np.abs(st) ** 2, P_TOL, "probs")
 
 
-@pytest.mark.parametrize("n,layers,B", [(14, 4, 5), (16, 4, 3), (17, 3, 2), (20, 2, 2)])
+@pytest.mark.parametrize("n,layers,B", [(14, 4, 517), (16, 4, 17), (17, 3, 9), (20, 2, 2)])
 def test_streaming_probs_out_of_order(torch_mod, n, layers, B):
     """Entangled circuits whose last pass covers few entries of a line of the
-    probabilities (order_kernel puts them in order), from an inference and from a
-    training call, whose backward then runs, with and without Psi_0."""
+    probabilities: from 2^20 (2^23 at 14 qubits) amplitudes on order_kernel puts them in
+    order, below the pass stores them itself.  From an inference and a training call,
+    whose backward then runs, with and without Psi_0; the first, a middle and the last
+    row against the oracle, and the first rows equal bit for bit from a batch below
+    the line."""
     torch = torch_mod
+    from paper_2607_11985_amd.api import Circuit
     ops, P, F = W.strongly_entangling_circuit(n, layers)
+    rows = sorted({0, B // 2, B - 1})
     p, x = W.random_inputs(B, P, F, seed=390 + n)
     cot = W.random_cotangent(B, n, seed=391 + n)
-    for s0 in (None, W.random_states(B, n, seed=392 + n)):
+    states = W.random_states(len(rows), n, seed=392 + n)
+    circ = Circuit(ops, n, P, F, path="stream")
+    tp, tx, tg = (torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in (p, x, cot))
+    for s0 in (None, states):
         note(f"ordered probs n={n} layers={layers} B={B} psi0={s0 is not None}")
-        dpr, _, Er = oracle.vjp(ops, n, p, x, cot, psi0=s0)
-        _, st = oracle.forward(ops, n, p, x, want_state=True, psi0=s0)
-        for training in (False, True):
-            r = run_ex(torch, ops, n, P, F, p, x, s0, path="stream", training=training)
-            check(r["E"], Er, E_TOL, "E")
-            check(r["probs"], np.abs(st) ** 2, P_TOL, "probs")
-        dp, _ = r["circ"].backward(r["p"], r["x"], torch.from_numpy(cot).cuda(), r["ws"])
-        err = np.max(np.abs(dp.cpu().numpy() - dpr), axis=1)
+        ts = None
+        if s0 is not None:
+            ts = torch.from_numpy(s0).cuda()[torch.arange(B) % len(rows)]
+            ts[rows] = torch.from_numpy(s0).cuda()
+        dpr, _, Er = oracle.vjp(ops, n, p[rows], x[rows], cot[rows], psi0=s0)
+        _, st = oracle.forward(ops, n, p[rows], x[rows], want_state=True, psi0=s0)
+        E, pr = circ.forward_ex(tp, tx, ts, probs=True)
+        E2, pr2, ws = circ.forward_ex(tp, tx, ts, probs=True, training=True)
+        dp, _ = circ.backward(tp, tx, tg, ws)
+        E1, pr1 = circ.forward_ex(tp[:1], tx[:1], None if ts is None else ts[:1], probs=True)
+        torch.cuda.synchronize()
+        assert torch.equal(E, E2) and torch.equal(pr, pr2)
+        if n < 20:
+            assert torch.equal(E1, E[:1]) and torch.equal(pr1, pr[:1])
+        check(E[rows].cpu().numpy(), Er, E_TOL, "E")
+        check(pr[rows].cpu().numpy(), np.abs(st) ** 2, P_TOL, "probs")
+        err = np.max(np.abs(dp[rows].cpu().numpy() - dpr), axis=1)
         assert np.all(err <= G_REL * np.max(np.abs(dpr), axis=1)
-                      + G_FLOOR * np.sum(np.abs(cot), axis=1)), err
+                      + G_FLOOR * np.sum(np.abs(cot[rows]), axis=1)), err
 
 
 @pytest.mark.parametrize("n,path", [(5, "auto"), (10, "auto"), (14, "stream")])
